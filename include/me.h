@@ -175,7 +175,9 @@ typedef struct {
     double avg_factor, sym_factor;
     double flops_amp_lane;     /* algorithmic flops of the amplitude kernel per (event, helicity) */
     double flops_amp_exec_lane;/* flops it executes (above when segment kernels recompute currents) */
-    int n_partial_slots;       /* partial jamp slots per (event, helicity) (0: jamps written directly) */
+    int n_partial_slots;       /* partial jamp slots per (event, helicity) of the segment kernels (mixed forms;
+                                  0: none).  Processes that have them run batches of more than one chunk on
+                                  two internal streams, in every precision */
     double flops_colour_lane;  /* algorithmic flops of the colour sum per (event, helicity) */
     int64_t bytes_resident;    /* device bytes held by the handle (tables) */
     int64_t bytes_per_event_scratch; /* jamp scratch per event (per stream in use) */

@@ -43,6 +43,7 @@ def build(verbose=True, jobs=None, names=None):
     generate(names)
     srcs = [os.path.join(CSRC, "me_abi.cpp")]
     srcs += [os.path.join(GEN, f"proc_{n}.hip") for n in SUPPORTED]
+    srcs += sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.startswith("rec_") and f.endswith(".hip"))
     # segment kernels of the large processes live in files of their own
     srcs += sorted(os.path.join(GEN, f) for f in os.listdir(GEN)
                    if f.endswith(".hip") and "_amp_seg" in f and f.split("_amp_seg")[0][5:] in SUPPORTED)

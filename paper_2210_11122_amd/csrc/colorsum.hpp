@@ -38,9 +38,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "flows.hpp"
+#include "helas.hpp"
+
 namespace me {
 
-typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -58,14 +60,7 @@ __device__ __forceinline__ float max_lane_groups(float x)
     return x;
 }
 
-// tile counts of the block upper-triangular colour matrix
-__host__ __device__ constexpr int cs64_tiles(int nc)
-{
-    int n = 0;
-    for (int mt = 0; mt < (nc + 15) / 16; ++mt)
-        for (int kt = 4 * mt; kt < (nc + 3) / 4; ++kt) ++n;
-    return n;
-}
+// tile count of the block upper-triangular colour matrix in the mixed forms
 __host__ __device__ constexpr int cs16_tiles(int nc)
 {
     int n = 0;
@@ -187,102 +182,96 @@ __device__ __forceinline__ double colour_sum_regs(const double* Jr, const double
         return csn<NC>([&](int c, int ri) { return Jr[2 * c + ri]; }, aop);
 }
 
-// One (16-event tile, helicity) column block of the FP64 form: returns this lane's share of
-// D * |M_h|^2 for event column i (the four lane groups' shares add up to it).  load(c, ri) gives
-// the jamp of colour c (re/im) of this lane's column.  A: the tile operands in registers when
-// AREG, else read from aop.
-template <int NC, bool AREG, class Load, bool ALDS = false>
-__device__ __forceinline__ double cs64_column(const Load& load, const double* A, const double* aop, int lane)
+// 24 and 120 flows (gg -> tt~gg, gg -> tt~ggg) in FP64: the colour matrix in its block form
+// (flows.hpp), D |M_h|^2 = sum over re/im and over the eight blocks of z^T B z, as scalar fused
+// multiply-adds on one lane's own jamps.  The blocks leave 80 (1808) of the 576 (14400) products of
+// the full matrix, and their symmetry 52 (964), so the sum is cheaper here than as matrix-core
+// tiles of the full matrix (which took 64 (512) 16x16x4 tiles per 64 events), and needs no exchange
+// between lanes.  tab: per block its upper triangle, off-diagonal entries doubled (me_abi.cpp,
+// block_table).  The rounding sequence is fixed: no contraction beyond the written ones.
+template <int NG, class Get>
+__device__ __forceinline__ double colour_blocks_part(const Get& x, const double* __restrict__ tab)
 {
-    if constexpr (NC == 1) {
-        // no tile for a 1x1 matrix: lane group 0 holds the whole value
-        return (lane >> 4) == 0 ? cs1((double)load(0, 0), (double)load(0, 1), aop[0]) : 0.0;
-    }
-    if constexpr (NC == 2) {
-        return (lane >> 4) == 0 ? cs2((double)load(0, 0), (double)load(0, 1), (double)load(1, 0), (double)load(1, 1), aop)
-                                : 0.0;
-    }
-    if constexpr (NC > 2 && NC <= 6) {
-        return (lane >> 4) == 0 ? csn<NC>([&](int c, int ri) { return (double)load(c, ri); }, aop) : 0.0;
-    }
-    constexpr int MT = (NC + 15) / 16, KT = (NC + 3) / 4;
-    // the real/imaginary loop stays rolled for the large matrices (register pressure)
-    constexpr int RI_UNROLL = NC > 24 ? 1 : 2;
-    const int g = lane >> 4;
-    double part_h = 0.0;
-#pragma unroll RI_UNROLL
-    for (int ri = 0; ri < 2; ++ri) {
-        // this lane's B elements: colours c = 4 kt + g, which are also its D rows
-        double b[KT];
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt) {
-            const int c = 4 * kt + g;
-            b[kt] = (c < NC) ? (double)load(c, ri) : 0.0;
-        }
-        int q = 0;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            // operands from LDS (ALDS): read tile row by tile row, not all at once
-            if constexpr (ALDS) __asm__ volatile("" ::: "memory");
-            const double* ap = ALDS ? aop : opaque(aop);
-            v4d d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int kt = 4 * mt; kt < KT; ++kt, ++q) {
-                const double a = AREG ? A[q] : ap[q * 64 + lane];
-                d = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[kt], d, 0, 0, 0);
+#pragma clang fp contract(off)
+    constexpr int NO = FlowBlocks<NG>::NO, NP = flow_blocks<NG>.n_pair;
+    double y[4][NO];
+    static_for<NO>([&](auto O) {
+        const double m00 = x(std::integral_constant<int, flow_blocks<NG>.member[O][0][0]>{}),
+                     m10 = x(std::integral_constant<int, flow_blocks<NG>.member[O][1][0]>{}),
+                     m01 = x(std::integral_constant<int, flow_blocks<NG>.member[O][0][1]>{}),
+                     m11 = x(std::integral_constant<int, flow_blocks<NG>.member[O][1][1]>{});
+        const double a = m00 + m10, b = m00 - m10, c = m01 + m11, d = m01 - m11;
+        y[0][O] = a + c;
+        y[1][O] = a - c;
+        y[2][O] = b + d;
+        y[3][O] = b - d;
+    });
+    double q = 0.0;
+    int t = 0;
+    static_for<8>([&](auto K) {
+        constexpr int s = K / 2, rho = K % 2 ? -1 : 1, chi = (s == 0 || s == 3) ? 1 : -1;
+        constexpr int nz = NP + (rho == chi ? flow_blocks<NG>.n_fix : 0);
+        double z[nz];
+        static_for<nz>([&](auto I) {
+            if constexpr (I < NP) {
+                const double u = y[s][flow_blocks<NG>.pair[I][0]], v = y[s][flow_blocks<NG>.pair[I][1]];
+                z[I] = rho * chi > 0 ? u + v : u - v;
+            } else {
+                z[I] = y[s][flow_blocks<NG>.fix[I - NP]];
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (4 * mt + r < KT) part_h += b[4 * mt + r] * d[r];
-        }
-    }
-    return part_h;
+        });
+        static_for<nz>([&](auto I) {
+            double r = tab[t++] * z[I];
+            static_for<nz - I - 1>([&](auto J) { r = __builtin_fma(tab[t++], z[I + 1 + J], r); });
+            q = __builtin_fma(z[I], r, q);
+        });
+    });
+    return q;
+}
+template <int NG>
+__device__ __forceinline__ double colour_blocks(const cx<double> (&J)[factorial(NG)], const double* __restrict__ tab)
+{
+#pragma clang fp contract(off)
+    const double re = colour_blocks_part<NG>([&](auto F) { return J[F].r; }, tab);
+    const double im = colour_blocks_part<NG>([&](auto F) { return J[F].i; }, tab);
+    double v = re + im;
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
-#ifndef CS64_A_IN_LDS
-#define CS64_A_IN_LDS 1
-#endif
-// A operands, per lane, in the kernel's tile order (mt ascending, then kt >= 4 mt):
-// aop[q * 64 + l] = A[16 mt + l % 16][4 kt + l / 16].
+// The separate colour sum in FP64: one lane per event, the good helicities of the group
+// blockIdx.y in turn.  aop: the 16x4 tile table (up to six flows) or the block table.
 template <int NC>
-__global__ __launch_bounds__(256) void colour_sum_f64(const double* __restrict__ J, int64_t ld, int n_good,
-                                                      int hel_per_group, int64_t n_evt,
-                                                      const double* __restrict__ aop, double scale_hel,
-                                                      double scale_avg, double* __restrict__ out,
-                                                      double* __restrict__ out_hel, double* __restrict__ part)
+__global__ __launch_bounds__(NC > 6 ? 64 : 256) void colour_sum_f64(
+    const double* __restrict__ J, int64_t ld, int n_good, int hel_per_group, int64_t n_evt,
+    const double* __restrict__ aop, double scale_hel, double scale_avg, double* __restrict__ out,
+    double* __restrict__ out_hel, double* __restrict__ part)
 {
-    constexpr int NT = cs64_tiles(NC);
-    constexpr bool AREG = NT <= 24;
-    // the large matrix: its operands staged in LDS once per workgroup (NT * 512 B), instead of
-    // each wave reading them through the caches for every tile
-    constexpr bool ALDS = !AREG && CS64_A_IN_LDS;
-    __shared__ double As[ALDS ? NT * 64 : 1];
-    if constexpr (ALDS) {
-        for (int k = threadIdx.x; k < NT * 64; k += 256) As[k] = aop[k];
-        __syncthreads();
-    }
-    const int lane = threadIdx.x & 63;
-    const int64_t e0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16;
-    if (e0 >= n_evt) return;
-    const int i = lane & 15, g = lane >> 4;
-    const int64_t e = e0 + i;
-    const bool valid = e < n_evt;
-    const int64_t ec = valid ? e : n_evt - 1;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n_evt) return;
     const int h0 = blockIdx.y * hel_per_group, h1 = min(n_good, h0 + hel_per_group);
-    double A[AREG ? NT : 1];
-    if (AREG) {
-#pragma unroll
-        for (int q = 0; q < NT; ++q) A[q] = aop[q * 64 + lane];
-    }
     double me = 0.0;
     for (int h = h0; h < h1; ++h) {
-        const double* Jh = J + (int64_t)h * (2 * NC) * ld;
-        const auto load = [&](int c, int ri) { return Jh[(int64_t)(2 * c + ri) * ld + ec]; };
-        double part_h = sum_lane_groups(cs64_column<NC, AREG, decltype(load), ALDS>(load, A, ALDS ? As : aop, lane));
-        if (out_hel && g == 0 && valid) out_hel[e * n_good + h] = part_h * scale_hel;
-        me += part_h;
+        const double* Jh = J + (int64_t)h * (2 * NC) * ld + e;
+        double me_h;
+        if constexpr (NC <= 6) {
+            double Jr[2 * NC];
+#pragma unroll
+            for (int s = 0; s < 2 * NC; ++s) Jr[s] = Jh[(int64_t)s * ld];
+            me_h = colour_sum_regs<NC>(Jr, aop);
+        } else {
+            constexpr int NG = NC == 24 ? 4 : 5;
+            static_assert(NC == factorial(NG), "24 or 120 flows");
+            // the real and imaginary rows in turn
+            const double re = colour_blocks_part<NG>([&](auto F) { return Jh[(int64_t)(2 * F) * ld]; }, aop);
+            const double im = colour_blocks_part<NG>([&](auto F) { return Jh[(int64_t)(2 * F + 1) * ld]; }, aop);
+            me_h = re + im;
+            asm volatile("" : "+v"(me_h));
+        }
+        if (out_hel) out_hel[e * n_good + h] = me_h * scale_hel;
+        me += me_h;
     }
-    if (g == 0 && valid) cs_store(me, e, n_evt, scale_avg, out, part);
+    cs_store(me, e, n_evt, scale_avg, out, part);
 }
 
 // 16-bit element types of the mixed colour sum
@@ -421,24 +410,6 @@ __global__ __launch_bounds__(256) void colour_sum_h16(const float* __restrict__ 
 // load the B operands from the other lanes' slots and run the same column body as the separate
 // kernels (so each |M_h|^2 is bitwise the same).  Returns this lane's event's D * |M_h|^2.  The
 // caller must have completed all jamp updates of the wave (a barrier) before the call.
-template <int NC, class JT>
-__device__ __forceinline__ double colour_sum_lds(const JT* Jl, const double* __restrict__ aop, int lane)
-{
-    constexpr int NT = cs64_tiles(NC);
-    static_assert(NT <= 24, "operands held in registers");
-    const int i = lane & 15, g = lane >> 4;
-    double A[NT];
-#pragma unroll
-    for (int q = 0; q < NT; ++q) A[q] = aop[q * 64 + lane];
-    double mine = 0.0;
-#pragma unroll 1
-    for (int j = 0; j < 4; ++j) {  // events 16 j .. 16 j + 15
-        const auto load = [&](int c, int ri) { return Jl[(2 * c + ri) * 64 + 16 * j + i]; };
-        const double part_h = sum_lane_groups(cs64_column<NC, true>(load, A, aop, lane));
-        if (g == j) mine = part_h;  // lane 16 g + i is event 16 g + i
-    }
-    return mine;
-}
 template <int NC, class T>
 __device__ __forceinline__ double colour_sum_lds_h16(const float* Jl, const typename T::elem* __restrict__ aop,
                                                      const typename T::elem* __restrict__ aop_lo, uint64_t lo_mask,

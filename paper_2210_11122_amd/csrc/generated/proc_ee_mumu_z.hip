@@ -77,9 +77,7 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
 #pragma unroll
         for (int s = 0; s < 2 * NC; ++s) Js[s * 64 + lane] = Jr[s];
         __syncthreads();
-        if constexpr (sizeof(R) == 8)
-            me_h = colour_sum_lds<NC>(Js, static_cast<const double*>(fc.aop), lane);
-        else if (fc.form == ME_MIXED_BF16)
+        if (fc.form == ME_MIXED_BF16)
             me_h = colour_sum_lds_h16<NC, Bf16Terms>(Js, static_cast<const __bf16*>(fc.aop), static_cast<const __bf16*>(fc.aop_lo), fc.lo_mask, lane);
         else
             me_h = colour_sum_lds_h16<NC, Fp16Terms>(Js, static_cast<const _Float16*>(fc.aop), static_cast<const _Float16*>(fc.aop), 0, lane);
@@ -190,7 +188,7 @@ static const int final_massive[NPAR - 2] = {0, 0};
 static const int orderings[] = {0};
 static const int diagram_lines[] = {12, 12};
 template <class R>
-static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st)
+static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, const HelicityGroups& hg, hipStream_t st)
 {
     if (fc && (chan || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
     const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
@@ -222,6 +220,7 @@ const ProcessDesc* process_ee_mumu_z()
         proc_ee_mumu_z::colour_num, 1, proc_ee_mumu_z::final_massive, proc_ee_mumu_z::orderings, 0,
         2, 2, 534.0, 534.0, proc_ee_mumu_z::NSLOT,
         proc_ee_mumu_z::diagram_lines, 1, 1, 1, 1, 65536,
+        nullptr, 0,
         proc_ee_mumu_z::launch<double>, proc_ee_mumu_z::launch<float>,
     };
     return &d;

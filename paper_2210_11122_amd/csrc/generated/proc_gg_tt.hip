@@ -95,9 +95,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 4 
 #pragma unroll
         for (int s = 0; s < 2 * NC; ++s) Js[s * 64 + lane] = Jr[s];
         __syncthreads();
-        if constexpr (sizeof(R) == 8)
-            me_h = colour_sum_lds<NC>(Js, static_cast<const double*>(fc.aop), lane);
-        else if (fc.form == ME_MIXED_BF16)
+        if (fc.form == ME_MIXED_BF16)
             me_h = colour_sum_lds_h16<NC, Bf16Terms>(Js, static_cast<const __bf16*>(fc.aop), static_cast<const __bf16*>(fc.aop_lo), fc.lo_mask, lane);
         else
             me_h = colour_sum_lds_h16<NC, Fp16Terms>(Js, static_cast<const _Float16*>(fc.aop), static_cast<const _Float16*>(fc.aop), 0, lane);
@@ -216,7 +214,7 @@ static const int final_massive[NPAR - 2] = {1, 1};
 static const int orderings[] = {0, 1, 1, 0};
 static const int diagram_lines[] = {10, 6, 12};
 template <class R>
-static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st)
+static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, const HelicityGroups& hg, hipStream_t st)
 {
     if (fc && (chan || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
     const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
@@ -246,6 +244,7 @@ const ProcessDesc* process_gg_tt()
         proc_gg_tt::colour_num, 3, proc_gg_tt::final_massive, proc_gg_tt::orderings, 2,
         3, 3, 835.0, 835.0, proc_gg_tt::NSLOT,
         proc_gg_tt::diagram_lines, 1, 1, 1, 0, 65536,
+        nullptr, 0,
         proc_gg_tt::launch<double>, proc_gg_tt::launch<float>,
     };
     return &d;

@@ -140,6 +140,8 @@ struct me_handle {
     int n_good = 0;
     signed char* d_hel_good = nullptr;
     int* d_hel_index = nullptr;  // helicity-combination index of each good helicity
+    int* d_hel_groups = nullptr;  // the good helicities by gluon helicities (HelicityGroups)
+    int n_hel_groups = 0;
     std::vector<signed char> h_hel_good;
     std::vector<double> hel_ratio;
     double* d_aop64 = nullptr;
@@ -181,7 +183,8 @@ struct ColourArgs {
 template <int NC>
 hipError_t launch_cs64(const double* J, const double* aop, const ColourArgs& a, hipStream_t st)
 {
-    hipLaunchKernelGGL((me::colour_sum_f64<NC>), dim3((unsigned)((a.n + 63) / 64), (unsigned)a.groups), dim3(256),
+    constexpr int T = NC > 6 ? 64 : 256;
+    hipLaunchKernelGGL((me::colour_sum_f64<NC>), dim3((unsigned)((a.n + T - 1) / T), (unsigned)a.groups), dim3(T),
                        0, st, J, a.ld, a.n_good, a.hel_per_group, a.n, aop, a.scale_hel, a.scale_avg, a.out, a.out_hel,
                        a.part);
     return hipGetLastError();
@@ -235,6 +238,15 @@ hipError_t colour_sum(const me_handle* h, int precision, const void* J, int64_t 
     if (e != hipSuccess || groups == 1) return e;
     hipLaunchKernelGGL(me::hel_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, groups, n, sa, out);
     return hipGetLastError();
+}
+
+// bytes of scratch per event for the jamps of n_hel helicities and what else the amplitude kernels
+// of this precision keep there
+size_t jamp_scratch(const me::ProcessDesc* P, int precision, int n_hel)
+{
+    if (precision != ME_FP64) return (size_t)n_hel * 2 * (P->nc + P->nslot) * sizeof(float);
+    const int slots = P->recursion ? 0 : P->nslot;
+    return ((size_t)n_hel * 2 * (P->nc + slots) + (P->aux_doubles ? (size_t)P->aux_doubles(n_hel) : 0)) * sizeof(double);
 }
 
 // helicity groups of the colour sum for launches of up to `chunk` events: enough
@@ -336,10 +348,31 @@ struct Selection {
     double *hel_me, *w;
 };
 
+// The helicity combinations hel (n x npar signs) by gluon helicities: rows of HelicityGroups.  Empty
+// for processes without a quark line between gluons.
+std::vector<int> helicity_group_table(const me::ProcessDesc* P, const signed char* hel, int n)
+{
+    std::vector<int> t;
+    if (P->coupling != 1 || P->n_order != P->npar - 2) return t;
+    std::map<int, size_t> row;
+    for (int k = 0; k < n; ++k) {
+        const signed char* l = hel + (size_t)k * P->npar;
+        int bits = 0;
+        for (int g = 0; g < P->npar - 2; ++g) bits |= (l[g < 2 ? g : g + 2] > 0 ? 1 : 0) << g;
+        auto it = row.find(bits);
+        if (it == row.end()) {
+            it = row.emplace(bits, t.size()).first;
+            t.insert(t.end(), {bits, -1, -1, -1, -1});
+        }
+        t[it->second + 1 + (l[2] > 0 ? 2 : 0) + (l[3] > 0 ? 1 : 0)] = k;
+    }
+    return t;
+}
+
 // amplitude kernel + colour sum (+ the optional per-event kernels) for events [0, n) of `mom`, in
 // chunks; scratch: jamps of `chunk` events (jamp_bytes_per_event each), then the helicity-group
 // partial sums
-int run_chunks(me_handle* h, int precision, const signed char* hel, int n_good, int hel_per_group, int groups,
+int run_chunks(me_handle* h, int precision, const signed char* hel, const me::HelicityGroups& hg, int n_good, int hel_per_group, int groups,
                int64_t chunk, size_t jamp_bytes_per_event, const double* mom, int64_t n, double* out, double* out_hel,
                void* scratch, hipStream_t st, bool timed = false, const Selection* sel = nullptr,
                const double* alphas = nullptr, const int* chan = nullptr, double* sde = nullptr)
@@ -375,18 +408,18 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, int n_good, 
             fcol.hsum_out = out + c0;
             fcol.hsum_scale = 1.0 / ((double)P->colour_den * P->avg);
             e = fp64 ? P->launch_f64(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<double*>(jamp), nullptr,
-                                     nullptr, &fcol, st)
+                                     nullptr, &fcol, hg, st)
                      : P->launch_f32(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<float*>(jamp), nullptr,
-                                     nullptr, &fcol, st);
+                                     nullptr, &fcol, hg, st);
             ta.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("amplitude kernel: ") + hipGetErrorString(e));
         } else if (fused) {
             // the amplitude kernel ends with the colour sum: D |M_h|^2 per (helicity, event) in the
             // jamp scratch, then the helicity sum in the separate kernels' order (same groups)
             e = fp64 ? P->launch_f64(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<double*>(jamp), nullptr,
-                                     nullptr, &fcol, st)
+                                     nullptr, &fcol, hg, st)
                      : P->launch_f32(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<float*>(jamp), nullptr,
-                                     nullptr, &fcol, st);
+                                     nullptr, &fcol, hg, st);
             ta.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("amplitude kernel: ") + hipGetErrorString(e));
             TimedLaunch tc(h, st, 1, timed);
@@ -397,8 +430,8 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, int n_good, 
             tc.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("helicity-sum kernel: ") + hipGetErrorString(e));
         } else {
-            e = fp64 ? P->launch_f64(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<double*>(jamp), ch, sde, nullptr, st)
-                     : P->launch_f32(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<float*>(jamp), ch, sde, nullptr, st);
+            e = fp64 ? P->launch_f64(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<double*>(jamp), ch, sde, nullptr, hg, st)
+                     : P->launch_f32(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<float*>(jamp), ch, sde, nullptr, hg, st);
             ta.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("amplitude kernel: ") + hipGetErrorString(e));
             TimedLaunch tc(h, st, 1, timed);
@@ -453,11 +486,65 @@ void free_handle(me_handle* h)
     }
     if (h->d_hel_good) (void)hipFree(h->d_hel_good);
     if (h->d_hel_index) (void)hipFree(h->d_hel_index);
+    if (h->d_hel_groups) (void)hipFree(h->d_hel_groups);
     if (h->d_aop64) (void)hipFree(h->d_aop64);
     if (h->d_aop16) (void)hipFree(h->d_aop16);
     if (h->d_aopb) (void)hipFree(h->d_aopb);
     if (h->d_aopb_lo) (void)hipFree(h->d_aopb_lo);
     delete h;
+}
+
+// The colour matrix of NG gluons in the block form of flows.hpp: for each block (in the order of
+// colour_blocks_part) its upper triangle, off-diagonal entries doubled.  With the block's basis
+// vectors v_i (z_i = v_i . J, of length |v_i|^2 = 8, or 4 for an orbit that the reversal keeps),
+// B_ij = v_i^T Chat v_j / (|v_i|^2 |v_j|^2): integers over 16, 32 or 64, exact.  False if Chat does
+// not have the symmetry (a mistake in the tables).
+template <int NG>
+bool block_table(const int* chat, std::vector<double>& tab)
+{
+    constexpr const me::FlowBlocks<NG>& F = me::flow_blocks<NG>;
+    constexpr int NC = me::FlowBlocks<NG>::NC;
+    std::vector<std::vector<int>> basis;   // all blocks' vectors
+    std::vector<int> block_of;
+    for (int b = 0; b < 8; ++b) {
+        const int s = b / 2, rho = b % 2 ? -1 : 1, c01 = s < 2 ? 1 : -1, c23 = s % 2 ? -1 : 1;
+        const int n = F.n_pair + (rho == c01 * c23 ? F.n_fix : 0);
+        for (int i = 0; i < n; ++i) {
+            std::vector<int> v(NC, 0);
+            auto add = [&](int o, int w) {
+                for (int g = 0; g < 2; ++g)
+                    for (int k = 0; k < 2; ++k) v[F.member[o][g][k]] += w * (g ? c01 : 1) * (k ? c23 : 1);
+            };
+            if (i < F.n_pair) {
+                add(F.pair[i][0], 1);
+                add(F.pair[i][1], rho * c01 * c23);
+            } else {
+                add(F.fix[i - F.n_pair], 1);
+            }
+            basis.push_back(v);
+            block_of.push_back(b);
+        }
+    }
+    if ((int)basis.size() != NC) return false;
+    tab.clear();
+    for (int i = 0; i < NC; ++i) {
+        std::vector<double> cv(NC, 0.0);
+        double ni = 0.0;
+        for (int r = 0; r < NC; ++r) {
+            ni += basis[i][r] * basis[i][r];
+            for (int c = 0; c < NC; ++c) cv[r] += (double)chat[r * NC + c] * basis[i][c];
+        }
+        for (int j = 0; j < NC; ++j) {
+            double x = 0.0, nj = 0.0;
+            for (int r = 0; r < NC; ++r) x += cv[r] * basis[j][r], nj += basis[j][r] * basis[j][r];
+            if (block_of[j] != block_of[i]) {
+                if (x != 0.0) return false;
+            } else if (j >= i) {
+                tab.push_back((j > i ? 2.0 : 1.0) * x / (ni * nj));
+            }
+        }
+    }
+    return (int)tab.size() == me::block_entries<NG>();
 }
 
 // colour matrix as matrix-core A operands, block upper-triangular (see colorsum.hpp for the
@@ -476,6 +563,9 @@ int upload_colour(me_handle* h)
     for (int mt = 0; mt < MT; ++mt)
         for (int kt = 4 * mt; kt < KT; ++kt)
             for (int l = 0; l < 64; ++l) a64.push_back(A(16 * mt + l % 16, 4 * kt + l / 16));
+    // FP64 with 24 or 120 flows: the block form instead
+    if ((NC == 24 && !block_table<4>(P->colour_num, a64)) || (NC == 120 && !block_table<5>(P->colour_num, a64)))
+        return fail(ME_EINVAL, "the colour matrix lacks the symmetry of the block form");
     std::vector<_Float16> a16;
     std::vector<__bf16> ab, ablo;
     uint64_t lo_mask = 0;
@@ -528,15 +618,18 @@ int helicity_prepass(me_handle* h, hipStream_t st)
     const int64_t n = PREPASS_EVENTS;
     const double sqrt_s = P->coupling ? 1500.0 : 500.0;
     signed char* d_all = nullptr;
+    int* d_groups = nullptr;
+    const std::vector<int> all_groups = helicity_group_table(P, all.data(), nhel);
     double *d_mom = nullptr, *d_out = nullptr, *d_hel = nullptr, *d_jamp = nullptr;
-    const size_t jamp_per_event = (size_t)nhel * 2 * (P->nc + P->nslot) * sizeof(double);
+    const size_t jamp_per_event = jamp_scratch(P, ME_FP64, nhel);
     const int64_t pchunk =
         std::min<int64_t>(n, std::max<int64_t>(64, (int64_t)((size_t(512) << 20) / jamp_per_event) / 64 * 64));
     int groups = 1, hpg = 1;
     helicity_groups(P, nhel, pchunk, &groups, &hpg);
     const size_t jbytes = (jamp_per_event + groups * sizeof(double)) * pchunk;
     int rc = ME_OK;
-    if (hipMalloc(&d_all, all.size()) != hipSuccess || hipMalloc(&d_mom, n * npar * 4 * sizeof(double)) != hipSuccess ||
+    if (hipMalloc(&d_all, all.size()) != hipSuccess ||
+        (!all_groups.empty() && hipMalloc(&d_groups, all_groups.size() * sizeof(int)) != hipSuccess) || hipMalloc(&d_mom, n * npar * 4 * sizeof(double)) != hipSuccess ||
         hipMalloc(&d_out, n * sizeof(double)) != hipSuccess ||
         hipMalloc(&d_hel, (size_t)n * nhel * sizeof(double)) != hipSuccess || hipMalloc(&d_jamp, jbytes) != hipSuccess) {
         rc = fail(ME_ENOMEM, "hipMalloc for the helicity pre-pass failed");
@@ -544,10 +637,13 @@ int helicity_prepass(me_handle* h, hipStream_t st)
     std::vector<double> out(n), hel((size_t)n * nhel);
     if (rc == ME_OK && hipMemcpyAsync(d_all, all.data(), all.size(), hipMemcpyHostToDevice, st) != hipSuccess)
         rc = fail(ME_EHIP, "upload of the helicity table failed");
+    if (rc == ME_OK && d_groups &&
+        hipMemcpyAsync(d_groups, all_groups.data(), all_groups.size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess)
+        rc = fail(ME_EHIP, "upload of the helicity groups failed");
     if (rc == ME_OK && rambo(h, PREPASS_SEED, std::max(sqrt_s, 2.0 * final_mass_sum(h) + 1.0), 0, n, d_mom, st) != hipSuccess)
         rc = fail(ME_EHIP, "pre-pass RAMBO launch failed");
     if (rc == ME_OK)
-        rc = run_chunks(h, ME_FP64, d_all, nhel, hpg, groups, pchunk, jamp_per_event, d_mom, n, d_out, d_hel, d_jamp, st);
+        rc = run_chunks(h, ME_FP64, d_all, {d_groups, (int)all_groups.size() / 5}, nhel, hpg, groups, pchunk, jamp_per_event, d_mom, n, d_out, d_hel, d_jamp, st);
     if (rc == ME_OK) {
         if (hipMemcpyAsync(out.data(), d_out, n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipMemcpyAsync(hel.data(), d_hel, hel.size() * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -555,6 +651,7 @@ int helicity_prepass(me_handle* h, hipStream_t st)
             rc = fail(ME_EHIP, "pre-pass copy-back failed");
     }
     if (d_all) (void)hipFree(d_all);
+    if (d_groups) (void)hipFree(d_groups);
     if (d_mom) (void)hipFree(d_mom);
     if (d_out) (void)hipFree(d_out);
     if (d_hel) (void)hipFree(d_hel);
@@ -581,7 +678,16 @@ int helicity_prepass(me_handle* h, hipStream_t st)
     if (hipMemcpy(h->d_hel_good, h->h_hel_good.data(), h->h_hel_good.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(h->d_hel_index, index.data(), index.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
         return fail(ME_EHIP, "upload of the helicity list failed");
-    h->bytes_resident += h->h_hel_good.size() + index.size() * sizeof(int);
+    const std::vector<int> groups_table = helicity_group_table(P, h->h_hel_good.data(), h->n_good);
+    h->n_hel_groups = (int)groups_table.size() / 5;
+    if (!groups_table.empty()) {
+        if (hipMalloc(&h->d_hel_groups, groups_table.size() * sizeof(int)) != hipSuccess)
+            return fail(ME_ENOMEM, "hipMalloc of the helicity groups failed");
+        if (hipMemcpy(h->d_hel_groups, groups_table.data(), groups_table.size() * sizeof(int), hipMemcpyHostToDevice) !=
+            hipSuccess)
+            return fail(ME_EHIP, "upload of the helicity groups failed");
+    }
+    h->bytes_resident += h->h_hel_good.size() + (index.size() + groups_table.size()) * sizeof(int);
     return ME_OK;
 }
 
@@ -637,8 +743,7 @@ me_handle* me_create(const char* process, const double* masses, int n_masses, co
         g_err = msg;
         return nullptr;
     }
-    const size_t rsize = (precision == ME_FP64) ? sizeof(double) : sizeof(float);
-    h->jamp_bytes_per_event = (size_t)h->n_good * 2 * (P->nc + P->nslot) * rsize;
+    h->jamp_bytes_per_event = jamp_scratch(P, precision, h->n_good);
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) total_b = size_t(64) << 30;
     h->scratch_cap = std::max(SCRATCH_MIN, std::min<size_t>(SCRATCH_EVENTS * h->jamp_bytes_per_event, total_b / 8));
@@ -762,7 +867,7 @@ int sigma_piped(me_handle* h, const double* momenta, int64_t n_evt, double* out,
     for (int64_t c0 = 0; c0 < n_evt && rc == ME_OK; c0 += chunk, ++k) {
         const int64_t nc = std::min(chunk, n_evt - c0);
         const int i = (int)(k & 1);
-        rc = run_chunks(h, h->precision, h->d_hel_good, h->n_good, h->hel_per_group, h->groups, chunk,
+        rc = run_chunks(h, h->precision, h->d_hel_good, {h->d_hel_groups, h->n_hel_groups}, h->n_good, h->hel_per_group, h->groups, chunk,
                         h->jamp_bytes_per_event, momenta + c0 * npar * 4, nc, out + c0, nullptr, scr[i], hp->s[i],
                         h->profiling, nullptr, alphas ? alphas + c0 : nullptr);
     }
@@ -832,7 +937,7 @@ int sigma_impl(me_handle* h, const double* momenta, int64_t n_evt, double* out_m
     double* sde = chan ? reinterpret_cast<double*>(static_cast<char*>(scratch) +
                                                    (size_t)chunk * (h->bytes_per_event + sel_bytes))
                        : nullptr;
-    return run_chunks(h, h->precision, h->d_hel_good, h->n_good, h->hel_per_group, h->groups, chunk,
+    return run_chunks(h, h->precision, h->d_hel_good, {h->d_hel_groups, h->n_hel_groups}, h->n_good, h->hel_per_group, h->groups, chunk,
                       h->jamp_bytes_per_event, momenta, n_evt, out_me2, out_hel, scratch, st, h->profiling,
                       sel_in ? &sel : nullptr, alphas, chan, sde);
 }
@@ -998,7 +1103,7 @@ int me_sigma_noalloc(me_handle* h, const double* momenta, int64_t n_evt, double*
     const int64_t n_chunks = (n_evt + cap - 1) / cap;
     const int64_t chunk = ((n_evt + n_chunks - 1) / n_chunks + 63) / 64 * 64;
     const size_t jamp_per_event = fused ? per_event : h->jamp_bytes_per_event;
-    return run_chunks(h, h->precision, h->d_hel_good, h->n_good, h->hel_per_group, h->groups, chunk, jamp_per_event,
+    return run_chunks(h, h->precision, h->d_hel_good, {h->d_hel_groups, h->n_hel_groups}, h->n_good, h->hel_per_group, h->groups, chunk, jamp_per_event,
                       momenta, n_evt, out_me2, nullptr, scr, static_cast<hipStream_t>(stream));
 }
 

@@ -25,13 +25,22 @@ struct FusedColour {
     int hel_per_group;
 };
 
+// The good helicities of a quark-line process by gluon helicities, for kernels whose workgroup
+// evaluates the four quark spin configurations of one gluon configuration.  table (device):
+// n rows of 5: the gluons' signs (bit i: gluon i has helicity +), then the index among the good
+// helicities of the quark spins (-,-), (-,+), (+,-), (+,+), or -1 where that combination is not good.
+struct HelicityGroups {
+    const int* table;
+    int n;
+};
+
 // fc: null, or the fused colour sum (then chan must be null)
 typedef hipError_t (*amp_launch_f64)(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel,
                                      int n_good, double mt, double g, double* jamp, const int* chan, double* sde,
-                                     const FusedColour* fc, hipStream_t st);
+                                     const FusedColour* fc, const HelicityGroups& hg, hipStream_t st);
 typedef hipError_t (*amp_launch_f32)(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel,
                                      int n_good, double mt, double g, float* jamp, const int* chan, double* sde,
-                                     const FusedColour* fc, hipStream_t st);
+                                     const FusedColour* fc, const HelicityGroups& hg, hipStream_t st);
 
 struct ProcessDesc {
     const char* name;
@@ -58,9 +67,23 @@ struct ProcessDesc {
     int hel_sum_in_kernel;     // ... and the helicity sum (FusedColour.hsum_out; at most 16 good helicities)
     int64_t lane_min_events;   // batches from this size can take the kernel with one lane per event, which
                                // also sums the helicities: FP64, and mixed forms of one flow (0: none)
+    int64_t (*aux_doubles)(int n_hel);  // doubles per event that the FP64 launch needs after the jamps (null: none)
+    int recursion;             // the FP64 jamps come from the recursion, without partial slots
     amp_launch_f64 launch_f64;
     amp_launch_f32 launch_f32;
 };
+
+// FP64 colour-flow amplitudes by recursion (rec_*.hip); the arguments of launch_f64
+namespace rec4 {
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
+                  double* jamp, const FusedColour* fc, hipStream_t st);
+}
+// gg -> tt~ggg: jamp is followed by aux_doubles(n_good) doubles per event of the padded batch (ld)
+namespace rec5 {
+int64_t aux_doubles(int n_good);
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, int n_good, double mt,
+                  double gs, double* jamp, hipStream_t st);
+}
 
 const ProcessDesc* process_ee_mumu();
 const ProcessDesc* process_gg_tt();

@@ -117,6 +117,9 @@ LANE_HOIST_EXT = True
 # registers.  Measured with the hoisted states: FP64 77 us at two waves, 79 at three; FP32 90 us at
 # two, 79 at three
 LANE_MIN_WAVES = (2, 3)
+# processes whose FP64 colour-flow amplitudes come from the colour-ordered recursion (csrc/rec_*.hip,
+# namespace): the FP64 diagram program then runs for the channel weights alone and keeps no jamps
+RECURSION = {"gg_ttgg": "rec4", "gg_ttggg": "rec5"}
 ALL_PROCESSES = ["ee_mumu", "gg_tt", "gg_ttg", "gg_ttgg", "gg_ttggg", "gg_gg", "ee_mumu_z"]
 # electroweak constants of ee -> mumu with Z exchange: M_Z, Gamma_Z, M_W [GeV]
 EW_MZ, EW_WZ, EW_MW = 91.188, 2.441404, 80.419
@@ -814,12 +817,15 @@ class Process:
                              f"const signed char* hel, int n_good, double mt, double gs, {R}* jamp, const int* chan, "
                              "double* sde, hipStream_t st, int64_t blocks)")
                     F.append("{")
-                    F.append("    if (chan)")
+                    # FP64 with the recursion: the channel weights only
+                    weights_only = R == "double" and nm in RECURSION
+                    F.append("    if (!chan) return hipErrorInvalidValue;" if weights_only else "    if (chan)")
                     F.append(f"        hipLaunchKernelGGL(({kname}<{R}, true>), dim3((unsigned)blocks), dim3({64 * wg}), 0, st, mom, "
                              "n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde);")
-                    F.append("    else")
-                    F.append(f"        hipLaunchKernelGGL(({kname}<{R}, false>), dim3((unsigned)blocks), dim3({64 * wg}), 0, st, mom, "
-                             "n_evt, ld, hel, n_good, mt, gs, jamp, nullptr, nullptr);")
+                    if not weights_only:
+                        F.append("    else")
+                        F.append(f"        hipLaunchKernelGGL(({kname}<{R}, false>), dim3((unsigned)blocks), dim3({64 * wg}), 0, st, mom, "
+                                 "n_evt, ld, hel, n_good, mt, gs, jamp, nullptr, nullptr);")
                     F.append("    return hipGetLastError();")
                     F.append("}")
                 F += ["}  // namespace", "}  // namespace me"]
@@ -847,7 +853,7 @@ class Process:
         L.append("template <class R>")
         L.append("static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, "
                  "int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, "
-                 "hipStream_t st)")
+                 "const HelicityGroups& hg, hipStream_t st)")
         L.append("{")
         if not fused:
             L.append("    if (fc) return hipErrorInvalidValue;  // no fused colour sum for this process")
@@ -859,6 +865,11 @@ class Process:
         L.append(f"    constexpr int WG = sizeof(R) == 8 ? {g64} : {g32};  // waves (helicities) per workgroup")
         L.append("    int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);")
         L.append("    if (blocks == 0) return hipSuccess;")
+        if self.segments and nm in RECURSION:
+            L.append("    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for")
+            L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, n_good, mt, gs, jamp, st);")
+            L.append("        if (err != hipSuccess || !chan) return err;")
+            L.append("    }")
         for kname, _, _, _ in kernels:
             if self.segments:
                 L.append("    {")
@@ -887,8 +898,16 @@ class Process:
                     else:
                         L.append("        return hipErrorInvalidValue;  // below the lane kernel's batch size: no such kernel")
                     L.append("    }")
-                L.append("    if (chan)")
                 tail = ", none" if fused else ""
+                if nm in RECURSION:
+                    L.append("    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for")
+                    L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);")
+                    L.append("        if (err != hipSuccess || !chan) return err;")
+                    L.append(f"        hipLaunchKernelGGL(({kname}<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
+                             f"ld, hel, n_good, mt, gs, jamp, chan, sde{tail});")
+                    L.append("    } else if (chan)")
+                else:
+                    L.append("    if (chan)")
                 L.append(f"        hipLaunchKernelGGL(({kname}<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
                          f"ld, hel, n_good, mt, gs, jamp, chan, sde{tail});")
                 L.append("    else")
@@ -896,6 +915,8 @@ class Process:
                 L.append(f"        hipLaunchKernelGGL(({kname}<R, false>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
                          f"ld, hel, n_good, mt, gs, jamp, nullptr, nullptr{tail});")
         if self.segments:
+            if nm in RECURSION:
+                L.append("    if constexpr (sizeof(R) == 4)")
             L.append("    hipLaunchKernelGGL(reduce_kernel<R>, dim3((unsigned)((n_evt + 255) / 256), (unsigned)n_good), "
                      "dim3(256), 0, st, jamp, ld, n_good, n_evt);")
         L.append("    return hipGetLastError();")
@@ -911,6 +932,7 @@ class Process:
         L.append(f"        {self.n_diagrams}, {self.n_amplitudes}, {fl}.0, {self.flops_exec}.0, proc_{nm}::NSLOT,")
         L.append(f"        proc_{nm}::diagram_lines, {nlines}, {0 if self.lines is None else 1}, {1 if fused else 0}, "
                  f"{1 if fused and nm in HEL_SUM_IN_KERNEL else 0}, {LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0},")
+        L.append(f"        {'rec5::aux_doubles' if nm == 'gg_ttggg' else 'nullptr'}, {1 if nm in RECURSION else 0},")
         L.append(f"        proc_{nm}::launch<double>, proc_{nm}::launch<float>,")
         L.append("    };")
         L.append("    return &d;")
@@ -929,6 +951,8 @@ class Process:
         sums of the segments before them."""
         L = []
         hsum = fused and self.name in HEL_SUM_IN_KERNEL
+        # the FP64 jamps come from the recursion: the FP64 instance sums the channel weights only
+        rec = self.name in RECURSION
         # HS: the instance that also sums the helicities (its workgroup holds an event block's
         # good helicities; the LDS it needs for that is only in this instance)
         L.append("template <class R, bool SDE, bool HS = false>" if hsum else "template <class R, bool SDE>")
@@ -1001,12 +1025,16 @@ class Process:
                 L.append(f"    {{ const W4<R> t = {code}; if constexpr (XWP[{k}] >= 0) st_w4<R>(xw, XWP[{k}], lane, t); "
                          f"else xwr[{k}] = t; }}")
             L.append("#define XW(k) (XWP[k] >= 0 ? ld_w4<R>(xw, XWP[k], lane) : xwr[k])")
+        if rec:
+            L.append("    constexpr bool JAMPS = sizeof(R) == 4;  // FP64: the channel weights only")
         L.append(f"    constexpr int NW = {nwin};")
         if jamps_in_lds or mode == "slots":
             acc = "double" if jamp_mode == "atomic64" else "R"
             L.append(f"    // jamps accumulate in LDS, one private slot per lane ({jamp_mode})")
-            L.append(f"    __shared__ {acc} Jl_wg[WG * 2 * NW * 64];")
+            L.append(f"    __shared__ {acc} Jl_wg[{'JAMPS ? WG * 2 * NW * 64 : 1' if rec else 'WG * 2 * NW * 64'}];")
             L.append(f"    {acc}* const Jl = Jl_wg + (threadIdx.x >> 6) * (2 * NW * 64);")
+            if rec:
+                L.append("    if constexpr (JAMPS)")
             L.append("#pragma unroll")
             if jamp_mode == "auto":
                 L.append("    for (int s = 0; s < 2 * NW; ++s) jamp_zero<R>(&Jl[s * 64 + lane]);")
@@ -1017,7 +1045,8 @@ class Process:
                 L.append("#define JGET(s, ri) ((R)Jl[(2 * (s) + (ri)) * 64 + lane])")
                 L.append(f"#define JZERO(s, ri) (Jl[(2 * (s) + (ri)) * 64 + lane] = ({acc})0)")
             elif jamp_mode == "auto":
-                L.append("#define JADD(s, ri, v) jamp_add<R>(&Jl[(2 * (s) + (ri)) * 64 + lane], (v))")
+                add = "jamp_add<R>(&Jl[(2 * (s) + (ri)) * 64 + lane], (v))"
+                L.append(f"#define JADD(s, ri, v) {f'do {{ if constexpr (JAMPS) {add}; }} while (0)' if rec else add}")
                 L.append("#define JGET(s, ri) jamp_get<R>(&Jl[(2 * (s) + (ri)) * 64 + lane])")
                 L.append("#define JZERO(s, ri) jamp_zero<R>(&Jl[(2 * (s) + (ri)) * 64 + lane])")
             else:
@@ -1033,13 +1062,21 @@ class Process:
             L.append("#define JADD(s, ri, v) (Jr[2 * (s) + (ri)] += (v))")
             L.append("#define JGET(s, ri) Jr[2 * (s) + (ri)]")
         if mode == "slots":
-            L.append("    R* const po = jamp + (int64_t)n_good * (2 * NC) * ld + (int64_t)h * (2 * NSLOT) * ld + e;")
+            L.append(("    [[maybe_unused]] " if rec else "    ") + "R* const po = jamp + (int64_t)n_good * (2 * NC) * ld + (int64_t)h * (2 * NSLOT) * ld + e;")
             # evicting a window slot: JTAKE reads it into registers and clears it (LDS
             # accesses complete in order, so no wait is needed there); JPUT stores the pair
             # to its partial slot later, once the read has long completed
-            L.append("#define JTAKE(s, k) const R fr##k = JGET(s, 0), fi##k = JGET(s, 1); JZERO(s, 0); JZERO(s, 1)")
-            L.append("#define JLAST(s, k) const R fr##k = JGET(s, 0), fi##k = JGET(s, 1)")
-            L.append("#define JPUT(p, k) do { if (live) { po[(int64_t)(2 * (p)) * ld] = fr##k; "
+            if rec:
+                L.append("#define JTAKE(s, k) [[maybe_unused]] R fr##k = 0, fi##k = 0; "
+                         "if constexpr (JAMPS) { fr##k = JGET(s, 0); fi##k = JGET(s, 1); JZERO(s, 0); JZERO(s, 1); }")
+                L.append("#define JLAST(s, k) [[maybe_unused]] R fr##k = 0, fi##k = 0; "
+                         "if constexpr (JAMPS) { fr##k = JGET(s, 0); fi##k = JGET(s, 1); }")
+                L.append("#define JPUT(p, k) do { if constexpr (JAMPS) { if (live) { po[(int64_t)(2 * (p)) * ld] = fr##k; "
+                         "po[(int64_t)(2 * (p) + 1) * ld] = fi##k; } } } while (0)")
+            else:
+                L.append("#define JTAKE(s, k) const R fr##k = JGET(s, 0), fi##k = JGET(s, 1); JZERO(s, 0); JZERO(s, 1)")
+                L.append("#define JLAST(s, k) const R fr##k = JGET(s, 0), fi##k = JGET(s, 1)")
+                L.append("#define JPUT(p, k) do { if (live) { po[(int64_t)(2 * (p)) * ld] = fr##k; "
                      "po[(int64_t)(2 * (p) + 1) * ld] = fi##k; } } while (0)")
         L.append("    cx<R> a, sa;")
         L.append("    int ch = -1;")
@@ -1060,6 +1097,8 @@ class Process:
             L.append("            so[ld] += sde_all;")
         L.append("        }")
         L.append("    }")
+        if rec and mode == "jamps":
+            L.append("    if constexpr (JAMPS) {")
         if mode == "jamps":
             if fused:
                 L.append("    if (fc.aop) {  // colour sum here: D |M_h|^2 of this lane's event, to [h][event]")
@@ -1092,9 +1131,7 @@ class Process:
                     L.append("#pragma unroll")
                     L.append("        for (int s = 0; s < 2 * NC; ++s) Js[s * 64 + lane] = Jr[s];")
                     L.append("        __syncthreads();")
-                L.append("        if constexpr (sizeof(R) == 8)")
-                L.append(f"            me_h = colour_sum_lds<NC>({src}, static_cast<const double*>(fc.aop), lane);")
-                L.append("        else if (fc.form == ME_MIXED_BF16)")
+                L.append("        if (fc.form == ME_MIXED_BF16)")
                 L.append(f"            me_h = colour_sum_lds_h16<NC, Bf16Terms>({src}, static_cast<const __bf16*>(fc.aop), "
                          "static_cast<const __bf16*>(fc.aop_lo), fc.lo_mask, lane);")
                 L.append("        else")
@@ -1133,6 +1170,8 @@ class Process:
             L.append("        R* o = jamp + (int64_t)h * (2 * NC) * ld + e;")
             L.append("#pragma unroll")
             L.append("        for (int s = 0; s < 2 * NC; ++s) o[s * ld] = jo[s];")
+            L.append("    }")
+        if rec and mode == "jamps":
             L.append("    }")
         for m in ("PM", "GB", "XW", "JADD", "JGET", "JZERO", "JTAKE", "JLAST", "JPUT", "SDEACC"):
             L.append(f"#undef {m}")

@@ -1,0 +1,60 @@
+"""The FP64 kernels of the colour-ordered recursion at the edges of their 64-event blocks, through
+every call that reads their colour-flow amplitudes: the fused colour sum, the separate one, the
+per-helicity values and the colour-flow draws; and with massless tops, where a workgroup's four
+quark spin configurations are not all good helicities.  The bar is the repository's FP64 bar:
+1e-12 per event against the oracle, with the long-double referee beyond it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests import referee
+from tests import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+PROCESSES = ["gg_ttgg", "gg_ttggg"]
+
+
+def check(name, p, got, params):
+    want = oracle.me_batch(name, p, params=params)
+    for i in np.where(~(np.abs(got / want - 1) <= referee.TOL))[0]:
+        ok, r, spread = referee.judge(name, p[i], got[i], params)
+        assert ok, (name, int(i), r, spread)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 129])
+@pytest.mark.parametrize("name", PROCESSES)
+def test_block_edges(name, n):
+    from paper_2210_11122_amd import Process
+    n = min(n, 65) if name == "gg_ttggg" else n
+    print(f"case recursion {name} n={n}", flush=True)
+    proc = Process(name, m_top=W.M_TOP, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
+    p = oracle.rambo(31, W.sqrt_s(name), W.final_masses(name), n)
+    x = torch.from_numpy(p).cuda()
+    me = proc.sigma(x)
+    check(name, p, me.cpu().numpy(), W.PARAMS)
+    tot, hel = proc.sigma(x, per_helicity=True)
+    assert torch.equal(tot, me)
+    assert np.allclose(hel.cpu().numpy().sum(axis=1) / proc.info["avg_factor"], me.cpu().numpy(), rtol=1e-13, atol=0)
+    # uniforms at both ends of [0, 1): the draws end at the first and last flow of positive weight
+    zero, one = torch.zeros(n, dtype=torch.float64).cuda(), torch.full((n,), 1 - 2.0 ** -53, dtype=torch.float64).cuda()
+    sel, h0, c0 = proc.select(x, zero, zero)
+    _, h1, c1 = proc.select(x, one, one)
+    assert torch.equal(sel, me) and bool((c0 == 0).all()) and bool((c1 == proc.info["n_colors"] - 1).all())
+    good = proc.good_helicities_index()
+    assert bool((h0 == good[0]).all()) and bool((h1 == good[-1]).all())
+
+
+@pytest.mark.parametrize("name,n", [("gg_ttgg", 65), ("gg_ttggg", 3)])
+def test_massless_tops_leave_spin_configurations_out(name, n):
+    from paper_2210_11122_amd import Process
+    print(f"case recursion massless {name} n={n}", flush=True)
+    params = (0.0, W.ALPHA_EM, W.ALPHA_S)
+    proc = Process(name, m_top=0.0, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
+    spins = {}
+    for lam in proc.good_helicities():
+        spins.setdefault(lam[:2] + lam[4:], set()).add(lam[2:4])
+    assert all(len(s) < 4 for s in spins.values())
+    p = oracle.rambo(33, W.sqrt_s(name), [0.0] * (W.n_par(name) - 2), n)
+    check(name, p, proc.sigma(torch.from_numpy(p).cuda()).cpu().numpy(), params)
