@@ -39,6 +39,7 @@
 #include <stdint.h>
 
 #include "flows.hpp"
+#include "generated/colour_blocks.hpp"
 #include "helas.hpp"
 
 namespace me {
@@ -187,60 +188,83 @@ __device__ __forceinline__ double colour_sum_regs(const double* Jr, const double
 // multiply-adds on one lane's own jamps.  The blocks leave 80 (1808) of the 576 (14400) products of
 // the full matrix, and their symmetry 52 (964), so the sum is cheaper here than as matrix-core
 // tiles of the full matrix (which took 64 (512) 16x16x4 tiles per 64 events), and needs no exchange
-// between lanes.  tab: per block its upper triangle, off-diagonal entries doubled (me_abi.cpp,
-// block_table).  The rounding sequence is fixed: no contraction beyond the written ones.
-template <int NG, class Get>
-__device__ __forceinline__ double colour_blocks_part(const Get& x, const double* __restrict__ tab)
+// between lanes.  The entries are compile-time integers: as scalar loads from a table, each batch
+// of them was waited for (120 flows: 390 us per 4096 events x 128 helicities).  The rounding
+// sequence is fixed: no contraction beyond the written ones.
+//
+// y of the orbit O for the signs numbered S = 0 .. 3, (chi01, chi23) = (+,+), (+,-), (-,+), (-,-),
+// from its four flows (relabelled by neither, (01), (23), both)
+template <int S>
+__device__ __forceinline__ double orbit_sum(double m00, double m10, double m01, double m11)
 {
 #pragma clang fp contract(off)
-    constexpr int NO = FlowBlocks<NG>::NO, NP = flow_blocks<NG>.n_pair;
-    double y[4][NO];
-    static_for<NO>([&](auto O) {
-        const double m00 = x(std::integral_constant<int, flow_blocks<NG>.member[O][0][0]>{}),
-                     m10 = x(std::integral_constant<int, flow_blocks<NG>.member[O][1][0]>{}),
-                     m01 = x(std::integral_constant<int, flow_blocks<NG>.member[O][0][1]>{}),
-                     m11 = x(std::integral_constant<int, flow_blocks<NG>.member[O][1][1]>{});
-        const double a = m00 + m10, b = m00 - m10, c = m01 + m11, d = m01 - m11;
-        y[0][O] = a + c;
-        y[1][O] = a - c;
-        y[2][O] = b + d;
-        y[3][O] = b - d;
-    });
+    const double a = S < 2 ? m00 + m10 : m00 - m10, c = S < 2 ? m01 + m11 : m01 - m11;
+    return S % 2 ? a - c : a + c;
+}
+// the two blocks of the signs S from their y over all orbits (of the real or imaginary parts)
+template <int NG, int S>
+__device__ __forceinline__ double sign_blocks(const double (&y)[FlowBlocks<NG>::NO])
+{
+#pragma clang fp contract(off)
+    constexpr int NP = flow_blocks<NG>.n_pair, NF = flow_blocks<NG>.n_fix;
     double q = 0.0;
-    int t = 0;
-    static_for<8>([&](auto K) {
-        constexpr int s = K / 2, rho = K % 2 ? -1 : 1, chi = (s == 0 || s == 3) ? 1 : -1;
-        constexpr int nz = NP + (rho == chi ? flow_blocks<NG>.n_fix : 0);
+    static_for<2>([&](auto K) {
+        constexpr int rho = K ? -1 : 1, chi = (S == 0 || S == 3) ? 1 : -1;
+        constexpr int nz = NP + (rho == chi ? NF : 0);
+        // table entries before this block: of the signs before (a block with the fixed orbits and one
+        // without, each), and of this sign's first block
+        constexpr int T0 = NP * (NP + 1) / 2, T1 = (NP + NF) * (NP + NF + 1) / 2;
+        constexpr int t0 = S * (T0 + T1) + (K ? (chi > 0 ? T1 : T0) : 0);
         double z[nz];
         static_for<nz>([&](auto I) {
             if constexpr (I < NP) {
-                const double u = y[s][flow_blocks<NG>.pair[I][0]], v = y[s][flow_blocks<NG>.pair[I][1]];
+                const double u = y[flow_blocks<NG>.pair[I][0]], v = y[flow_blocks<NG>.pair[I][1]];
                 z[I] = rho * chi > 0 ? u + v : u - v;
             } else {
-                z[I] = y[s][flow_blocks<NG>.fix[I - NP]];
+                z[I] = y[flow_blocks<NG>.fix[I - NP]];
             }
         });
         static_for<nz>([&](auto I) {
-            double r = tab[t++] * z[I];
-            static_for<nz - I - 1>([&](auto J) { r = __builtin_fma(tab[t++], z[I + 1 + J], r); });
+            constexpr int t = t0 + I * nz - I * (I - 1) / 2;
+            double r = ColourBlocks<NG>::table[t] * z[I];
+            static_for<nz - I - 1>([&](auto J) {
+                constexpr int c = ColourBlocks<NG>::table[t + 1 + J];
+                if constexpr (c != 0) r = __builtin_fma((double)c, z[I + 1 + J], r);
+            });
             q = __builtin_fma(z[I], r, q);
         });
     });
     return q;
 }
+template <int NG, int S, class Get>
+__device__ __forceinline__ double colour_blocks_part(const Get& x)
+{
+    double y[FlowBlocks<NG>::NO];
+    static_for<FlowBlocks<NG>::NO>([&](auto O) {
+        y[O] = orbit_sum<S>(x(std::integral_constant<int, flow_blocks<NG>.member[O][0][0]>{}),
+                            x(std::integral_constant<int, flow_blocks<NG>.member[O][1][0]>{}),
+                            x(std::integral_constant<int, flow_blocks<NG>.member[O][0][1]>{}),
+                            x(std::integral_constant<int, flow_blocks<NG>.member[O][1][1]>{}));
+    });
+    return sign_blocks<NG, S>(y);
+}
 template <int NG>
-__device__ __forceinline__ double colour_blocks(const cx<double> (&J)[factorial(NG)], const double* __restrict__ tab)
+__device__ __forceinline__ double colour_blocks(const cx<double> (&J)[factorial(NG)])
 {
 #pragma clang fp contract(off)
-    const double re = colour_blocks_part<NG>([&](auto F) { return J[F].r; }, tab);
-    const double im = colour_blocks_part<NG>([&](auto F) { return J[F].i; }, tab);
-    double v = re + im;
+    const auto re = [&](auto F) { return J[F].r; };
+    const auto im = [&](auto F) { return J[F].i; };
+    const double r = (colour_blocks_part<NG, 0>(re) + colour_blocks_part<NG, 1>(re)) +
+                     (colour_blocks_part<NG, 2>(re) + colour_blocks_part<NG, 3>(re));
+    const double i = (colour_blocks_part<NG, 0>(im) + colour_blocks_part<NG, 1>(im)) +
+                     (colour_blocks_part<NG, 2>(im) + colour_blocks_part<NG, 3>(im));
+    double v = (r + i) * (1.0 / 64.0);
     asm volatile("" : "+v"(v));
     return v;
 }
 
 // The separate colour sum in FP64: one lane per event, the good helicities of the group
-// blockIdx.y in turn.  aop: the 16x4 tile table (up to six flows) or the block table.
+// blockIdx.y in turn.  aop: the 16x4 tile table (up to six flows).
 template <int NC>
 __global__ __launch_bounds__(NC > 6 ? 64 : 256) void colour_sum_f64(
     const double* __restrict__ J, int64_t ld, int n_good, int hel_per_group, int64_t n_evt,
@@ -260,18 +284,73 @@ __global__ __launch_bounds__(NC > 6 ? 64 : 256) void colour_sum_f64(
             for (int s = 0; s < 2 * NC; ++s) Jr[s] = Jh[(int64_t)s * ld];
             me_h = colour_sum_regs<NC>(Jr, aop);
         } else {
-            constexpr int NG = NC == 24 ? 4 : 5;
-            static_assert(NC == factorial(NG), "24 or 120 flows");
-            // the real and imaginary rows in turn
-            const double re = colour_blocks_part<NG>([&](auto F) { return Jh[(int64_t)(2 * F) * ld]; }, aop);
-            const double im = colour_blocks_part<NG>([&](auto F) { return Jh[(int64_t)(2 * F + 1) * ld]; }, aop);
-            me_h = re + im;
-            asm volatile("" : "+v"(me_h));
+            static_assert(NC == 24, "120 flows: colour_sum_f64_120");
+            cx<double> Jr[NC];
+            static_for<NC>([&](auto F) { Jr[F] = {Jh[(int64_t)(2 * F) * ld], Jh[(int64_t)(2 * F + 1) * ld]}; });
+            me_h = colour_blocks<4>(Jr);
         }
         if (out_hel) out_hel[e * n_good + h] = me_h * scale_hel;
         me += me_h;
     }
     cs_store(me, e, n_evt, scale_avg, out, part);
+}
+// 120 flows: bound by reading the jamps (1920 B per (event, helicity)).  One workgroup: 64 events;
+// its four waves are the real and imaginary rows times the two signs chi01.  The rows are read five
+// orbits (20 rows) at a time, one group ahead of its use, past the caches (each is read by two waves
+// of one workgroup only): 4096 events x 128 helicities 253 us, 4.0 TB/s; 388 us where the compiler
+// placed the reads, which kept few of them in flight, and 333 us with six orbits (spills).
+template <int C01>
+__device__ __forceinline__ double colour_sign_pair_120(const double* __restrict__ Jh, int64_t ld, unsigned col)
+{
+    constexpr int NO = FlowBlocks<5>::NO, STEP = 5;
+    double y0[NO], y1[NO], m[2][STEP][4];
+    const auto read = [&](auto G, double (&d)[STEP][4]) {
+        static_for<STEP>([&](auto I) {
+            static_for<4>([&](auto K) {
+                constexpr int f = flow_blocks<5>.member[G * STEP + I][K % 2][K / 2];
+                d[I][K] = __builtin_nontemporal_load(&(Jh + (int64_t)(2 * f) * ld)[col]);
+            });
+        });
+    };
+    read(std::integral_constant<int, 0>{}, m[0]);
+    static_for<NO / STEP>([&](auto G) {
+        if constexpr (G + 1 < NO / STEP) read(std::integral_constant<int, G + 1>{}, m[(G + 1) % 2]);
+        static_for<STEP>([&](auto I) {
+            double(&d)[4] = m[G % 2][I];
+            // the group ahead is read before this one is waited for
+            asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3]) : : "memory");
+            y0[G * STEP + I] = orbit_sum<2 * C01>(d[0], d[1], d[2], d[3]);
+            y1[G * STEP + I] = orbit_sum<2 * C01 + 1>(d[0], d[1], d[2], d[3]);
+        });
+    });
+    return sign_blocks<5, 2 * C01>(y0) + sign_blocks<5, 2 * C01 + 1>(y1);
+}
+static __global__ __launch_bounds__(256, 2) void colour_sum_f64_120(
+    const double* __restrict__ J, int64_t ld, int n_good, int hel_per_group, int64_t n_evt, double scale_hel,
+    double scale_avg, double* __restrict__ out, double* __restrict__ out_hel, double* __restrict__ part)
+{
+    __shared__ double red[2][3][64];
+    const unsigned lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t e0 = (int64_t)blockIdx.x * 64, e = e0 + lane;
+    // lanes past the batch read the last event's column
+    const unsigned col = (e < n_evt ? lane : (unsigned)(n_evt - 1 - e0)) & 63;
+    const int h0 = blockIdx.y * hel_per_group, h1 = min(n_good, h0 + hel_per_group);
+    double me = 0.0;
+    for (int h = h0; h < h1; ++h) {
+        const double* Jh = J + ((int64_t)h * 240 + (wave >> 1)) * ld + e0;
+        int64_t stride = ld;
+        asm volatile("" : "+s"(stride));   // the row offsets are formed here, not kept over the loop (and spilled)
+        const double q = wave & 1 ? colour_sign_pair_120<1>(Jh, stride, col) : colour_sign_pair_120<0>(Jh, stride, col);
+        if (wave > 0) red[h & 1][wave - 1][lane] = q;
+        __syncthreads();
+        if (wave == 0) {   // the other buffer is free for the next helicity until the next barrier
+            const double me_h = ((q + red[h & 1][0][lane]) + (red[h & 1][1][lane] + red[h & 1][2][lane])) * (1.0 / 64.0);
+            if (out_hel && e < n_evt) out_hel[e * n_good + h] = me_h * scale_hel;
+            me += me_h;
+        }
+    }
+    if (wave == 0 && e < n_evt) cs_store(me, e, n_evt, scale_avg, out, part);
 }
 
 // 16-bit element types of the mixed colour sum

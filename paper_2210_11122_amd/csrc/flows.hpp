@@ -146,12 +146,4 @@ __host__ __device__ constexpr FlowBlocks<NG> make_blocks()
 template <int NG>
 inline constexpr FlowBlocks<NG> flow_blocks = make_blocks<NG>();
 
-// entries of the block form's operand table: for each of the eight blocks its upper triangle
-template <int NG>
-__host__ __device__ constexpr int block_entries()
-{
-    const int p = flow_blocks<NG>.n_pair, q = p + flow_blocks<NG>.n_fix;
-    return 4 * (p * (p + 1) / 2) + 4 * (q * (q + 1) / 2);
-}
-
 }  // namespace me

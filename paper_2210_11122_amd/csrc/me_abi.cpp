@@ -183,10 +183,16 @@ struct ColourArgs {
 template <int NC>
 hipError_t launch_cs64(const double* J, const double* aop, const ColourArgs& a, hipStream_t st)
 {
-    constexpr int T = NC > 6 ? 64 : 256;
-    hipLaunchKernelGGL((me::colour_sum_f64<NC>), dim3((unsigned)((a.n + T - 1) / T), (unsigned)a.groups), dim3(T),
-                       0, st, J, a.ld, a.n_good, a.hel_per_group, a.n, aop, a.scale_hel, a.scale_avg, a.out, a.out_hel,
-                       a.part);
+    if constexpr (NC == 120) {
+        hipLaunchKernelGGL(me::colour_sum_f64_120, dim3((unsigned)((a.n + 63) / 64), (unsigned)a.groups), dim3(256), 0,
+                           st, J, a.ld, a.n_good, a.hel_per_group, a.n, a.scale_hel, a.scale_avg, a.out, a.out_hel,
+                           a.part);
+    } else {
+        constexpr int T = NC > 6 ? 64 : 256;
+        hipLaunchKernelGGL((me::colour_sum_f64<NC>), dim3((unsigned)((a.n + T - 1) / T), (unsigned)a.groups), dim3(T),
+                           0, st, J, a.ld, a.n_good, a.hel_per_group, a.n, aop, a.scale_hel, a.scale_avg, a.out,
+                           a.out_hel, a.part);
+    }
     return hipGetLastError();
 }
 template <int NC, class T>
@@ -494,59 +500,6 @@ void free_handle(me_handle* h)
     delete h;
 }
 
-// The colour matrix of NG gluons in the block form of flows.hpp: for each block (in the order of
-// colour_blocks_part) its upper triangle, off-diagonal entries doubled.  With the block's basis
-// vectors v_i (z_i = v_i . J, of length |v_i|^2 = 8, or 4 for an orbit that the reversal keeps),
-// B_ij = v_i^T Chat v_j / (|v_i|^2 |v_j|^2): integers over 16, 32 or 64, exact.  False if Chat does
-// not have the symmetry (a mistake in the tables).
-template <int NG>
-bool block_table(const int* chat, std::vector<double>& tab)
-{
-    constexpr const me::FlowBlocks<NG>& F = me::flow_blocks<NG>;
-    constexpr int NC = me::FlowBlocks<NG>::NC;
-    std::vector<std::vector<int>> basis;   // all blocks' vectors
-    std::vector<int> block_of;
-    for (int b = 0; b < 8; ++b) {
-        const int s = b / 2, rho = b % 2 ? -1 : 1, c01 = s < 2 ? 1 : -1, c23 = s % 2 ? -1 : 1;
-        const int n = F.n_pair + (rho == c01 * c23 ? F.n_fix : 0);
-        for (int i = 0; i < n; ++i) {
-            std::vector<int> v(NC, 0);
-            auto add = [&](int o, int w) {
-                for (int g = 0; g < 2; ++g)
-                    for (int k = 0; k < 2; ++k) v[F.member[o][g][k]] += w * (g ? c01 : 1) * (k ? c23 : 1);
-            };
-            if (i < F.n_pair) {
-                add(F.pair[i][0], 1);
-                add(F.pair[i][1], rho * c01 * c23);
-            } else {
-                add(F.fix[i - F.n_pair], 1);
-            }
-            basis.push_back(v);
-            block_of.push_back(b);
-        }
-    }
-    if ((int)basis.size() != NC) return false;
-    tab.clear();
-    for (int i = 0; i < NC; ++i) {
-        std::vector<double> cv(NC, 0.0);
-        double ni = 0.0;
-        for (int r = 0; r < NC; ++r) {
-            ni += basis[i][r] * basis[i][r];
-            for (int c = 0; c < NC; ++c) cv[r] += (double)chat[r * NC + c] * basis[i][c];
-        }
-        for (int j = 0; j < NC; ++j) {
-            double x = 0.0, nj = 0.0;
-            for (int r = 0; r < NC; ++r) x += cv[r] * basis[j][r], nj += basis[j][r] * basis[j][r];
-            if (block_of[j] != block_of[i]) {
-                if (x != 0.0) return false;
-            } else if (j >= i) {
-                tab.push_back((j > i ? 2.0 : 1.0) * x / (ni * nj));
-            }
-        }
-    }
-    return (int)tab.size() == me::block_entries<NG>();
-}
-
 // colour matrix as matrix-core A operands, block upper-triangular (see colorsum.hpp for the
 // layouts and the tile order)
 int upload_colour(me_handle* h)
@@ -563,9 +516,6 @@ int upload_colour(me_handle* h)
     for (int mt = 0; mt < MT; ++mt)
         for (int kt = 4 * mt; kt < KT; ++kt)
             for (int l = 0; l < 64; ++l) a64.push_back(A(16 * mt + l % 16, 4 * kt + l / 16));
-    // FP64 with 24 or 120 flows: the block form instead
-    if ((NC == 24 && !block_table<4>(P->colour_num, a64)) || (NC == 120 && !block_table<5>(P->colour_num, a64)))
-        return fail(ME_EINVAL, "the colour matrix lacks the symmetry of the block form");
     std::vector<_Float16> a16;
     std::vector<__bf16> ab, ablo;
     uint64_t lo_mask = 0;

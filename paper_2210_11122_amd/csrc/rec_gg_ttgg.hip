@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256, 1) void amp_rec(const double* __restrict__ mom
         });
     }
     if (fc.aop) {
-        const double me_h = colour_blocks<NG>(J, static_cast<const double*>(fc.aop));
+        const double me_h = colour_blocks<NG>(J);
         if (e < n_evt) jamp[(int64_t)h * n_evt + e] = me_h;
         return;
     }

@@ -9,7 +9,7 @@
 // flows, 24 at a time (those with the same last gluon), each stored once.
 //
 // Against the 14 diagram segments (247k flops per lane, 977 partial jamp sums through memory):
-// 2^17 events, colour sum included, 208.7 -> 56.6 ms per call; 1531 events 3.07 -> 0.76 ms.
+// 2^17 events, colour sum included, 208.9 -> 43.8 ms per call; 1531 events 3.05 -> 0.53 ms.
 #include "process.hpp"
 #include "recursion.hpp"
 
@@ -301,7 +301,7 @@ __device__ __forceinline__ V4 lds2(const double* lds, int lane)
 // gluon configuration; wave w takes the six orderings that begin with gluon w + 1.
 __global__ __launch_bounds__(256, 1) void five_currents(const double* __restrict__ mom, int64_t n_evt,
                                                         const int* __restrict__ cfg, int n_cfg,
-                                                        const v2d* __restrict__ cur_, int n_good, double* __restrict__ five)
+                                                        const v2d* __restrict__ cur_, int n_good, v2d* __restrict__ five)
 {
     __shared__ double lds[NS * 512];
     const int lane = threadIdx.x & 63;
@@ -375,8 +375,7 @@ __global__ __launch_bounds__(256, 1) void five_currents(const double* __restrict
             const int h = rc_[1 + SP];
             if (h < 0) return;
             const C x = rc(q[SP], o);
-            (five + ((e0 >> 6) * n_good + h) * (int64_t)(48 * 64) + 128 * r)[(unsigned)lane] = x.r;
-            (five + ((e0 >> 6) * n_good + h) * (int64_t)(48 * 64) + 128 * r + 64)[(unsigned)lane] = x.i;
+            (five + ((e0 >> 6) * n_good + h) * (int64_t)(24 * 64) + 64 * r)[(unsigned)lane] = v2d{x.r, x.i};
         });
     });
 }
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(256, 1) void five_currents(const double* __restrict
 // --- the flows.  One workgroup: 64 events, one gluon configuration, the four quark spin
 // configurations in its four waves, which share the currents of up to three gluons in LDS.
 __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, const int* __restrict__ cfg, int n_cfg,
-                                                  const v2d* __restrict__ cur_, int n_good, const double* __restrict__ five,
+                                                  const v2d* __restrict__ cur_, int n_good, const v2d* __restrict__ five,
                                                   double* __restrict__ jamp)
 {
     __shared__ double lds[NS * 512];
@@ -413,15 +412,28 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
         static_for<6>([&](auto R) { D3[X][R] = rc(c, ldm(src, m4(X, h4, R), lane)); });
         static_for<6>([&](auto R) { pin_cx(D3[X][R]); });
     });
+    // per last gluon: the contractions of all five, the string R1 and the currents of the others, read
+    // before the stores of the flows before, which the waits for later reads would include
+    C D4[24];
+    V4 Rn, q4[6];
+    const auto read_ahead = [&](int g) {
+        src = fresh(cur);
+        const v2d* f5 = fresh(five) + ((e0 >> 6) * n_good + h) * (int64_t)(24 * 64);
+        static_for<24>([&](auto R) {
+            const v2d t = (f5 + 64 * R)[(unsigned)lane];
+            D4[R] = {t.x, t.y};
+        });
+        Rn = R1(g);
+        const int h4 = bits_without(bits, g);
+        static_for<6>([&](auto R) { q4[R] = ldm(src, m4(g, h4, R), lane); });
+    };
+    read_ahead(0);
     // the 24 flows that end with gluon g; J[rank of the others' order]
     static_for<NG>([&](auto G_) {
         constexpr int g = G_;
         C J[24];
         src = fresh(cur);
-        const double* f5 = fresh(five) + ((e0 >> 6) * n_good + h) * (int64_t)(48 * 64);
         {   // all five gluons in one current
-            C D4[24];
-            static_for<24>([&](auto R) { D4[R] = {f5[128 * R + (unsigned)lane], f5[128 * R + 64 + (unsigned)lane]}; });
             static_for<24>([&](auto F) {
                 constexpr int r5 = flow_with_last(g, F);
                 J[F] = {0.0, 0.0};
@@ -432,12 +444,15 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
                 });
             });
         }
-        const V4 Rg = R1(g);
+        const V4 Rg = Rn;
+        V4 rn, lh[4];
         {   // four gluons next to the quark, the last one at the antiquark
+            src = fresh(cur);
+            rn = R2(rest(g, 0), g);
+            static_for<4>([&](auto M) { lh[M] = L1(rest(g, M)); });
             const V4 c = pair(U, Rg);
-            const int h4 = bits_without(bits, g);
             C s[6];
-            static_for<6>([&](auto R) { s[R] = rc(c, ldm(src, m4(g, h4, R), lane)); });
+            static_for<6>([&](auto R) { s[R] = rc(c, q4[R]); });
             static_for<24>([&](auto F) {
                 // and four next to the antiquark: (a | b c d g)
                 constexpr int a = rest(g, perm_at<4>(F).p[0]), r4 = last_four(g, F);
@@ -456,10 +471,13 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
             constexpr int m = M, x = m == 0 ? 1 : 0, y = m <= 1 ? 2 : 1, z = m <= 2 ? 3 : 2;
             constexpr int a = rest(g, m);
             constexpr int t = triple_index(rest(g, x), rest(g, y), rest(g, z));
-            src = fresh(cur);
             const V4 G0 = ld_v(lds, S3 + 2 * t, lane), G1 = ld_v(lds, S3 + 2 * t + 1, lane);
-            const V4 Rag = R2(a, g);
-            const V4 cl = pair(L1(a), Rg), cr = pair(U, Rag);
+            const V4 Rag = rn;
+            if constexpr (m < 3) {
+                src = fresh(cur);
+                rn = R2(rest(g, m < 3 ? m + 1 : 0), g);
+            }
+            const V4 cl = pair(lh[m], Rg), cr = pair(U, Rag);
             const C l0 = rc(cl, G0), l1 = rc(cl, G1), r0 = rc(cr, G0), r1 = rc(cr, G1), l2 = l0 + l1, r2 = r0 + r1;
             // (a | x y z | g) and (x y z | a g)
             constexpr int f0 = rank4(m, x, y, z), f1 = rank4(m, z, y, x), f2 = rank4(m, x, z, y), f3 = rank4(m, y, z, x),
@@ -472,7 +490,7 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
             // (i | j k | a g): the quark takes i, a two-gluon current, the antiquark the string (a g)
             static_for<3>([&](auto I_) {
                 constexpr int i = I_ == 0 ? x : I_ == 1 ? y : z, j = I_ == 0 ? y : x, k = I_ == 2 ? y : z;
-                const C s = rc(L1(rest(g, i)), col(lds2<rest(g, j), rest(g, k)>(lds, lane), Rag));
+                const C s = rc(lh[i], col(lds2<rest(g, j), rest(g, k)>(lds, lane), Rag));
                 constexpr int u0 = rank4(i, j, k, m), u1 = rank4(i, k, j, m);
                 J[u0] = J[u0] + s;
                 J[u1] = J[u1] - s;
@@ -482,16 +500,24 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
                 if constexpr (q.p[0] == m || q.p[3] == m) pin_cx(J[F]);
             });
         });
+        V4 pf[4];
+        src = fresh(cur);
+        pf[0] = R2(rest(g, 3), g), pf[1] = R2(rest(g, 2), g), pf[2] = L2(rest(g, 0), rest(g, 1)), pf[3] = L2(rest(g, 1), rest(g, 0));
         // two gluons at the quark, the others at the antiquark: (a b | c d g)
         static_for<6>([&](auto P_) {
             constexpr int pi[6] = {0, 0, 0, 1, 1, 2}, pj[6] = {1, 2, 3, 2, 3, 3};
             constexpr int a = pi[P_], b = pj[P_], c = pi[5 - P_], d = pj[5 - P_];
             constexpr int ga = rest(g, a), gb = rest(g, b), gc = rest(g, c), gd = rest(g, d);
-            src = fresh(cur);
+            const V4 rd = pf[0], rc_ = pf[1], Lab = pf[2], Lba = pf[3];
+            if constexpr (P_ < 5) {
+                constexpr int n = P_ < 5 ? P_ + 1 : 0;
+                src = fresh(cur);
+                pf[0] = R2(rest(g, pj[5 - n]), g), pf[1] = R2(rest(g, pi[5 - n]), g);
+                pf[2] = L2(rest(g, pi[n]), rest(g, pj[n])), pf[3] = L2(rest(g, pj[n]), rest(g, pi[n]));
+            }
             const V4 y = col(lds2<gc, gd>(lds, lane), Rg);
-            const V4 Rcd = col_acc(col_acc(y, J1(gc), R2(gd, g)), lds3<gc, gd, g>(lds, lane), S);
-            const V4 Rdc = col_acc(col_acc(-y, J1(gd), R2(gc, g)), lds3<gd, gc, g>(lds, lane), S);
-            const V4 Lab = L2(ga, gb), Lba = L2(gb, ga);
+            const V4 Rcd = col_acc(col_acc(y, J1(gc), rd), lds3<gc, gd, g>(lds, lane), S);
+            const V4 Rdc = col_acc(col_acc(-y, J1(gd), rc_), lds3<gd, gc, g>(lds, lane), S);
             constexpr int f0 = rank4(a, b, c, d), f1 = rank4(a, b, d, c), f2 = rank4(b, a, c, d), f3 = rank4(b, a, d, c);
             J[f0] = rc_acc(J[f0], Lab, Rcd);
             J[f1] = rc_acc(J[f1], Lab, Rdc);
@@ -499,12 +525,13 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
             J[f3] = rc_acc(J[f3], Lba, Rdc);
             pin_cx(J[f0]), pin_cx(J[f1]), pin_cx(J[f2]), pin_cx(J[f3]);
         });
+        if constexpr (g + 1 < NG) read_ahead(g + 1);
         if (e < n_evt) {
             double* const o = jamp + (int64_t)h * (2 * NC) * ld + e0;
             static_for<24>([&](auto F) {
                 constexpr int r5 = flow_with_last(g, F);
-                (o + (2 * r5) * ld)[(unsigned)lane] = J[F].r;
-                (o + (2 * r5 + 1) * ld)[(unsigned)lane] = J[F].i;
+                __builtin_nontemporal_store(J[F].r, (o + (2 * r5) * ld) + (unsigned)lane);
+                __builtin_nontemporal_store(J[F].i, (o + (2 * r5 + 1) * ld) + (unsigned)lane);
             });
         }
     });
@@ -518,7 +545,7 @@ hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGr
     if (n_evt == 0 || hg.n == 0) return hipSuccess;
     // after the jamps: the currents and strings of the events, then the five-gluon contractions
     v2d* const cur = reinterpret_cast<v2d*>(jamp + (int64_t)n_good * 2 * NC * ld);
-    double* const five = reinterpret_cast<double*>(cur + (int64_t)4 * MEND * ld);
+    v2d* const five = cur + (int64_t)4 * MEND * ld;
     const unsigned nb = (unsigned)((n_evt + 255) / 256), n64 = (unsigned)((n_evt + 63) / 64);
     hipLaunchKernelGGL(level1, dim3(nb, NG + 2), dim3(256), 0, st, mom, n_evt, mt, gs, cur);
     hipLaunchKernelGGL(level2, dim3(nb, 40 + 40), dim3(256), 0, st, mom, n_evt, mt, cur);

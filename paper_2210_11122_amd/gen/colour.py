@@ -195,3 +195,57 @@ def common_denominator(C):
         for x in row:
             d = lcm(d, x.denominator)
     return d
+
+
+def block_form(n, cnum):
+    """The colour matrix of n >= 4 gluons on a quark line in block form.  cnum: its integer
+    numerators in the order of itertools.permutations.  It commutes with relabelling the gluons by
+    (01) and by (23) and with the reversal of all orderings; the basis vectors of the eight blocks
+    of their signs are, for an orbit O of the relabellings with representative r (0 before 1 and 2
+    before 3) and characters chi,
+        y(O) = sum_g chi(g) J(g r),   z = y(O) + rho chi(01) chi(23) y(O')   (r reversed lies in O')
+    or z = y(O) alone where O' = O and rho = chi(01) chi(23).  Orbits are numbered by their
+    representatives in lexicographic order.  Returns (blocks, table): blocks, in the order
+    (+,+), (+,-), (-,+), (-,-) of chi with rho = + before -, each the list of its basis vectors
+    (dicts flow -> sign); table: per block the upper triangle of 64 B, off-diagonal entries doubled,
+    with J^T Chat J = sum over the blocks of z^T B z.  All integers."""
+    perms = list(permutations(range(n)))
+    index = {p: i for i, p in enumerate(perms)}
+
+    def relabel(p, s, t):
+        m = list(range(n))
+        if s:
+            m[0], m[1] = 1, 0
+        if t:
+            m[2], m[3] = 3, 2
+        return tuple(m[g] for g in p)
+
+    reps = [p for p in perms if p.index(0) < p.index(1) and p.index(2) < p.index(3)]
+    members = [{(s, t): index[relabel(p, s, t)] for s in (0, 1) for t in (0, 1)} for p in reps]
+    orbit = {i: o for o, m in enumerate(members) for i in m.values()}
+    other = [orbit[index[p[::-1]]] for p in reps]
+    blocks, table = [], []
+    for c01 in (1, -1):
+        for c23 in (1, -1):
+            for rho in (1, -1):
+                def y(o, w):
+                    return {i: w * (c01 if s else 1) * (c23 if t else 1) for (s, t), i in members[o].items()}
+
+                vecs = [{**y(o, 1), **y(q, rho * c01 * c23)} for o, q in enumerate(other) if q > o]
+                if rho == c01 * c23:
+                    vecs += [y(o, 1) for o, q in enumerate(other) if q == o]
+                blocks.append(vecs)
+    images = [[[sum(cnum[r][c] * w for c, w in v.items()) for r in range(len(perms))] for v in vecs] for vecs in blocks]
+    for a, vecs in enumerate(blocks):
+        for b, im in enumerate(images):
+            for i, v in enumerate(vecs):
+                for j, cv in enumerate(im):
+                    x = sum(w * cv[r] for r, w in v.items())
+                    if a != b:
+                        assert x == 0, "the colour matrix does not commute with the symmetries"
+                    elif j >= i:
+                        num = 64 * x * (2 if j > i else 1)
+                        den = len(v) * len(vecs[j])
+                        assert num % den == 0
+                        table.append(num // den)
+    return blocks, table

@@ -1347,8 +1347,27 @@ def stub_source(nm):
             f"namespace me {{ const ProcessDesc* process_{nm}() {{ return nullptr; }} }}\n")
 
 
+def colour_blocks_source():
+    """csrc/generated/colour_blocks.hpp: the block form of the colour matrices of 24 and 120 flows"""
+    L = ["// Generated by paper_2210_11122_amd.gen; do not edit.",
+         "// 64 times the upper triangles of the blocks of the colour matrix (flows.hpp), off-diagonal entries",
+         "// doubled, block by block.", "#pragma once", "namespace me {",
+         "template <int NG>", "struct ColourBlocks;"]
+    for n in (4, 5):
+        _, C = colour.colour_matrix_quark_line(n)
+        den = colour.common_denominator(C)
+        _, table = colour.block_form(n, [[int(x * den) for x in row] for row in C])
+        L += ["template <>", f"struct ColourBlocks<{n}> {{",
+              f"    static constexpr int table[{len(table)}] = {{{', '.join(map(str, table))}}};", "};"]
+    return "\n".join(L + ["}  // namespace me"]) + "\n"
+
+
 def generate(outdir, names=None):
     os.makedirs(outdir, exist_ok=True)
+    bpath, bsrc = os.path.join(outdir, "colour_blocks.hpp"), colour_blocks_source()
+    if not os.path.exists(bpath) or open(bpath).read() != bsrc:
+        with open(bpath, "w") as f:
+            f.write(bsrc)
     written = []
     for nm in names or ALL_PROCESSES:
         if nm in NOT_EMITTED:
