@@ -33,11 +33,12 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
     int lam[NPAR];
 #pragma unroll
     for (int i = 0; i < NPAR; ++i) lam[i] = hel[h * NPAR + i];
+    constexpr bool JAMPS = sizeof(R) == 4;  // FP64: the channel weights only
     constexpr int NW = 1;
     R Jr[2 * NW];
 #pragma unroll
     for (int s = 0; s < 2 * NW; ++s) Jr[s] = (R)0;
-#define JADD(s, ri, v) (Jr[2 * (s) + (ri)] += (v))
+#define JADD(s, ri, v) do { if constexpr (JAMPS) Jr[2 * (s) + (ri)] += (v); } while (0)
 #define JGET(s, ri) Jr[2 * (s) + (ri)]
     cx<R> a, sa;
     int ch = -1;
@@ -59,6 +60,7 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
             so[ld] = sde_all;
         }
     }
+    if constexpr (JAMPS) {
     if (fc.aop) {  // colour sum here: D |M_h|^2 of this lane's event, to [h][event]
         double me_h;
         if constexpr (sizeof(R) == 8) {
@@ -107,6 +109,7 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
         R* o = jamp + (int64_t)h * (2 * NC) * ld + e;
 #pragma unroll
         for (int s = 0; s < 2 * NC; ++s) o[s * ld] = jo[s];
+    }
     }
 #undef PM
 #undef GB
@@ -187,6 +190,11 @@ static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const sig
     constexpr int WG = sizeof(R) == 8 ? 1 : 1;  // waves (helicities) per workgroup
     int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);
     if (blocks == 0) return hipSuccess;
+    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for
+        const hipError_t err = rec_ee::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);
+        if (err != hipSuccess || !chan) return err;
+        hipLaunchKernelGGL((amp_kernel<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde, none);
+    } else {
     if (fc && fc->hsum_out) {  // the kernel also sums the helicities
         // batches large enough to fill the GPU with one lane per event (the mixed forms when
         // their one colour operand is exact in the 16-bit type, as the scalar form assumes)
@@ -202,6 +210,7 @@ static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const sig
         hipLaunchKernelGGL((amp_kernel<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde, none);
     else
         hipLaunchKernelGGL((amp_kernel<R, false>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, nullptr, nullptr, fc ? *fc : none);
+    }
     return hipGetLastError();
 }
 }  // namespace
@@ -211,8 +220,8 @@ const ProcessDesc* process_ee_mumu()
         "ee_mumu", proc_ee_mumu::NPAR, proc_ee_mumu::NC, 16, 4, 1, 0,
         proc_ee_mumu::colour_num, 1, proc_ee_mumu::final_massive, proc_ee_mumu::orderings, 0,
         1, 1, 295.0, 295.0, proc_ee_mumu::NSLOT,
-        proc_ee_mumu::diagram_lines, 1, 1, 1, 1, 65536,
-        nullptr, 0,
+        proc_ee_mumu::diagram_lines, 1, 1, 1, 1, 1, 65536,
+        nullptr, 1,
         proc_ee_mumu::launch<double>, proc_ee_mumu::launch<float>,
     };
     return &d;

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "colorsum.hpp"
+#include "colorsum120.hpp"
 #include "process.hpp"
 #include "rambo.hpp"
 #include "select.hpp"
@@ -138,9 +139,9 @@ struct me_handle {
     int precision = ME_FP64;
     double mt = 173.0, alpha_em = 1.0 / 132.507, alpha_s = 0.118, g = 0.0;
     int n_good = 0;
-    signed char* d_hel_good = nullptr;
-    int* d_hel_index = nullptr;  // helicity-combination index of each good helicity
+    int* d_hel_index = nullptr;  // helicity-combination index of each good helicity; the next two are in its buffer
     int* d_hel_groups = nullptr;  // the good helicities by gluon helicities (HelicityGroups)
+    signed char* d_hel_good = nullptr;
     int n_hel_groups = 0;
     std::vector<signed char> h_hel_good;
     std::vector<double> hel_ratio;
@@ -354,14 +355,14 @@ struct Selection {
     double *hel_me, *w;
 };
 
-// The helicity combinations hel (n x npar signs) by gluon helicities: rows of HelicityGroups.  Empty
-// for processes without a quark line between gluons.
+// The helicity combinations hel (n x npar signs) by gluon helicities: the rows of HelicityGroups (none
+// for processes without a quark line between gluons), then its index.
 std::vector<int> helicity_group_table(const me::ProcessDesc* P, const signed char* hel, int n)
 {
     std::vector<int> t;
-    if (P->coupling != 1 || P->n_order != P->npar - 2) return t;
+    const bool quark_line = P->coupling == 1 && P->n_order == P->npar - 2;
     std::map<int, size_t> row;
-    for (int k = 0; k < n; ++k) {
+    for (int k = 0; quark_line && k < n; ++k) {
         const signed char* l = hel + (size_t)k * P->npar;
         int bits = 0;
         for (int g = 0; g < P->npar - 2; ++g) bits |= (l[g < 2 ? g : g + 2] > 0 ? 1 : 0) << g;
@@ -372,8 +373,17 @@ std::vector<int> helicity_group_table(const me::ProcessDesc* P, const signed cha
         }
         t[it->second + 1 + (l[2] > 0 ? 2 : 0) + (l[3] > 0 ? 1 : 0)] = k;
     }
+    const size_t rows = t.size();
+    t.resize(rows + P->nhel, -1);
+    for (int k = 0; k < n; ++k) {
+        int hh = 0;
+        for (int i = 0; i < P->npar; ++i) hh = 2 * hh + (hel[(size_t)k * P->npar + i] > 0 ? 1 : 0);
+        t[rows + hh] = k;
+    }
     return t;
 }
+
+me::HelicityGroups helicity_groups_at(const int* table, int n_rows) { return {table, n_rows, table + 5 * n_rows}; }
 
 // amplitude kernel + colour sum (+ the optional per-event kernels) for events [0, n) of `mom`, in
 // chunks; scratch: jamps of `chunk` events (jamp_bytes_per_event each), then the helicity-group
@@ -397,8 +407,8 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
     // of all good helicities, or with one lane per event for large enough chunks (FP64, and the
     // mixed forms of one flow whose colour operand the 16-bit type holds exactly)
     const bool hsum_waves = fused && P->hel_sum_in_kernel && n_good <= 16;
-    const bool lane_form = fused && P->lane_min_events > 0 &&
-                           (precision == ME_FP64 || (P->nc == 1 && !(fcol.lo_mask & 1)));
+    const int64_t lane_min = precision == ME_FP64 ? P->lane_min_f64 : P->lane_min_mixed;
+    const bool lane_form = fused && lane_min > 0 && (precision == ME_FP64 || !(fcol.lo_mask & 1));
     void* jamp = scratch;
     double* part = reinterpret_cast<double*>(static_cast<char*>(scratch) + (size_t)chunk * jamp_bytes_per_event);
     for (int64_t c0 = 0; c0 < n; c0 += chunk) {
@@ -407,7 +417,7 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
         const double* m = mom + c0 * P->npar * 4;
         TimedLaunch ta(h, st, 0, timed);
         const int* ch = chan ? chan + c0 : nullptr;
-        const bool hsum = hsum_waves || (lane_form && nc >= P->lane_min_events);
+        const bool hsum = hsum_waves || (lane_form && nc >= lane_min);
         hipError_t e;
         if (fused && hsum) {
             // the amplitude kernel ends with the colour sum and the helicity sum
@@ -490,9 +500,7 @@ void free_handle(me_handle* h)
         (void)hipEventDestroy(m.a);
         (void)hipEventDestroy(m.b);
     }
-    if (h->d_hel_good) (void)hipFree(h->d_hel_good);
     if (h->d_hel_index) (void)hipFree(h->d_hel_index);
-    if (h->d_hel_groups) (void)hipFree(h->d_hel_groups);
     if (h->d_aop64) (void)hipFree(h->d_aop64);
     if (h->d_aop16) (void)hipFree(h->d_aop16);
     if (h->d_aopb) (void)hipFree(h->d_aopb);
@@ -567,45 +575,44 @@ int helicity_prepass(me_handle* h, hipStream_t st)
         for (int i = 0; i < npar; ++i) all[(size_t)hh * npar + i] = ((hh >> (npar - 1 - i)) & 1) ? 1 : -1;
     const int64_t n = PREPASS_EVENTS;
     const double sqrt_s = P->coupling ? 1500.0 : 500.0;
-    signed char* d_all = nullptr;
-    int* d_groups = nullptr;
     const std::vector<int> all_groups = helicity_group_table(P, all.data(), nhel);
-    double *d_mom = nullptr, *d_out = nullptr, *d_hel = nullptr, *d_jamp = nullptr;
     const size_t jamp_per_event = jamp_scratch(P, ME_FP64, nhel);
     const int64_t pchunk =
         std::min<int64_t>(n, std::max<int64_t>(64, (int64_t)((size_t(512) << 20) / jamp_per_event) / 64 * 64));
     int groups = 1, hpg = 1;
     helicity_groups(P, nhel, pchunk, &groups, &hpg);
-    const size_t jbytes = (jamp_per_event + groups * sizeof(double)) * pchunk;
+    // one allocation for all buffers
+    const size_t sizes[6] = {n * npar * 4 * sizeof(double),      n * sizeof(double),
+                             (size_t)n * nhel * sizeof(double),  (jamp_per_event + groups * sizeof(double)) * pchunk,
+                             all_groups.size() * sizeof(int),    all.size()};
+    size_t at[7] = {0};
+    for (int i = 0; i < 6; ++i) at[i + 1] = at[i] + (sizes[i] + 255) / 256 * 256;
+    char* base = nullptr;
     int rc = ME_OK;
-    if (hipMalloc(&d_all, all.size()) != hipSuccess ||
-        (!all_groups.empty() && hipMalloc(&d_groups, all_groups.size() * sizeof(int)) != hipSuccess) || hipMalloc(&d_mom, n * npar * 4 * sizeof(double)) != hipSuccess ||
-        hipMalloc(&d_out, n * sizeof(double)) != hipSuccess ||
-        hipMalloc(&d_hel, (size_t)n * nhel * sizeof(double)) != hipSuccess || hipMalloc(&d_jamp, jbytes) != hipSuccess) {
-        rc = fail(ME_ENOMEM, "hipMalloc for the helicity pre-pass failed");
-    }
+    if (hipMalloc(&base, at[6]) != hipSuccess) rc = fail(ME_ENOMEM, "hipMalloc for the helicity pre-pass failed");
+    double* const d_mom = reinterpret_cast<double*>(base + at[0]);
+    double* const d_out = reinterpret_cast<double*>(base + at[1]);
+    double* const d_hel = reinterpret_cast<double*>(base + at[2]);
+    double* const d_jamp = reinterpret_cast<double*>(base + at[3]);
+    int* const d_groups = reinterpret_cast<int*>(base + at[4]);
+    signed char* const d_all = reinterpret_cast<signed char*>(base + at[5]);
     std::vector<double> out(n), hel((size_t)n * nhel);
     if (rc == ME_OK && hipMemcpyAsync(d_all, all.data(), all.size(), hipMemcpyHostToDevice, st) != hipSuccess)
         rc = fail(ME_EHIP, "upload of the helicity table failed");
-    if (rc == ME_OK && d_groups &&
+    if (rc == ME_OK &&
         hipMemcpyAsync(d_groups, all_groups.data(), all_groups.size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess)
         rc = fail(ME_EHIP, "upload of the helicity groups failed");
     if (rc == ME_OK && rambo(h, PREPASS_SEED, std::max(sqrt_s, 2.0 * final_mass_sum(h) + 1.0), 0, n, d_mom, st) != hipSuccess)
         rc = fail(ME_EHIP, "pre-pass RAMBO launch failed");
     if (rc == ME_OK)
-        rc = run_chunks(h, ME_FP64, d_all, {d_groups, (int)all_groups.size() / 5}, nhel, hpg, groups, pchunk, jamp_per_event, d_mom, n, d_out, d_hel, d_jamp, st);
+        rc = run_chunks(h, ME_FP64, d_all, helicity_groups_at(d_groups, ((int)all_groups.size() - nhel) / 5), nhel, hpg, groups, pchunk, jamp_per_event, d_mom, n, d_out, d_hel, d_jamp, st);
     if (rc == ME_OK) {
         if (hipMemcpyAsync(out.data(), d_out, n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipMemcpyAsync(hel.data(), d_hel, hel.size() * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             rc = fail(ME_EHIP, "pre-pass copy-back failed");
     }
-    if (d_all) (void)hipFree(d_all);
-    if (d_groups) (void)hipFree(d_groups);
-    if (d_mom) (void)hipFree(d_mom);
-    if (d_out) (void)hipFree(d_out);
-    if (d_hel) (void)hipFree(d_hel);
-    if (d_jamp) (void)hipFree(d_jamp);
+    if (base) (void)hipFree(base);
     if (rc != ME_OK) return rc;
     h->hel_ratio.assign(nhel, 0.0);
     for (int64_t e = 0; e < n; ++e) {
@@ -622,21 +629,18 @@ int helicity_prepass(me_handle* h, hipStream_t st)
     std::vector<int> index;
     for (int hh = 0; hh < nhel; ++hh)
         if (h->hel_ratio[hh] > PREPASS_THRESHOLD) index.push_back(hh);
-    if (hipMalloc(&h->d_hel_good, h->h_hel_good.size()) != hipSuccess ||
-        hipMalloc(&h->d_hel_index, index.size() * sizeof(int)) != hipSuccess)
-        return fail(ME_ENOMEM, "hipMalloc of the helicity list failed");
-    if (hipMemcpy(h->d_hel_good, h->h_hel_good.data(), h->h_hel_good.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(h->d_hel_index, index.data(), index.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
-        return fail(ME_EHIP, "upload of the helicity list failed");
     const std::vector<int> groups_table = helicity_group_table(P, h->h_hel_good.data(), h->n_good);
-    h->n_hel_groups = (int)groups_table.size() / 5;
-    if (!groups_table.empty()) {
-        if (hipMalloc(&h->d_hel_groups, groups_table.size() * sizeof(int)) != hipSuccess)
-            return fail(ME_ENOMEM, "hipMalloc of the helicity groups failed");
-        if (hipMemcpy(h->d_hel_groups, groups_table.data(), groups_table.size() * sizeof(int), hipMemcpyHostToDevice) !=
-            hipSuccess)
-            return fail(ME_EHIP, "upload of the helicity groups failed");
-    }
+    h->n_hel_groups = ((int)groups_table.size() - nhel) / 5;
+    // the helicity index, the groups and the good helicities in one buffer
+    std::vector<char> tables((index.size() + groups_table.size()) * sizeof(int) + h->h_hel_good.size());
+    std::memcpy(tables.data(), index.data(), index.size() * sizeof(int));
+    std::memcpy(tables.data() + index.size() * sizeof(int), groups_table.data(), groups_table.size() * sizeof(int));
+    std::memcpy(tables.data() + (index.size() + groups_table.size()) * sizeof(int), h->h_hel_good.data(), h->h_hel_good.size());
+    if (hipMalloc(&h->d_hel_index, tables.size()) != hipSuccess) return fail(ME_ENOMEM, "hipMalloc of the helicity tables failed");
+    h->d_hel_groups = h->d_hel_index + index.size();
+    h->d_hel_good = reinterpret_cast<signed char*>(h->d_hel_groups + groups_table.size());
+    if (hipMemcpy(h->d_hel_index, tables.data(), tables.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return fail(ME_EHIP, "upload of the helicity tables failed");
     h->bytes_resident += h->h_hel_good.size() + (index.size() + groups_table.size()) * sizeof(int);
     return ME_OK;
 }
@@ -817,7 +821,7 @@ int sigma_piped(me_handle* h, const double* momenta, int64_t n_evt, double* out,
     for (int64_t c0 = 0; c0 < n_evt && rc == ME_OK; c0 += chunk, ++k) {
         const int64_t nc = std::min(chunk, n_evt - c0);
         const int i = (int)(k & 1);
-        rc = run_chunks(h, h->precision, h->d_hel_good, {h->d_hel_groups, h->n_hel_groups}, h->n_good, h->hel_per_group, h->groups, chunk,
+        rc = run_chunks(h, h->precision, h->d_hel_good, helicity_groups_at(h->d_hel_groups, h->n_hel_groups), h->n_good, h->hel_per_group, h->groups, chunk,
                         h->jamp_bytes_per_event, momenta + c0 * npar * 4, nc, out + c0, nullptr, scr[i], hp->s[i],
                         h->profiling, nullptr, alphas ? alphas + c0 : nullptr);
     }
@@ -887,7 +891,7 @@ int sigma_impl(me_handle* h, const double* momenta, int64_t n_evt, double* out_m
     double* sde = chan ? reinterpret_cast<double*>(static_cast<char*>(scratch) +
                                                    (size_t)chunk * (h->bytes_per_event + sel_bytes))
                        : nullptr;
-    return run_chunks(h, h->precision, h->d_hel_good, {h->d_hel_groups, h->n_hel_groups}, h->n_good, h->hel_per_group, h->groups, chunk,
+    return run_chunks(h, h->precision, h->d_hel_good, helicity_groups_at(h->d_hel_groups, h->n_hel_groups), h->n_good, h->hel_per_group, h->groups, chunk,
                       h->jamp_bytes_per_event, momenta, n_evt, out_me2, out_hel, scratch, st, h->profiling,
                       sel_in ? &sel : nullptr, alphas, chan, sde);
 }
@@ -1053,7 +1057,7 @@ int me_sigma_noalloc(me_handle* h, const double* momenta, int64_t n_evt, double*
     const int64_t n_chunks = (n_evt + cap - 1) / cap;
     const int64_t chunk = ((n_evt + n_chunks - 1) / n_chunks + 63) / 64 * 64;
     const size_t jamp_per_event = fused ? per_event : h->jamp_bytes_per_event;
-    return run_chunks(h, h->precision, h->d_hel_good, {h->d_hel_groups, h->n_hel_groups}, h->n_good, h->hel_per_group, h->groups, chunk, jamp_per_event,
+    return run_chunks(h, h->precision, h->d_hel_good, helicity_groups_at(h->d_hel_groups, h->n_hel_groups), h->n_good, h->hel_per_group, h->groups, chunk, jamp_per_event,
                       momenta, n_evt, out_me2, nullptr, scr, static_cast<hipStream_t>(stream));
 }
 

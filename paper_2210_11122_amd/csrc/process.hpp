@@ -15,9 +15,9 @@ struct FusedColour {
     const void* aop_lo;  // BF16 lo tiles (BF16 form)
     uint64_t lo_mask;    // tiles with a non-zero lo part (BF16 form)
     int form;            // ME_FP64, ME_MIXED_FP16 or ME_MIXED_BF16 (me.h)
-    // processes with hel_sum_in_kernel or lane_min_events: if hsum_out is set, the kernel also
+    // processes with hel_sum_in_kernel or lane_min_f64 / lane_min_mixed: if hsum_out is set, the kernel also
     // sums the good helicities (one workgroup holding all of an event block's, or one lane per
-    // event for batches of at least lane_min_events), in groups of hel_per_group from the first
+    // event for batches of at least that size), in groups of hel_per_group from the first
     // (the order of the separate helicity-sum kernel), times hsum_scale, into hsum_out[event];
     // nothing goes to the jamp scratch
     double* hsum_out;
@@ -29,9 +29,11 @@ struct FusedColour {
 // evaluates the four quark spin configurations of one gluon configuration.  table (device):
 // n rows of 5: the gluons' signs (bit i: gluon i has helicity +), then the index among the good
 // helicities of the quark spins (-,-), (-,+), (+,-), (+,+), or -1 where that combination is not good.
+// index (device): for each helicity combination its index among the good ones, or -1.
 struct HelicityGroups {
     const int* table;
     int n;
+    const int* index;
 };
 
 // fc: null, or the fused colour sum (then chan must be null)
@@ -65,8 +67,9 @@ struct ProcessDesc {
     int sde_supported;         // single-diagram channel weights available
     int fused_colour;          // the amplitude kernels can do the colour sum themselves (FusedColour)
     int hel_sum_in_kernel;     // ... and the helicity sum (FusedColour.hsum_out; at most 16 good helicities)
-    int64_t lane_min_events;   // batches from this size can take the kernel with one lane per event, which
-                               // also sums the helicities: FP64, and mixed forms of one flow (0: none)
+    // batches from this size take the kernel with one lane per event, which also sums the helicities
+    // (0: none): FP64, and mixed forms (of one flow)
+    int64_t lane_min_f64, lane_min_mixed;
     int64_t (*aux_doubles)(int n_hel);  // doubles per event that the FP64 launch needs after the jamps (null: none)
     int recursion;             // the FP64 jamps come from the recursion, without partial slots
     amp_launch_f64 launch_f64;
@@ -74,6 +77,14 @@ struct ProcessDesc {
 };
 
 // FP64 colour-flow amplitudes by recursion (rec_*.hip); the arguments of launch_f64
+namespace rec_ee {
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
+                  double* jamp, const FusedColour* fc, hipStream_t st);
+}
+namespace rec2 {
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
+                  double* jamp, const FusedColour* fc, hipStream_t st);
+}
 namespace rec4 {
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
                   double* jamp, const FusedColour* fc, hipStream_t st);

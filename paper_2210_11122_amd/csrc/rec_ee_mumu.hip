@@ -1,0 +1,75 @@
+// rec_ee_mumu.hip -- FP64 |M|^2 of e+e- -> mu+ mu- through a photon, one lane per event.
+//
+// The amplitude is the product of an electron and a muon current over s.  The spinors and currents
+// of each helicity are formed once per event and every good combination is one product of two
+// currents; the colour sum (one flow) and the helicity sum stay in the lane, one launch for any
+// batch size.  2^20 events 69 -> 42 us per call (the bytes of momenta and results take 28 us at the
+// rate of a large copy); 8192 events 7.5 us, host time.
+#include "colorsum.hpp"
+#include "process.hpp"
+#include "recursion.hpp"
+
+namespace me {
+namespace rec_ee {
+using namespace rec;
+
+constexpr int NPAR = 4, NC = 1;
+
+// HSUM: |M|^2 to fc.hsum_out; else the jamps
+template <bool HSUM>
+__global__ __launch_bounds__(64, 2) void amp_rec(const double* __restrict__ mom, int64_t n_evt, int64_t ld,
+                                                 const int* __restrict__ index, double g, double* __restrict__ jamp,
+                                                 FusedColour fc)
+{
+    __shared__ double lds[4 * NPAR * 64];
+    const unsigned lane = threadIdx.x;
+    const int64_t e0 = xcd_remap(blockIdx.x, gridDim.x) * 64, e = e0 + lane;
+    stage_momenta<NPAR, 1>(mom, n_evt, e0, lds, lane);
+    const P4 p0 = lds_p4(lds, 0, lane), p1 = lds_p4(lds, 1, lane), p2 = lds_p4(lds, 2, lane), p3 = lds_p4(lds, 3, lane);
+    // (ubar gamma^mu s)(ubar' gamma_mu s') = 2 dot2(pair, pair')
+    const double f = 2.0 * g * g * rcp(sq(lc(p0) + lc(p1)));
+    const V4 ep[2] = {spinor(ext_vbar<double>(p0, 0.0, -1)), spinor(ext_vbar<double>(p0, 0.0, 1))};
+    const V4 em[2] = {spinor(ext_u<double>(p1, 0.0, -1)), spinor(ext_u<double>(p1, 0.0, 1))};
+    const V4 mp[2] = {spinor(ext_v<double>(p2, 0.0, -1)), spinor(ext_v<double>(p2, 0.0, 1))};
+    const V4 mm[2] = {spinor(ext_ubar<double>(p3, 0.0, -1)), spinor(ext_ubar<double>(p3, 0.0, 1))};
+    double s = 0.0, m = 0.0;
+    int in_group = 0;
+    static_for<4>([&](auto A) {
+        // good combinations with these electron helicities?
+        if (index[4 * A] < 0 && index[4 * A + 1] < 0 && index[4 * A + 2] < 0 && index[4 * A + 3] < 0) return;
+        const V4 c = pair(ep[A / 2], em[A % 2]);
+        static_for<4>([&](auto B) {
+            constexpr int h = 4 * A + B;
+            if (index[h] < 0) return;
+            C j = times(f, dot2(c, pair(mm[B % 2], mp[B / 2])));
+            pin_cx(j);   // rounded the same way whatever uses it
+            if constexpr (HSUM) {
+                // in the groups and order of the separate helicity sum
+                m += cs1(j.r, j.i, *static_cast<const double*>(fc.aop));
+                if (++in_group == fc.hel_per_group) s += m, m = 0.0, in_group = 0;
+            } else if (e < n_evt) {
+                double* const o = jamp + (int64_t)index[h] * (2 * NC) * ld + e0;
+                o[lane] = j.r;
+                (o + ld)[lane] = j.i;
+            }
+        });
+    });
+    if (!HSUM || e >= n_evt) return;
+    if (in_group) s += m;
+    (fc.hsum_out + e0)[lane] = s * fc.hsum_scale;
+}
+
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double, double g,
+                  double* jamp, const FusedColour* fc, hipStream_t st)
+{
+    if (fc && !fc->hsum_out) return hipErrorInvalidValue;   // the colour sum here includes the helicity sum
+    const dim3 grid((unsigned)((n_evt + 63) / 64));
+    if (fc)
+        hipLaunchKernelGGL(amp_rec<true>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp, *fc);
+    else
+        hipLaunchKernelGGL(amp_rec<false>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp,
+                           FusedColour{nullptr, nullptr, 0, 0, nullptr, 0.0, 1});
+    return hipGetLastError();
+}
+}  // namespace rec_ee
+}  // namespace me

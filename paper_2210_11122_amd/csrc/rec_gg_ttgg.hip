@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256, 1) void amp_rec(const double* __restrict__ mom
     // --- gluon currents, shared out among the waves
     {
         const int p = wave < 2 ? wave : wave + 2;
-        st_v(cur, S1 + wave, lane, gluon(lds_p4(lds, p, lane), (bits >> wave) & 1 ? 1 : -1, wave >= 2, gs));
+        st_v(cur, S1 + wave, lane, full(gluon(lds_p4(lds, p, lane), (bits >> wave) & 1 ? 1 : -1, wave >= 2, gs)));
     }
     __syncthreads();
     static_for<6>([&](auto P_) {

@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void level1(const double* __restrict__ mom, in
     if (e >= n_evt) return;
     if (i < NG) {
         const P4 p = mom4(mom, e, i < 2 ? i : i + 2);
-        for (int h = 0; h < 2; ++h) stm(cur, m1(i, h), lane, gluon(p, h ? 1 : -1, i >= 2, gs));
+        for (int h = 0; h < 2; ++h) stm(cur, m1(i, h), lane, full(gluon(p, h ? 1 : -1, i >= 2, gs)));
     } else if (i == NG) {
         const P4 p = mom4(mom, e, 2);
         for (int h = 0; h < 2; ++h) stm(cur, MU + h, lane, spinor(ext_ubar<double>(p, mt, h ? 1 : -1)));

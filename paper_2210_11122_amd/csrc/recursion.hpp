@@ -26,13 +26,16 @@ typedef cx<double> C;
 struct V4 {
     C a, b, c, d;
 };
-// a real momentum in the same components (d = conj(c))
+// A real momentum in the same components (d = conj(c)).  Momenta are also summed in them: measured
+// against long double, gg -> tt~gg then comes out more exact (p99.9 1.4e-13) than with sums of
+// (E, px, py, pz) converted after (4.5e-13).
 struct K4 {
     double a, b, x, y;
 };
 __device__ __forceinline__ K4 lc(const P4& p) { return {p.t + p.z, p.t - p.z, p.x, p.y}; }
 __device__ __forceinline__ K4 operator+(const K4& p, const K4& q) { return {p.a + q.a, p.b + q.b, p.x + q.x, p.y + q.y}; }
 __device__ __forceinline__ K4 operator-(const K4& p, const K4& q) { return {p.a - q.a, p.b - q.b, p.x - q.x, p.y - q.y}; }
+__device__ __forceinline__ K4 operator-(const K4& p) { return {-p.a, -p.b, -p.x, -p.y}; }
 __device__ __forceinline__ double sq(const K4& p) { return fma(p.a, p.b, -fma(p.x, p.x, p.y * p.y)); }
 
 __device__ __forceinline__ C cmul(C a, C b) { return {fma(a.r, b.r, -a.i * b.i), fma(a.r, b.i, a.i * b.r)}; }
@@ -66,14 +69,53 @@ __device__ __forceinline__ V4 axmy(const V4& acc, C s, const V4& A)
 {
     return {cfms(s, A.a, acc.a), cfms(s, A.b, acc.b), cfms(s, A.c, acc.c), cfms(s, A.d, acc.d)};
 }
+// A polarisation vector (times g): no time component, a real longitudinal one, so a = G3 is real
+// and b = -a: five numbers, and products with it take three quarters of the operations.
+struct E4 {
+    double a;
+    C c, d;
+};
+__device__ __forceinline__ C conj(C a) { return {a.r, -a.i}; }
+// the vector of the other helicity
+__device__ __forceinline__ E4 flip(const E4& e) { return {-e.a, neg(conj(e.d)), neg(conj(e.c))}; }
+__device__ __forceinline__ V4 full(const E4& e) { return {{e.a, 0.0}, {-e.a, 0.0}, e.c, e.d}; }
+__device__ __forceinline__ C scaled_add(C o, double f, C x) { return {fma(f, x.r, o.r), fma(f, x.i, o.i)}; }
+__device__ __forceinline__ C dot2(const E4& A, const V4& B)
+{
+    const C t = B.b - B.a;
+    return cfms(A.d, B.c, cfms(A.c, B.d, {A.a * t.r, A.a * t.i}));
+}
+__device__ __forceinline__ C dot2(const V4& A, const E4& B) { return dot2(B, A); }
+__device__ __forceinline__ C dot2(const E4& A, const E4& B)
+{
+    return cfms(A.d, B.c, cfms(A.c, B.d, {-2.0 * (A.a * B.a), 0.0}));
+}
+__device__ __forceinline__ C dot2(const E4& A, const K4& k)
+{
+    C o = {A.a * (k.b - k.a), 0.0};
+    o.r = fma(-A.c.r, k.x, fma(-A.c.i, k.y, o.r));
+    o.i = fma(-A.c.i, k.x, A.c.r * k.y);
+    o.r = fma(-A.d.r, k.x, fma(A.d.i, k.y, o.r));
+    o.i = fma(-A.d.i, k.x, fma(-A.d.r, k.y, o.i));
+    return o;
+}
+__device__ __forceinline__ V4 axpy(const V4& acc, C s, const E4& A)
+{
+    return {scaled_add(acc.a, A.a, s), scaled_add(acc.b, -A.a, s), cfma(s, A.c, acc.c), cfma(s, A.d, acc.d)};
+}
+__device__ __forceinline__ V4 axmy(const V4& acc, C s, const E4& A)
+{
+    return {scaled_add(acc.a, -A.a, s), scaled_add(acc.b, A.a, s), cfms(s, A.c, acc.c), cfms(s, A.d, acc.d)};
+}
+
 // k/2 + q
 __device__ __forceinline__ K4 half_plus(const K4& k, const K4& q)
 {
     return {fma(0.5, k.a, q.a), fma(0.5, k.b, q.b), fma(0.5, k.x, q.x), fma(0.5, k.y, q.y)};
 }
 // acc + V(A, B); AB = 2 A.B.  SGN = -1: acc - V(A, B)
-template <int SGN = 1>
-__device__ __forceinline__ V4 vvv_acc(const V4& acc, const V4& A, const K4& ka, const V4& B, const K4& kb, C AB)
+template <int SGN = 1, class TA, class TB>
+__device__ __forceinline__ V4 vvv_acc(const V4& acc, const TA& A, const K4& ka, const TB& B, const K4& kb, C AB)
 {
     const K4 k = ka - kb;
     const C h = (SGN * 0.5) * AB, s = dot2(A, half_plus(ka, kb)), t = dot2(B, half_plus(kb, ka));
@@ -86,26 +128,23 @@ __device__ __forceinline__ V4 vvv_acc(const V4& acc, const V4& A, const K4& ka, 
     return o;
 }
 // acc + Q(A, B, D) from AB = 2 A.B, BD = 2 B.D, AD = 2 A.D; SGN as above
-template <int SGN = 1>
-__device__ __forceinline__ V4 vvvv_acc(const V4& acc, const V4& A, const V4& B, const V4& D, C AB, C BD, C AD)
+template <int SGN = 1, class TA, class TB, class TD>
+__device__ __forceinline__ V4 vvvv_acc(const V4& acc, const TA& A, const TB& B, const TD& D, C AB, C BD, C AD)
 {
     const V4 o = axpy(axpy(acc, (SGN * 0.5) * BD, A), (SGN * 0.5) * AB, D);
     return SGN > 0 ? axmy(o, AD, B) : axpy(o, AD, B);
 }
 __device__ __forceinline__ V4 operator-(const V4& x) { return {neg(x.a), neg(x.b), neg(x.c), neg(x.d)}; }
-__device__ __forceinline__ K4 operator-(const K4& p) { return {-p.a, -p.b, -p.x, -p.y}; }
 __device__ __forceinline__ V4 zero4() { return {{0, 0}, {0, 0}, {0, 0}, {0, 0}}; }
 
 // polarisation vector of a gluon, times g
-__device__ __forceinline__ V4 gluon(const P4& p, int lam, bool outgoing, double g)
+__device__ __forceinline__ E4 gluon(const P4& p, int lam, bool outgoing, double g)
 {
-    const W4<double> w = ext_vec<double>(p, lam, outgoing);
-    V4 v;
-    v.a = {g * w.c[3].r, g * w.c[3].i};
-    v.b = {-v.a.r, -v.a.i};
-    v.c = {g * (w.c[1].r - w.c[2].i), g * (w.c[1].i + w.c[2].r)};
-    v.d = {g * (w.c[1].r + w.c[2].i), g * (w.c[1].i - w.c[2].r)};
-    return v;
+    const W4<double> w = ext_vec<double>(p, 1, outgoing);
+    const E4 e = {g * w.c[3].r,
+                  {g * (w.c[1].r - w.c[2].i), g * (w.c[1].i + w.c[2].r)},
+                  {g * (w.c[1].r + w.c[2].i), g * (w.c[1].i - w.c[2].r)}};
+    return lam > 0 ? e : flip(e);
 }
 __device__ __forceinline__ V4 spinor(const W4<double>& w) { return {w.c[0], w.c[1], w.c[2], w.c[3]}; }
 
@@ -137,6 +176,36 @@ __device__ __forceinline__ V4 col(const V4& G, const V4& s)
 {
     return {cfms(G.d, s.d, cmul(G.b, s.c)), cfms(G.c, s.c, cmul(G.a, s.d)), cfma(G.d, s.b, cmul(G.a, s.a)),
             cfma(G.b, s.b, cmul(G.c, s.a))};
+}
+// the same with a polarisation vector
+template <int SGN = 1>
+__device__ __forceinline__ V4 row_acc(const V4& o, const V4& u, const E4& G)
+{
+    if (SGN > 0)
+        return {cfma(u.d, G.c, scaled_add(o.a, G.a, u.c)), cfma(u.c, G.d, scaled_add(o.b, -G.a, u.d)),
+                cfms(u.b, G.c, scaled_add(o.c, -G.a, u.a)), cfms(u.a, G.d, scaled_add(o.d, G.a, u.b))};
+    return {cfms(u.d, G.c, scaled_add(o.a, -G.a, u.c)), cfms(u.c, G.d, scaled_add(o.b, G.a, u.d)),
+            cfma(u.b, G.c, scaled_add(o.c, G.a, u.a)), cfma(u.a, G.d, scaled_add(o.d, -G.a, u.b))};
+}
+__device__ __forceinline__ C times(double f, C x) { return {f * x.r, f * x.i}; }
+__device__ __forceinline__ V4 row(const V4& u, const E4& G)
+{
+    return {cfma(u.d, G.c, times(G.a, u.c)), cfma(u.c, G.d, times(-G.a, u.d)), cfms(u.b, G.c, times(-G.a, u.a)),
+            cfms(u.a, G.d, times(G.a, u.b))};
+}
+template <int SGN = 1>
+__device__ __forceinline__ V4 col_acc(const V4& o, const E4& G, const V4& s)
+{
+    if (SGN > 0)
+        return {cfms(G.d, s.d, scaled_add(o.a, -G.a, s.c)), cfms(G.c, s.c, scaled_add(o.b, G.a, s.d)),
+                cfma(G.d, s.b, scaled_add(o.c, G.a, s.a)), cfma(G.c, s.a, scaled_add(o.d, -G.a, s.b))};
+    return {cfma(G.d, s.d, scaled_add(o.a, G.a, s.c)), cfma(G.c, s.c, scaled_add(o.b, -G.a, s.d)),
+            cfms(G.d, s.b, scaled_add(o.c, -G.a, s.a)), cfms(G.c, s.a, scaled_add(o.d, G.a, s.b))};
+}
+__device__ __forceinline__ V4 col(const E4& G, const V4& s)
+{
+    return {cfms(G.d, s.d, times(-G.a, s.c)), cfms(G.c, s.c, times(G.a, s.d)), cfma(G.d, s.b, times(G.a, s.a)),
+            cfma(G.c, s.a, times(-G.a, s.b))};
 }
 // a quark propagator -(qslash + m) / (q^2 - m^2) in a form ready to apply
 struct Prop {

@@ -105,7 +105,7 @@ HEL_SUM_IN_KERNEL = {"ee_mumu", "ee_mumu_z"}
 # good helicities in turn (amp_lanes): no helicity waves to combine, no barrier after the
 # momentum staging.  In the mixed forms the one-flow 16-bit tile has a scalar equivalent
 # (colorsum.hpp, cs1_h16), so they use it too
-LANE_PER_EVENT = {"ee_mumu", "ee_mumu_z", "gg_tt"}
+LANE_PER_EVENT = {"ee_mumu", "ee_mumu_z"}
 # the batch size from which calls take that kernel (smaller batches fill the GPU only with a
 # wave per helicity)
 LANE_MIN_EVENTS = 1 << 16
@@ -119,7 +119,7 @@ LANE_HOIST_EXT = True
 LANE_MIN_WAVES = (2, 3)
 # processes whose FP64 colour-flow amplitudes come from the colour-ordered recursion (csrc/rec_*.hip,
 # namespace): the FP64 diagram program then runs for the channel weights alone and keeps no jamps
-RECURSION = {"gg_ttgg": "rec4", "gg_ttggg": "rec5"}
+RECURSION = {"ee_mumu": "rec_ee", "gg_tt": "rec2", "gg_ttgg": "rec4", "gg_ttggg": "rec5"}
 ALL_PROCESSES = ["ee_mumu", "gg_tt", "gg_ttg", "gg_ttgg", "gg_ttggg", "gg_gg", "ee_mumu_z"]
 # electroweak constants of ee -> mumu with Z exchange: M_Z, Gamma_Z, M_W [GeV]
 EW_MZ, EW_WZ, EW_MW = 91.188, 2.441404, 80.419
@@ -880,6 +880,13 @@ class Process:
                 L.append("        if (e != hipSuccess) return e;")
                 L.append("    }")
             else:
+                if nm in RECURSION:
+                    L.append("    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for")
+                    L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);")
+                    L.append("        if (err != hipSuccess || !chan) return err;")
+                    L.append(f"        hipLaunchKernelGGL(({kname}<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
+                             f"ld, hel, n_good, mt, gs, jamp, chan, sde, none);")
+                    L.append("    } else {")
                 if fused and (self.name in HEL_SUM_IN_KERNEL or nm in LANE_PER_EVENT):
                     L.append("    if (fc && fc->hsum_out) {  // the kernel also sums the helicities")
                     if nm in LANE_PER_EVENT:
@@ -899,21 +906,15 @@ class Process:
                         L.append("        return hipErrorInvalidValue;  // below the lane kernel's batch size: no such kernel")
                     L.append("    }")
                 tail = ", none" if fused else ""
-                if nm in RECURSION:
-                    L.append("    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for")
-                    L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);")
-                    L.append("        if (err != hipSuccess || !chan) return err;")
-                    L.append(f"        hipLaunchKernelGGL(({kname}<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
-                             f"ld, hel, n_good, mt, gs, jamp, chan, sde{tail});")
-                    L.append("    } else if (chan)")
-                else:
-                    L.append("    if (chan)")
+                L.append("    if (chan)")
                 L.append(f"        hipLaunchKernelGGL(({kname}<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
                          f"ld, hel, n_good, mt, gs, jamp, chan, sde{tail});")
                 L.append("    else")
                 tail = ", fc ? *fc : none" if fused else ""
                 L.append(f"        hipLaunchKernelGGL(({kname}<R, false>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
                          f"ld, hel, n_good, mt, gs, jamp, nullptr, nullptr{tail});")
+                if nm in RECURSION:
+                    L.append("    }")
         if self.segments:
             if nm in RECURSION:
                 L.append("    if constexpr (sizeof(R) == 4)")
@@ -931,7 +932,7 @@ class Process:
                  f"{n_order},")
         L.append(f"        {self.n_diagrams}, {self.n_amplitudes}, {fl}.0, {self.flops_exec}.0, proc_{nm}::NSLOT,")
         L.append(f"        proc_{nm}::diagram_lines, {nlines}, {0 if self.lines is None else 1}, {1 if fused else 0}, "
-                 f"{1 if fused and nm in HEL_SUM_IN_KERNEL else 0}, {LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0},")
+                 f"{1 if fused and nm in HEL_SUM_IN_KERNEL else 0}, {1 if nm in ('ee_mumu', 'gg_tt') else LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0}, {LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0},")
         L.append(f"        {'rec5::aux_doubles' if nm == 'gg_ttggg' else 'nullptr'}, {1 if nm in RECURSION else 0},")
         L.append(f"        proc_{nm}::launch<double>, proc_{nm}::launch<float>,")
         L.append("    };")
@@ -1059,7 +1060,8 @@ class Process:
             L.append("    R Jr[2 * NW];")
             L.append("#pragma unroll")
             L.append("    for (int s = 0; s < 2 * NW; ++s) Jr[s] = (R)0;")
-            L.append("#define JADD(s, ri, v) (Jr[2 * (s) + (ri)] += (v))")
+            L.append("#define JADD(s, ri, v) " + ("do { if constexpr (JAMPS) Jr[2 * (s) + (ri)] += (v); } while (0)" if rec
+                                                  else "(Jr[2 * (s) + (ri)] += (v))"))
             L.append("#define JGET(s, ri) Jr[2 * (s) + (ri)]")
         if mode == "slots":
             L.append(("    [[maybe_unused]] " if rec else "    ") + "R* const po = jamp + (int64_t)n_good * (2 * NC) * ld + (int64_t)h * (2 * NSLOT) * ld + e;")

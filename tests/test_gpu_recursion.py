@@ -13,7 +13,7 @@ from tests import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-PROCESSES = ["gg_ttgg", "gg_ttggg"]
+PROCESSES = ["ee_mumu", "gg_tt", "gg_ttgg", "gg_ttggg"]
 
 
 def check(name, p, got, params):
@@ -27,7 +27,7 @@ def check(name, p, got, params):
 @pytest.mark.parametrize("name", PROCESSES)
 def test_block_edges(name, n):
     from paper_2210_11122_amd import Process
-    n = min(n, 65) if name == "gg_ttggg" else n
+    n = min(n, 65) if name == "gg_ttggg" else n + 65536 if n == 129 and name in ("ee_mumu", "gg_tt") else n
     print(f"case recursion {name} n={n}", flush=True)
     proc = Process(name, m_top=W.M_TOP, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
     p = oracle.rambo(31, W.sqrt_s(name), W.final_masses(name), n)
@@ -42,11 +42,14 @@ def test_block_edges(name, n):
     sel, h0, c0 = proc.select(x, zero, zero)
     _, h1, c1 = proc.select(x, one, one)
     assert torch.equal(sel, me) and bool((c0 == 0).all()) and bool((c1 == proc.info["n_colors"] - 1).all())
+    # the same events through the separate colour sum
+    proc.set_fused_colour(False)
+    assert torch.equal(proc.sigma(x), me)
     good = proc.good_helicities_index()
     assert bool((h0 == good[0]).all()) and bool((h1 == good[-1]).all())
 
 
-@pytest.mark.parametrize("name,n", [("gg_ttgg", 65), ("gg_ttggg", 3)])
+@pytest.mark.parametrize("name,n", [("gg_tt", 65), ("gg_ttgg", 65), ("gg_ttggg", 3)])
 def test_massless_tops_leave_spin_configurations_out(name, n):
     from paper_2210_11122_amd import Process
     print(f"case recursion massless {name} n={n}", flush=True)
