@@ -44,7 +44,7 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
     const W4<R> w0 = ext_vbar<R>(PM(0), 0.0, lam[0]);
     const W4<R> w1 = ext_u<R>(PM(1), 0.0, lam[1]);
     const W4<R> w2 = ext_v<R>(PM(2), 0.0, lam[2]);
@@ -185,15 +185,13 @@ static const int diagram_lines[] = {12};
 template <class R>
 static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, const HelicityGroups& hg, hipStream_t st)
 {
-    if (fc && (chan || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
+    if (fc && ((chan && sizeof(R) == 4) || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
     const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
     constexpr int WG = sizeof(R) == 8 ? 1 : 1;  // waves (helicities) per workgroup
     int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);
     if (blocks == 0) return hipSuccess;
-    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for
-        const hipError_t err = rec_ee::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);
-        if (err != hipSuccess || !chan) return err;
-        hipLaunchKernelGGL((amp_kernel<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde, none);
+    if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion
+        return rec_ee::launch(mom, n_evt, ld, hg, mt, gs, jamp, chan, sde, fc, st);
     } else {
     if (fc && fc->hsum_out) {  // the kernel also sums the helicities
         // batches large enough to fill the GPU with one lane per event (the mixed forms when
@@ -221,7 +219,7 @@ const ProcessDesc* process_ee_mumu()
         proc_ee_mumu::colour_num, 1, proc_ee_mumu::final_massive, proc_ee_mumu::orderings, 0,
         1, 1, 295.0, 295.0, proc_ee_mumu::NSLOT,
         proc_ee_mumu::diagram_lines, 1, 1, 1, 1, 1, 65536,
-        nullptr, 1,
+        nullptr, 1, 1,
         proc_ee_mumu::launch<double>, proc_ee_mumu::launch<float>,
     };
     return &d;

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 4 
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
     P4 m0_0 = PM(0);
     P4 m0_1 = PM(1);
     P4 m0_2 = PM(2);
@@ -136,15 +136,13 @@ static const int diagram_lines[] = {10, 6, 12};
 template <class R>
 static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, const HelicityGroups& hg, hipStream_t st)
 {
-    if (fc && (chan || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
+    if (fc && ((chan && sizeof(R) == 4) || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
     const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
     constexpr int WG = sizeof(R) == 8 ? 4 : 4;  // waves (helicities) per workgroup
     int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);
     if (blocks == 0) return hipSuccess;
-    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for
-        const hipError_t err = rec2::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);
-        if (err != hipSuccess || !chan) return err;
-        hipLaunchKernelGGL((amp_kernel<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde, none);
+    if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion
+        return rec2::launch(mom, n_evt, ld, hg, mt, gs, jamp, chan, sde, fc, st);
     } else {
     if (chan)
         hipLaunchKernelGGL((amp_kernel<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde, none);
@@ -161,7 +159,7 @@ const ProcessDesc* process_gg_tt()
         proc_gg_tt::colour_num, 3, proc_gg_tt::final_massive, proc_gg_tt::orderings, 2,
         3, 3, 835.0, 835.0, proc_gg_tt::NSLOT,
         proc_gg_tt::diagram_lines, 1, 1, 1, 0, 1, 0,
-        nullptr, 1,
+        nullptr, 1, 1,
         proc_gg_tt::launch<double>, proc_gg_tt::launch<float>,
     };
     return &d;

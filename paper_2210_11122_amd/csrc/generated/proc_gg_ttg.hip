@@ -37,17 +37,18 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     { const W4<R> t = ext_v<R>(PM(3), mt, lam[3]); if constexpr (XWP[1] >= 0) st_w4<R>(xw, XWP[1], lane, t); else xwr[1] = t; }
     { const W4<R> t = ext_vec<R>(PM(1), lam[1], false); if constexpr (XWP[2] >= 0) st_w4<R>(xw, XWP[2], lane, t); else xwr[2] = t; }
 #define XW(k) (XWP[k] >= 0 ? ld_w4<R>(xw, XWP[k], lane) : xwr[k])
+    constexpr bool JAMPS = sizeof(R) == 4;  // FP64: the channel weights only
     constexpr int NW = 6;
     R Jr[2 * NW];
 #pragma unroll
     for (int s = 0; s < 2 * NW; ++s) Jr[s] = (R)0;
-#define JADD(s, ri, v) (Jr[2 * (s) + (ri)] += (v))
+#define JADD(s, ri, v) do { if constexpr (JAMPS) Jr[2 * (s) + (ri)] += (v); } while (0)
 #define JGET(s, ri) Jr[2 * (s) + (ri)]
     cx<R> a, sa;
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
     P4 m0_0 = PM(0);
     P4 m0_2 = PM(2);
     P4 m0_3 = PM(3);
@@ -259,6 +260,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
             so[ld] = sde_all;
         }
     }
+    if constexpr (JAMPS) {
     if (fc.aop) {  // colour sum here: D |M_h|^2 of this lane's event, to [h][event]
         double me_h;
         if constexpr (sizeof(R) == 8) {
@@ -292,6 +294,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
 #pragma unroll
         for (int s = 0; s < 2 * NC; ++s) o[s * ld] = jo[s];
     }
+    }
 #undef PM
 #undef GB
 #undef XW
@@ -311,15 +314,19 @@ static const int diagram_lines[] = {24, 26, 10, 26, 18, 26, 6, 24, 6, 22, 6, 14,
 template <class R>
 static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel, int n_good, double mt, double gs, R* jamp, const int* chan, double* sde, const FusedColour* fc, const HelicityGroups& hg, hipStream_t st)
 {
-    if (fc && (chan || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
+    if (fc && ((chan && sizeof(R) == 4) || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
     const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
     constexpr int WG = sizeof(R) == 8 ? 4 : 4;  // waves (helicities) per workgroup
     int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);
     if (blocks == 0) return hipSuccess;
+    if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion
+        return rec3::launch(mom, n_evt, ld, hg, n_good, mt, gs, jamp, chan, sde, fc, st);
+    } else {
     if (chan)
         hipLaunchKernelGGL((amp_kernel<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde, none);
     else
         hipLaunchKernelGGL((amp_kernel<R, false>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, nullptr, nullptr, fc ? *fc : none);
+    }
     return hipGetLastError();
 }
 }  // namespace
@@ -329,8 +336,8 @@ const ProcessDesc* process_gg_ttg()
         "gg_ttg", proc_gg_ttg::NPAR, proc_gg_ttg::NC, 32, 256, 1, 1,
         proc_gg_ttg::colour_num, 9, proc_gg_ttg::final_massive, proc_gg_ttg::orderings, 3,
         16, 18, 3647.0, 3647.0, proc_gg_ttg::NSLOT,
-        proc_gg_ttg::diagram_lines, 2, 1, 1, 0, 0, 0,
-        nullptr, 0,
+        proc_gg_ttg::diagram_lines, 2, 1, 1, 0, 16384, 0,
+        nullptr, 1, 1,
         proc_gg_ttg::launch<double>, proc_gg_ttg::launch<float>,
     };
     return &d;

@@ -395,9 +395,10 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
 {
     const me::ProcessDesc* P = h->P;
     const bool fp64 = precision == ME_FP64;
-    // the colour sum inside the amplitude kernel: plain |M|^2 only (the selection, the
-    // per-helicity output and the channel weights read the jamps)
-    const bool fused = P->fused_colour && h->fuse_colour && !sel && !out_hel && !chan;
+    // the colour sum inside the amplitude kernel: plain |M|^2 (the selection, the per-helicity output
+    // and, but for the kernels that apply them, the channel weights read the jamps)
+    const bool chan_fused = chan && precision == ME_FP64 && P->channel_in_kernel;
+    const bool fused_any = P->fused_colour && h->fuse_colour && !sel && !out_hel && (!chan || chan_fused);
     // the operand tables of the separate colour sum of this precision
     me::FusedColour fcol{nullptr, nullptr, 0, precision, nullptr, 0.0, hel_per_group};
     if (precision == ME_FP64) fcol.aop = h->d_aop64, fcol.form = ME_FP64;
@@ -406,9 +407,9 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
     // small processes: the amplitude kernel also sums the helicities (one launch), in a workgroup
     // of all good helicities, or with one lane per event for large enough chunks (FP64, and the
     // mixed forms of one flow whose colour operand the 16-bit type holds exactly)
-    const bool hsum_waves = fused && P->hel_sum_in_kernel && n_good <= 16;
+    const bool hsum_waves = fused_any && P->hel_sum_in_kernel && n_good <= 16;
     const int64_t lane_min = precision == ME_FP64 ? P->lane_min_f64 : P->lane_min_mixed;
-    const bool lane_form = fused && lane_min > 0 && (precision == ME_FP64 || !(fcol.lo_mask & 1));
+    const bool lane_form = fused_any && lane_min > 0 && (precision == ME_FP64 || !(fcol.lo_mask & 1));
     void* jamp = scratch;
     double* part = reinterpret_cast<double*>(static_cast<char*>(scratch) + (size_t)chunk * jamp_bytes_per_event);
     for (int64_t c0 = 0; c0 < n; c0 += chunk) {
@@ -418,13 +419,14 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
         TimedLaunch ta(h, st, 0, timed);
         const int* ch = chan ? chan + c0 : nullptr;
         const bool hsum = hsum_waves || (lane_form && nc >= lane_min);
+        const bool fused = fused_any && (hsum || !chan);   // with a channel weight: only where it is applied in the kernel
         hipError_t e;
         if (fused && hsum) {
             // the amplitude kernel ends with the colour sum and the helicity sum
             fcol.hsum_out = out + c0;
             fcol.hsum_scale = 1.0 / ((double)P->colour_den * P->avg);
-            e = fp64 ? P->launch_f64(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<double*>(jamp), nullptr,
-                                     nullptr, &fcol, hg, st)
+            e = fp64 ? P->launch_f64(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<double*>(jamp), ch, nullptr,
+                                     &fcol, hg, st)
                      : P->launch_f32(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<float*>(jamp), nullptr,
                                      nullptr, &fcol, hg, st);
             ta.done();
@@ -456,7 +458,7 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             tc.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("colour-sum kernel: ") + hipGetErrorString(e));
         }
-        if (chan) {
+        if (chan && !fused) {
             hipLaunchKernelGGL(sde_apply, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, out + c0, sde, ch,
                                n_good, ld, nc);
             e = hipGetLastError();

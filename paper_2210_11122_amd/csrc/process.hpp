@@ -36,7 +36,7 @@ struct HelicityGroups {
     const int* index;
 };
 
-// fc: null, or the fused colour sum (then chan must be null)
+// fc: null, or the fused colour sum (then chan must be null, but for channel_in_kernel)
 typedef hipError_t (*amp_launch_f64)(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel,
                                      int n_good, double mt, double g, double* jamp, const int* chan, double* sde,
                                      const FusedColour* fc, const HelicityGroups& hg, hipStream_t st);
@@ -71,6 +71,7 @@ struct ProcessDesc {
     // (0: none): FP64, and mixed forms (of one flow)
     int64_t lane_min_f64, lane_min_mixed;
     int64_t (*aux_doubles)(int n_hel);  // doubles per event that the FP64 launch needs after the jamps (null: none)
+    int channel_in_kernel;     // the FP64 kernel that sums the helicities also applies the channel weight (chan with fc)
     int recursion;             // the FP64 jamps come from the recursion, without partial slots
     amp_launch_f64 launch_f64;
     amp_launch_f32 launch_f32;
@@ -79,11 +80,15 @@ struct ProcessDesc {
 // FP64 colour-flow amplitudes by recursion (rec_*.hip); the arguments of launch_f64
 namespace rec_ee {
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
-                  double* jamp, const FusedColour* fc, hipStream_t st);
+                  double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st);
 }
 namespace rec2 {
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
-                  double* jamp, const FusedColour* fc, hipStream_t st);
+                  double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st);
+}
+namespace rec3 {
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, int n_good, double mt, double gs,
+                  double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st);
 }
 namespace rec4 {
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,

@@ -19,7 +19,7 @@ constexpr int NPAR = 4, NC = 1;
 template <bool HSUM>
 __global__ __launch_bounds__(64, 2) void amp_rec(const double* __restrict__ mom, int64_t n_evt, int64_t ld,
                                                  const int* __restrict__ index, double g, double* __restrict__ jamp,
-                                                 FusedColour fc)
+                                                 const int* __restrict__ chan, double* __restrict__ sde, FusedColour fc)
 {
     __shared__ double lds[4 * NPAR * 64];
     const unsigned lane = threadIdx.x;
@@ -51,23 +51,33 @@ __global__ __launch_bounds__(64, 2) void amp_rec(const double* __restrict__ mom,
                 double* const o = jamp + (int64_t)index[h] * (2 * NC) * ld + e0;
                 o[lane] = j.r;
                 (o + ld)[lane] = j.i;
+                if (chan) {   // one diagram: its square is the sum over all
+                    ChannelSums w;
+                    w.add(0, 1.0, chan[e], j);
+                    double* const t = sde + (int64_t)index[h] * 2 * ld + e0;
+                    t[lane] = w.ch;
+                    (t + ld)[lane] = w.all;
+                }
             }
         });
     });
     if (!HSUM || e >= n_evt) return;
     if (in_group) s += m;
-    (fc.hsum_out + e0)[lane] = s * fc.hsum_scale;
+    double r = s * fc.hsum_scale;
+    if (chan && chan[e] > 0) r *= 0.0;   // one diagram, 0: its weight is 1, any other channel's 0
+    (fc.hsum_out + e0)[lane] = r;
 }
 
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double, double g,
-                  double* jamp, const FusedColour* fc, hipStream_t st)
+                  double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st)
 {
     if (fc && !fc->hsum_out) return hipErrorInvalidValue;   // the colour sum here includes the helicity sum
     const dim3 grid((unsigned)((n_evt + 63) / 64));
     if (fc)
-        hipLaunchKernelGGL(amp_rec<true>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp, *fc);
+        hipLaunchKernelGGL(amp_rec<true>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp, chan,
+                           nullptr, *fc);
     else
-        hipLaunchKernelGGL(amp_rec<false>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp,
+        hipLaunchKernelGGL(amp_rec<false>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp, chan, sde,
                            FusedColour{nullptr, nullptr, 0, 0, nullptr, 0.0, 1});
     return hipGetLastError();
 }

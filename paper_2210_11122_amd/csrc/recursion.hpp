@@ -256,8 +256,9 @@ __device__ __forceinline__ V4 pair(const V4& u, const V4& s)
 struct V4x2 {
     V4 v[2];
 };
-__device__ __forceinline__ V4x2 three_currents(const V4& X, const K4& kx, const V4& Y, const K4& ky, const V4& Z,
-                                               const K4& kz, const V4& XY, const V4& XZ, const V4& YZ)
+template <class T>
+__device__ __forceinline__ V4x2 three_currents(const T& X, const K4& kx, const T& Y, const K4& ky, const T& Z, const K4& kz,
+                                               const V4& XY, const V4& XZ, const V4& YZ)
 {
     const C xy = dot2(X, Y), yz = dot2(Y, Z), xz = dot2(X, Z);
     const double f = -rcp(sq(kx + ky + kz));
@@ -297,6 +298,19 @@ __device__ __forceinline__ void pin_v(V4& v)
 {
     asm volatile("" : "+v"(v.a.r), "+v"(v.a.i), "+v"(v.b.r), "+v"(v.b.i), "+v"(v.c.r), "+v"(v.c.i), "+v"(v.d.r), "+v"(v.d.i));
 }
+
+// The channel-weight sums of one helicity: K |a|^2 of every diagram's amplitude, and of the event's
+// channel.  Pinned: put off to the end of the program they would hold every amplitude until then.
+struct ChannelSums {
+    double ch = 0.0, all = 0.0;
+    __device__ __forceinline__ void add(int diagram, double weight, int channel, C a)
+    {
+        const double w = weight * fma(a.r, a.r, a.i * a.i);
+        all += w;
+        ch += diagram == channel ? w : 0.0;
+        asm volatile("" : "+v"(all), "+v"(ch));
+    }
+};
 
 // vectors in LDS: slot k holds (re, im) pairs of its components at [(4 k + m) * 64 + lane]
 __device__ __forceinline__ void st_v(double* base, int k, int lane, const V4& v)

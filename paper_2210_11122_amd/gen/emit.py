@@ -119,7 +119,13 @@ LANE_HOIST_EXT = True
 LANE_MIN_WAVES = (2, 3)
 # processes whose FP64 colour-flow amplitudes come from the colour-ordered recursion (csrc/rec_*.hip,
 # namespace): the FP64 diagram program then runs for the channel weights alone and keeps no jamps
-RECURSION = {"ee_mumu": "rec_ee", "gg_tt": "rec2", "gg_ttgg": "rec4", "gg_ttggg": "rec5"}
+RECURSION = {"ee_mumu": "rec_ee", "gg_tt": "rec2", "gg_ttg": "rec3", "gg_ttgg": "rec4", "gg_ttggg": "rec5"}
+# ... and also the channel weights (no FP64 instance of the diagram program)
+CHANNELS_IN_RECURSION = {"ee_mumu", "gg_tt", "gg_ttg"}
+# ... and whose FP64 kernel also sums the helicities: from this batch size on.  gg_ttg: with the sum a
+# workgroup takes the 8 gluon configurations of an event block in two turns; below 16384 events that
+# leaves CUs idle, and two workgroups share them
+FP64_HSUM_EVENTS = {"ee_mumu": 1, "gg_tt": 1, "gg_ttg": 16384}
 ALL_PROCESSES = ["ee_mumu", "gg_tt", "gg_ttg", "gg_ttgg", "gg_ttggg", "gg_gg", "ee_mumu_z"]
 # electroweak constants of ee -> mumu with Z exchange: M_Z, Gamma_Z, M_W [GeV]
 EW_MZ, EW_WZ, EW_MW = 91.188, 2.441404, 80.419
@@ -556,7 +562,9 @@ class Process:
                 self.emit_groups.append(line)
                 out.append(f"    a = {fn}({', '.join(args)});")
                 flops[0] += amp_flops(fn)
-                out.append("    pin_cx<R>(a);")
+                # a shared vertex feeds the jamps only: unpinned, it is left out where none are kept
+                shared = len(grp) > 1 and self.name in RECURSION
+                out.append("    if constexpr (JAMPS) pin_cx<R>(a);" if shared else "    pin_cx<R>(a);")
                 if self.fd_index is not None:
                     if len(grp) == 1:
                         di = members[grp[0]][0]
@@ -858,7 +866,8 @@ class Process:
         if not fused:
             L.append("    if (fc) return hipErrorInvalidValue;  // no fused colour sum for this process")
         else:
-            L.append("    if (fc && (chan || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) "
+            no_chan = "(chan && sizeof(R) == 4)" if nm in CHANNELS_IN_RECURSION else "chan"
+            L.append(f"    if (fc && ({no_chan} || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) "
                      "return hipErrorInvalidValue;")
             L.append("    const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};")
         g64, g32 = WAVES_PER_GROUP.get(self.name, (1, 1))
@@ -882,10 +891,15 @@ class Process:
             else:
                 if nm in RECURSION:
                     L.append("    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for")
-                    L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);")
-                    L.append("        if (err != hipSuccess || !chan) return err;")
-                    L.append(f"        hipLaunchKernelGGL(({kname}<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
-                             f"ld, hel, n_good, mt, gs, jamp, chan, sde, none);")
+                    if nm in CHANNELS_IN_RECURSION:
+                        L[-1] = "    if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion"
+                        L.append(f"        return {RECURSION[nm]}::launch(mom, n_evt, ld, hg, {'n_good, ' if nm == 'gg_ttg' else ''}mt, gs, jamp, "
+                                 "chan, sde, fc, st);")
+                    else:
+                        L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);")
+                        L.append("        if (err != hipSuccess || !chan) return err;")
+                        L.append(f"        hipLaunchKernelGGL(({kname}<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, "
+                                 f"ld, hel, n_good, mt, gs, jamp, chan, sde, none);")
                     L.append("    } else {")
                 if fused and (self.name in HEL_SUM_IN_KERNEL or nm in LANE_PER_EVENT):
                     L.append("    if (fc && fc->hsum_out) {  // the kernel also sums the helicities")
@@ -932,8 +946,9 @@ class Process:
                  f"{n_order},")
         L.append(f"        {self.n_diagrams}, {self.n_amplitudes}, {fl}.0, {self.flops_exec}.0, proc_{nm}::NSLOT,")
         L.append(f"        proc_{nm}::diagram_lines, {nlines}, {0 if self.lines is None else 1}, {1 if fused else 0}, "
-                 f"{1 if fused and nm in HEL_SUM_IN_KERNEL else 0}, {1 if nm in ('ee_mumu', 'gg_tt') else LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0}, {LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0},")
-        L.append(f"        {'rec5::aux_doubles' if nm == 'gg_ttggg' else 'nullptr'}, {1 if nm in RECURSION else 0},")
+                 f"{1 if fused and nm in HEL_SUM_IN_KERNEL else 0}, {FP64_HSUM_EVENTS[nm] if nm in FP64_HSUM_EVENTS else LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0}, {LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0},")
+        L.append(f"        {'rec5::aux_doubles' if nm == 'gg_ttggg' else 'nullptr'}, "
+                 f"{1 if nm in CHANNELS_IN_RECURSION else 0}, {1 if nm in RECURSION else 0},")
         L.append(f"        proc_{nm}::launch<double>, proc_{nm}::launch<float>,")
         L.append("    };")
         L.append("    return &d;")
@@ -1084,9 +1099,11 @@ class Process:
         L.append("    int ch = -1;")
         L.append("    double sde_ch = 0.0, sde_all = 0.0;")
         L.append("    if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;")
+        # pinned: the sums, which nothing else waits for, would be put off to the end of the program with
+        # every amplitude held until then (gg_ttgg FP64 5.8 KB of spills per lane)
         L.append("#define SDEACC(d, k) do { if constexpr (SDE) { "
                  "const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); "
-                 "sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; } } while (0)")
+                 "sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile(\"\" : \"+v\"(sde_all), \"+v\"(sde_ch)); } } while (0)")
         L.extend(body)
         L.append("    if constexpr (SDE) {")
         L.append("        if (live && e < n_evt) {")
@@ -1364,8 +1381,63 @@ def colour_blocks_source():
     return "\n".join(L + ["}  // namespace me"]) + "\n"
 
 
+def channel_entries(P):
+    """the amplitudes that the recursion kernels of gg_tt and gg_ttg square for the channel weights, as
+    (internal lines, four-gluon structure or None), in the kernels' order: the gluons one after the
+    other along the quark line for each flow; gg_ttg: gluon a, then a pair; a pair, then a; the
+    three-gluon trees ((01) 2), ((02) 1), ((12) 0); the three structures of the four-gluon vertex"""
+    full = (1 << P.npar) - 1
+    bit = [1 << p for p in P.gpar]
+
+    def lines(*masks):
+        return tuple(sorted(full ^ m if m & 1 else m for m in masks))
+
+    q = 1 << 2
+    out = []
+    for f in P.perms:
+        acc, ls = q, []
+        for g in f[:-1]:
+            acc |= bit[g]
+            ls.append(acc)
+        out.append((lines(*ls), None))
+    every = sum(bit)
+    if P.ng == 2:
+        return out + [(lines(every), None)]
+    pairs = [(1, 2), (0, 2), (0, 1)]
+    out += [(lines(q | bit[a], bit[b] | bit[c]), None) for a, (b, c) in enumerate(pairs)]
+    out += [(lines(q | bit[b] | bit[c], bit[b] | bit[c]), None) for b, c in pairs]
+    out += [(lines(bit[b] | bit[c], every), None) for b, c in reversed(pairs)]
+    return out + [(lines(every), k) for k in range(3)]
+
+
+def channels_source():
+    """csrc/generated/channels.hpp: diagram and colour weight of each of those amplitudes"""
+    L = ["// Generated by paper_2210_11122_amd.gen; do not edit.",
+         "// The amplitudes whose squares are the channel weights, in the order of the kernels: Feynman diagram and",
+         "// colour weight of each.", "#pragma once", "namespace me {"]
+    for nm in ("gg_tt", "gg_ttg"):
+        P = Process(nm)
+        by = {}
+        for i, d in enumerate(P.fd_index):
+            by.setdefault(P.lines[d], []).append(i)
+        rows = []
+        for ln, k in channel_entries(P):
+            mine = by[ln]
+            assert len(mine) == (1 if k is None else 3) and len({P.kweight[i] for i in mine}) == 1
+            rows.append((P.fd_index[mine[0]], P.kweight[mine[0]]))
+        assert sorted(set(d for d, _ in rows)) == list(range(P.n_diagrams)) and len(rows) == P.n_amplitudes
+        L += [f"namespace {RECURSION[nm]} {{",
+              f"constexpr int channel_diagram[{len(rows)}] = {{{', '.join(str(d) for d, _ in rows)}}};",
+              f"constexpr double channel_weight[{len(rows)}] = {{{', '.join(repr(k) for _, k in rows)}}};", "}"]
+    return "\n".join(L + ["}  // namespace me"]) + "\n"
+
+
 def generate(outdir, names=None):
     os.makedirs(outdir, exist_ok=True)
+    cpath, csrc = os.path.join(outdir, "channels.hpp"), channels_source()
+    if not os.path.exists(cpath) or open(cpath).read() != csrc:
+        with open(cpath, "w") as f:
+            f.write(csrc)
     bpath, bsrc = os.path.join(outdir, "colour_blocks.hpp"), colour_blocks_source()
     if not os.path.exists(bpath) or open(bpath).read() != bsrc:
         with open(bpath, "w") as f:

@@ -13,7 +13,7 @@ from tests import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-PROCESSES = ["ee_mumu", "gg_tt", "gg_ttgg", "gg_ttggg"]
+PROCESSES = ["ee_mumu", "gg_tt", "gg_ttg", "gg_ttgg", "gg_ttggg"]
 
 
 def check(name, p, got, params):
@@ -27,7 +27,9 @@ def check(name, p, got, params):
 @pytest.mark.parametrize("name", PROCESSES)
 def test_block_edges(name, n):
     from paper_2210_11122_amd import Process
-    n = min(n, 65) if name == "gg_ttggg" else n + 65536 if n == 129 and name in ("ee_mumu", "gg_tt") else n
+    # the largest case also crosses the batch size from which the process takes another kernel
+    last = {"ee_mumu": 65665, "gg_tt": 65665, "gg_ttg": 16385, "gg_ttgg": 129, "gg_ttggg": 65}
+    n = last[name] if n == 129 else n
     print(f"case recursion {name} n={n}", flush=True)
     proc = Process(name, m_top=W.M_TOP, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
     p = oracle.rambo(31, W.sqrt_s(name), W.final_masses(name), n)
@@ -49,7 +51,29 @@ def test_block_edges(name, n):
     assert bool((h0 == good[0]).all()) and bool((h1 == good[-1]).all())
 
 
-@pytest.mark.parametrize("name,n", [("gg_tt", 65), ("gg_ttgg", 65), ("gg_ttggg", 3)])
+@pytest.mark.parametrize("n", [65, 4161, 16385])
+def test_channel_weights_in_the_kernel(n):
+    """gg_tt and gg_ttg form the channel weights in the recursion kernels (gg_ttg with one spin configuration
+    per lane up to 4096 events, four above): they sum to one over the channels, the mixed forms' diagram
+    program gives the same weights to its own precision (1e-5), and without a channel |M|^2 is sigma's"""
+    from paper_2210_11122_amd import Process
+    for name in ("gg_tt", "gg_ttg"):
+        print(f"case channels {name} n={n}", flush=True)
+        a = dict(m_top=W.M_TOP, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
+        proc, mixed = Process(name, **a), Process(name, precision="mixed_fp16", **a)
+        x = torch.from_numpy(oracle.rambo(35, W.sqrt_s(name), W.final_masses(name), n)).cuda()
+        me, me32 = proc.sigma(x), mixed.sigma(x)
+        total = torch.zeros_like(me)
+        for c in range(proc.info["n_diagrams"]):
+            ch = torch.full((n,), c, dtype=torch.int32, device="cuda")
+            got = proc.sigma_channel(x, ch)
+            total += got
+            assert torch.allclose(got / me, mixed.sigma_channel(x, ch) / me32, rtol=1e-3, atol=1e-5)
+        assert torch.allclose(total, me, rtol=1e-13, atol=0)
+        assert torch.equal(proc.sigma_channel(x, torch.full((n,), -1, dtype=torch.int32, device="cuda")), me)
+
+
+@pytest.mark.parametrize("name,n", [("gg_tt", 65), ("gg_ttg", 65), ("gg_ttgg", 65), ("gg_ttggg", 3)])
 def test_massless_tops_leave_spin_configurations_out(name, n):
     from paper_2210_11122_amd import Process
     print(f"case recursion massless {name} n={n}", flush=True)
