@@ -41,6 +41,7 @@
 #include "flows.hpp"
 #include "generated/colour_blocks.hpp"
 #include "helas.hpp"
+#include "process.hpp"
 
 namespace me {
 
@@ -263,13 +264,21 @@ __device__ __forceinline__ double colour_blocks(const cx<double> (&J)[factorial(
     return v;
 }
 
-// The separate colour sum in FP64: one lane per event, the good helicities of the group
-// blockIdx.y in turn.  aop: the 16x4 tile table (up to six flows).
+// |M_h|^2 of row h to the helicities that it stands for
+__device__ __forceinline__ void store_hel(double* __restrict__ out, const int2* __restrict__ members, int h, double v)
+{
+    const int2 m = members ? members[h] : make_int2(h, -1);
+    if (m.x >= 0) out[m.x] = v;
+    if (m.y >= 0) out[m.y] = v;
+}
+
+// The separate colour sum in FP64: one lane per event, the rows (good helicities, or pairs) of the
+// group blockIdx.y in turn.  aop: the 16x4 tile table (up to six flows).
 template <int NC>
 __global__ __launch_bounds__(NC > 6 ? 64 : 256) void colour_sum_f64(
     const double* __restrict__ J, int64_t ld, int n_good, int hel_per_group, int64_t n_evt,
     const double* __restrict__ aop, double scale_hel, double scale_avg, double* __restrict__ out,
-    double* __restrict__ out_hel, double* __restrict__ part)
+    double* __restrict__ out_hel, double* __restrict__ part, const int2* __restrict__ members, int n_hel)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n_evt) return;
@@ -289,8 +298,8 @@ __global__ __launch_bounds__(NC > 6 ? 64 : 256) void colour_sum_f64(
             static_for<NC>([&](auto F) { Jr[F] = {Jh[(int64_t)(2 * F) * ld], Jh[(int64_t)(2 * F + 1) * ld]}; });
             me_h = colour_blocks<4>(Jr);
         }
-        if (out_hel) out_hel[e * n_good + h] = me_h * scale_hel;
-        me += me_h;
+        if (out_hel) store_hel(out_hel + e * n_hel, members, h, me_h * scale_hel);
+        me += members_of(members, h) * me_h;
     }
     cs_store(me, e, n_evt, scale_avg, out, part);
 }
@@ -453,12 +462,13 @@ __device__ __forceinline__ double colour_sum_lds_h16(const float* Jl, const type
 }
 
 // The helicity sum after the fused colour sum, in the order of the separate colour-sum kernel
-// with the same helicity groups: within each group of hel_per_group consecutive helicities from
+// with the same helicity groups: within each group of hel_per_group consecutive rows from
 // zero, then the groups in order (so the result is bitwise that of the separate kernels).
-// part_h[h][e] = D |M_h|^2.
+// part_h[row][e] = D |M_h|^2.
 static __global__ __launch_bounds__(256) void hel_reduce_grouped(const double* __restrict__ part_h, int n_good,
                                                                  int hel_per_group, int64_t n_evt, double scale,
-                                                                 double* __restrict__ out)
+                                                                 double* __restrict__ out,
+                                                                 const int2* __restrict__ members)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= n_evt) return;
@@ -466,7 +476,7 @@ static __global__ __launch_bounds__(256) void hel_reduce_grouped(const double* _
     for (int h0 = 0; h0 < n_good; h0 += hel_per_group) {
         const int h1 = min(n_good, h0 + hel_per_group);
         double m = 0.0;
-        for (int h = h0; h < h1; ++h) m += part_h[(int64_t)h * n_evt + e];
+        for (int h = h0; h < h1; ++h) m += members_of(members, h) * part_h[(int64_t)h * n_evt + e];
         s += m;
     }
     out[e] = s * scale;

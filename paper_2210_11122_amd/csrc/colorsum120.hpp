@@ -37,7 +37,8 @@ __device__ __forceinline__ double colour_sign_pair_120(const double* __restrict_
 }
 static __global__ __launch_bounds__(256, 2) void colour_sum_f64_120(
     const double* __restrict__ J, int64_t ld, int n_good, int hel_per_group, int64_t n_evt, double scale_hel,
-    double scale_avg, double* __restrict__ out, double* __restrict__ out_hel, double* __restrict__ part)
+    double scale_avg, double* __restrict__ out, double* __restrict__ out_hel, double* __restrict__ part,
+    const int2* __restrict__ members, int n_hel)
 {
     __shared__ double red[2][3][64];
     const unsigned lane = threadIdx.x & 63;
@@ -56,8 +57,8 @@ static __global__ __launch_bounds__(256, 2) void colour_sum_f64_120(
         __syncthreads();
         if (wave == 0) {   // the other buffer is free for the next helicity until the next barrier
             const double me_h = ((q + red[h & 1][0][lane]) + (red[h & 1][1][lane] + red[h & 1][2][lane])) * (1.0 / 64.0);
-            if (out_hel && e < n_evt) out_hel[e * n_good + h] = me_h * scale_hel;
-            me += me_h;
+            if (out_hel && e < n_evt) store_hel(out_hel + e * n_hel, members, h, me_h * scale_hel);
+            me += members_of(members, h) * me_h;
         }
     }
     if (wave == 0 && e < n_evt) cs_store(me, e, n_evt, scale_avg, out, part);

@@ -320,7 +320,7 @@ static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const sig
     int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);
     if (blocks == 0) return hipSuccess;
     if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion
-        return rec3::launch(mom, n_evt, ld, hg, n_good, mt, gs, jamp, chan, sde, fc, st);
+        return rec3::launch(mom, n_evt, ld, hg, mt, gs, jamp, chan, sde, fc, st);
     } else {
     if (chan)
         hipLaunchKernelGGL((amp_kernel<R, true>), dim3((unsigned)blocks), dim3(64 * WG), 0, st, mom, n_evt, ld, hel, n_good, mt, gs, jamp, chan, sde, none);
@@ -336,7 +336,7 @@ const ProcessDesc* process_gg_ttg()
         "gg_ttg", proc_gg_ttg::NPAR, proc_gg_ttg::NC, 32, 256, 1, 1,
         proc_gg_ttg::colour_num, 9, proc_gg_ttg::final_massive, proc_gg_ttg::orderings, 3,
         16, 18, 3647.0, 3647.0, proc_gg_ttg::NSLOT,
-        proc_gg_ttg::diagram_lines, 2, 1, 1, 0, 16384, 0,
+        proc_gg_ttg::diagram_lines, 2, 1, 1, 0, 4097, 0,
         nullptr, 1, 1,
         proc_gg_ttg::launch<double>, proc_gg_ttg::launch<float>,
     };

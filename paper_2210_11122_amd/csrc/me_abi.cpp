@@ -139,10 +139,11 @@ struct me_handle {
     int precision = ME_FP64;
     double mt = 173.0, alpha_em = 1.0 / 132.507, alpha_s = 0.118, g = 0.0;
     int n_good = 0;
-    int* d_hel_index = nullptr;  // helicity-combination index of each good helicity; the next two are in its buffer
-    int* d_hel_groups = nullptr;  // the good helicities by gluon helicities (HelicityGroups)
+    int* d_hel_tables = nullptr;  // the buffer of the next three
+    int* d_hel_index = nullptr;   // helicity-combination index of each good helicity
     signed char* d_hel_good = nullptr;
-    int n_hel_groups = 0;
+    me::HelicityGroups hel_groups{};   // used in FP64 (its tables are in that buffer, too)
+    int n_rows = 0;                    // rows of the jamps: good helicities, or pairs of them (HelicityGroups)
     std::vector<signed char> h_hel_good;
     std::vector<double> hel_ratio;
     double* d_aop64 = nullptr;
@@ -179,6 +180,8 @@ struct ColourArgs {
     int64_t n;
     double scale_hel, scale_avg;
     double *out, *out_hel, *part;
+    const int2* members;   // of each row (HelicityGroups), or null
+    int n_hel;             // row length of out_hel
 };
 
 template <int NC>
@@ -187,12 +190,12 @@ hipError_t launch_cs64(const double* J, const double* aop, const ColourArgs& a, 
     if constexpr (NC == 120) {
         hipLaunchKernelGGL(me::colour_sum_f64_120, dim3((unsigned)((a.n + 63) / 64), (unsigned)a.groups), dim3(256), 0,
                            st, J, a.ld, a.n_good, a.hel_per_group, a.n, a.scale_hel, a.scale_avg, a.out, a.out_hel,
-                           a.part);
+                           a.part, a.members, a.n_hel);
     } else {
         constexpr int T = NC > 6 ? 64 : 256;
         hipLaunchKernelGGL((me::colour_sum_f64<NC>), dim3((unsigned)((a.n + T - 1) / T), (unsigned)a.groups), dim3(T),
                            0, st, J, a.ld, a.n_good, a.hel_per_group, a.n, aop, a.scale_hel, a.scale_avg, a.out,
-                           a.out_hel, a.part);
+                           a.out_hel, a.part, a.members, a.n_hel);
     }
     return hipGetLastError();
 }
@@ -222,10 +225,11 @@ hipError_t dispatch_cs16(int nc, const float* j, const typename T::elem* aop, co
 // colour sum of one chunk; with several helicity groups the partial sums go through `part`
 // (groups x n doubles) and a fixed-order reduction
 hipError_t colour_sum(const me_handle* h, int precision, const void* J, int64_t ld, int n_good, int hel_per_group,
-                      int groups, int64_t n, double* out, double* out_hel, double* part, hipStream_t st)
+                      int groups, int64_t n, double* out, double* out_hel, double* part, const int2* members, int n_hel,
+                      hipStream_t st)
 {
     const double sh = 1.0 / h->P->colour_den, sa = 1.0 / ((double)h->P->colour_den * h->P->avg);
-    const ColourArgs a{ld, n_good, hel_per_group, groups, n, sh, sa, out, out_hel, part};
+    const ColourArgs a{ld, n_good, hel_per_group, groups, n, sh, sa, out, out_hel, part, members, n_hel};
     hipError_t e = hipErrorInvalidValue;
     if (precision == ME_FP64) {
         const double* j = static_cast<const double*>(J);
@@ -247,8 +251,8 @@ hipError_t colour_sum(const me_handle* h, int precision, const void* J, int64_t 
     return hipGetLastError();
 }
 
-// bytes of scratch per event for the jamps of n_hel helicities and what else the amplitude kernels
-// of this precision keep there
+// bytes of scratch per event for n_hel rows of jamps and what else the amplitude kernels of this
+// precision keep there
 size_t jamp_scratch(const me::ProcessDesc* P, int precision, int n_hel)
 {
     if (precision != ME_FP64) return (size_t)n_hel * 2 * (P->nc + P->nslot) * sizeof(float);
@@ -336,14 +340,16 @@ __global__ __launch_bounds__(256) void scale_alphas(double* __restrict__ out, co
 // single-diagram enhancement: out[e] *= (sum_h W_chan,h) / (sum_h sum_d W_d,h) from the
 // per-lane sums sde[h][0: channel, 1: all][column] of the amplitude kernel; chan[e] < 0: no factor
 __global__ __launch_bounds__(256) void sde_apply(double* __restrict__ out, const double* __restrict__ sde,
-                                                 const int* __restrict__ chan, int n_good, int64_t ld, int64_t n)
+                                                 const int* __restrict__ chan, int n_rows, int64_t ld, int64_t n,
+                                                 const int2* __restrict__ members)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= n || chan[e] < 0) return;
     double num = 0.0, den = 0.0;
-    for (int h = 0; h < n_good; ++h) {
-        num += sde[(int64_t)(2 * h) * ld + e];
-        den += sde[(int64_t)(2 * h + 1) * ld + e];
+    for (int h = 0; h < n_rows; ++h) {
+        const double w = me::members_of(members, h);
+        num += w * sde[(int64_t)(2 * h) * ld + e];
+        den += w * sde[(int64_t)(2 * h + 1) * ld + e];
     }
     out[e] *= num / den;
 }
@@ -355,35 +361,56 @@ struct Selection {
     double *hel_me, *w;
 };
 
-// The helicity combinations hel (n x npar signs) by gluon helicities: the rows of HelicityGroups (none
-// for processes without a quark line between gluons), then its index.
-std::vector<int> helicity_group_table(const me::ProcessDesc* P, const signed char* hel, int n)
+// The n good helicity combinations hel (n x npar signs) as the device tables of HelicityGroups
+struct HelicityTables {
+    std::vector<int> ints;           // members (two per row), row and count of each combination, the groups
+    std::vector<signed char> hel;    // of each row
+    int n_rows = 0, n_groups = 0;
+};
+HelicityTables helicity_tables(const me::ProcessDesc* P, const signed char* hel, int n)
 {
-    std::vector<int> t;
-    const bool quark_line = P->coupling == 1 && P->n_order == P->npar - 2;
-    std::map<int, size_t> row;
-    for (int k = 0; quark_line && k < n; ++k) {
-        const signed char* l = hel + (size_t)k * P->npar;
-        int bits = 0;
-        for (int g = 0; g < P->npar - 2; ++g) bits |= (l[g < 2 ? g : g + 2] > 0 ? 1 : 0) << g;
-        auto it = row.find(bits);
-        if (it == row.end()) {
-            it = row.emplace(bits, t.size()).first;
-            t.insert(t.end(), {bits, -1, -1, -1, -1});
-        }
-        t[it->second + 1 + (l[2] > 0 ? 2 : 0) + (l[3] > 0 ? 1 : 0)] = k;
-    }
-    const size_t rows = t.size();
-    t.resize(rows + P->nhel, -1);
+    HelicityTables t;
+    if (!P->recursion) return t;
+    const int npar = P->npar, nhel = P->nhel;
+    std::vector<int> good(nhel, -1), row(nhel / 2, -1), table;
     for (int k = 0; k < n; ++k) {
         int hh = 0;
-        for (int i = 0; i < P->npar; ++i) hh = 2 * hh + (hel[(size_t)k * P->npar + i] > 0 ? 1 : 0);
-        t[rows + hh] = k;
+        for (int i = 0; i < npar; ++i) hh = 2 * hh + (hel[(size_t)k * npar + i] > 0 ? 1 : 0);
+        good[hh] = k;
     }
+    const bool quark_line = P->coupling == 1 && P->n_order == npar - 2;
+    std::map<int, size_t> group;
+    for (int hh = 0; hh < nhel / 2; ++hh) {
+        if (good[hh] < 0 && good[nhel - 1 - hh] < 0) continue;
+        t.ints.insert(t.ints.end(), {good[hh], good[nhel - 1 - hh]});
+        row[hh] = t.n_rows++;
+        int bits = 0;
+        for (int i = 0; i < npar; ++i) {
+            const int plus = (hh >> (npar - 1 - i)) & 1;
+            t.hel.push_back(plus ? 1 : -1);
+            if (i < 2 || i >= 4) bits |= plus << (i < 2 ? i : i - 2);
+        }
+        if (!quark_line) continue;
+        auto it = group.find(bits);
+        if (it == group.end()) {
+            it = group.emplace(bits, table.size()).first;
+            table.insert(table.end(), {bits, -1, -1, -1, -1});
+        }
+        table[it->second + 1 + ((hh >> (npar - 3)) & 1) * 2 + ((hh >> (npar - 4)) & 1)] = row[hh];
+    }
+    t.n_groups = (int)table.size() / 5;
+    t.ints.insert(t.ints.end(), row.begin(), row.end());
+    for (int hh = 0; hh < nhel / 2; ++hh) t.ints.push_back((good[hh] >= 0) + (good[nhel - 1 - hh] >= 0));
+    t.ints.insert(t.ints.end(), table.begin(), table.end());
     return t;
 }
-
-me::HelicityGroups helicity_groups_at(const int* table, int n_rows) { return {table, n_rows, table + 5 * n_rows}; }
+// ... at their place on the device
+me::HelicityGroups helicity_groups_at(const me::ProcessDesc* P, const HelicityTables& t, const int* ints, const signed char* hel)
+{
+    if (!t.n_rows) return {nullptr, 0, nullptr, nullptr, nullptr, 0};
+    const int* const row = ints + 2 * t.n_rows;
+    return {row + P->nhel, t.n_groups, row, reinterpret_cast<const int2*>(ints), hel, t.n_rows};
+}
 
 // amplitude kernel + colour sum (+ the optional per-event kernels) for events [0, n) of `mom`, in
 // chunks; scratch: jamps of `chunk` events (jamp_bytes_per_event each), then the helicity-group
@@ -395,6 +422,8 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
 {
     const me::ProcessDesc* P = h->P;
     const bool fp64 = precision == ME_FP64;
+    const int2* const members = fp64 ? hg.members : nullptr;
+    const int n_rows = members ? hg.n_rows : n_good;
     // the colour sum inside the amplitude kernel: plain |M|^2 (the selection, the per-helicity output
     // and, but for the kernels that apply them, the channel weights read the jamps)
     const bool chan_fused = chan && precision == ME_FP64 && P->channel_in_kernel;
@@ -442,8 +471,8 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             if (e != hipSuccess) return fail(ME_EHIP, std::string("amplitude kernel: ") + hipGetErrorString(e));
             TimedLaunch tc(h, st, 1, timed);
             hipLaunchKernelGGL(me::hel_reduce_grouped, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st,
-                               static_cast<const double*>(jamp), n_good, hel_per_group, nc,
-                               1.0 / ((double)P->colour_den * P->avg), out + c0);
+                               static_cast<const double*>(jamp), n_rows, hel_per_group, nc,
+                               1.0 / ((double)P->colour_den * P->avg), out + c0, members);
             e = hipGetLastError();
             tc.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("helicity-sum kernel: ") + hipGetErrorString(e));
@@ -454,13 +483,13 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             if (e != hipSuccess) return fail(ME_EHIP, std::string("amplitude kernel: ") + hipGetErrorString(e));
             TimedLaunch tc(h, st, 1, timed);
             double* oh = sel ? sel->hel_me : (out_hel ? out_hel + c0 * n_good : nullptr);
-            e = colour_sum(h, precision, jamp, ld, n_good, hel_per_group, groups, nc, out + c0, oh, part, st);
+            e = colour_sum(h, precision, jamp, ld, n_rows, hel_per_group, groups, nc, out + c0, oh, part, members, n_good, st);
             tc.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("colour-sum kernel: ") + hipGetErrorString(e));
         }
         if (chan && !fused) {
             hipLaunchKernelGGL(sde_apply, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, out + c0, sde, ch,
-                               n_good, ld, nc);
+                               n_rows, ld, nc, members);
             e = hipGetLastError();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("channel-weight kernel: ") + hipGetErrorString(e));
         }
@@ -474,10 +503,10 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             const dim3 grid((unsigned)((nc + 255) / 256), (unsigned)P->nc);
             if (fp64)
                 hipLaunchKernelGGL(me::lc_weights<double>, grid, dim3(256), 0, st, static_cast<const double*>(jamp), ld,
-                                   P->nc, n_good, nc, sel->w);
+                                   P->nc, n_rows, nc, sel->w, members);
             else
                 hipLaunchKernelGGL(me::lc_weights<float>, grid, dim3(256), 0, st, static_cast<const float*>(jamp), ld,
-                                   P->nc, n_good, nc, sel->w);
+                                   P->nc, n_rows, nc, sel->w, members);
             hipLaunchKernelGGL(me::select_events, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, sel->hel_me,
                                n_good, sel->w, P->nc, nc, h->d_hel_index, sel->r_hel + c0, sel->r_col + c0,
                                sel->out_hel + c0, sel->out_col + c0);
@@ -502,7 +531,7 @@ void free_handle(me_handle* h)
         (void)hipEventDestroy(m.a);
         (void)hipEventDestroy(m.b);
     }
-    if (h->d_hel_index) (void)hipFree(h->d_hel_index);
+    if (h->d_hel_tables) (void)hipFree(h->d_hel_tables);
     if (h->d_aop64) (void)hipFree(h->d_aop64);
     if (h->d_aop16) (void)hipFree(h->d_aop16);
     if (h->d_aopb) (void)hipFree(h->d_aopb);
@@ -577,16 +606,17 @@ int helicity_prepass(me_handle* h, hipStream_t st)
         for (int i = 0; i < npar; ++i) all[(size_t)hh * npar + i] = ((hh >> (npar - 1 - i)) & 1) ? 1 : -1;
     const int64_t n = PREPASS_EVENTS;
     const double sqrt_s = P->coupling ? 1500.0 : 500.0;
-    const std::vector<int> all_groups = helicity_group_table(P, all.data(), nhel);
-    const size_t jamp_per_event = jamp_scratch(P, ME_FP64, nhel);
+    const HelicityTables all_tables = helicity_tables(P, all.data(), nhel);
+    const int all_rows = all_tables.n_rows ? all_tables.n_rows : nhel;
+    const size_t jamp_per_event = jamp_scratch(P, ME_FP64, all_rows);
     const int64_t pchunk =
         std::min<int64_t>(n, std::max<int64_t>(64, (int64_t)((size_t(512) << 20) / jamp_per_event) / 64 * 64));
     int groups = 1, hpg = 1;
-    helicity_groups(P, nhel, pchunk, &groups, &hpg);
+    helicity_groups(P, all_rows, pchunk, &groups, &hpg);
     // one allocation for all buffers
     const size_t sizes[6] = {n * npar * 4 * sizeof(double),      n * sizeof(double),
                              (size_t)n * nhel * sizeof(double),  (jamp_per_event + groups * sizeof(double)) * pchunk,
-                             all_groups.size() * sizeof(int),    all.size()};
+                             all_tables.ints.size() * sizeof(int), all.size() + all_tables.hel.size()};
     size_t at[7] = {0};
     for (int i = 0; i < 6; ++i) at[i + 1] = at[i] + (sizes[i] + 255) / 256 * 256;
     char* base = nullptr;
@@ -596,18 +626,21 @@ int helicity_prepass(me_handle* h, hipStream_t st)
     double* const d_out = reinterpret_cast<double*>(base + at[1]);
     double* const d_hel = reinterpret_cast<double*>(base + at[2]);
     double* const d_jamp = reinterpret_cast<double*>(base + at[3]);
-    int* const d_groups = reinterpret_cast<int*>(base + at[4]);
+    int* const d_tables = reinterpret_cast<int*>(base + at[4]);
     signed char* const d_all = reinterpret_cast<signed char*>(base + at[5]);
+    std::vector<signed char> all_hel = all;   // then those of the rows
+    all_hel.insert(all_hel.end(), all_tables.hel.begin(), all_tables.hel.end());
     std::vector<double> out(n), hel((size_t)n * nhel);
-    if (rc == ME_OK && hipMemcpyAsync(d_all, all.data(), all.size(), hipMemcpyHostToDevice, st) != hipSuccess)
+    if (rc == ME_OK && hipMemcpyAsync(d_all, all_hel.data(), all_hel.size(), hipMemcpyHostToDevice, st) != hipSuccess)
         rc = fail(ME_EHIP, "upload of the helicity table failed");
-    if (rc == ME_OK &&
-        hipMemcpyAsync(d_groups, all_groups.data(), all_groups.size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess)
-        rc = fail(ME_EHIP, "upload of the helicity groups failed");
+    if (rc == ME_OK && !all_tables.ints.empty() &&
+        hipMemcpyAsync(d_tables, all_tables.ints.data(), all_tables.ints.size() * sizeof(int), hipMemcpyHostToDevice, st) !=
+            hipSuccess)
+        rc = fail(ME_EHIP, "upload of the helicity tables failed");
     if (rc == ME_OK && rambo(h, PREPASS_SEED, std::max(sqrt_s, 2.0 * final_mass_sum(h) + 1.0), 0, n, d_mom, st) != hipSuccess)
         rc = fail(ME_EHIP, "pre-pass RAMBO launch failed");
     if (rc == ME_OK)
-        rc = run_chunks(h, ME_FP64, d_all, helicity_groups_at(d_groups, ((int)all_groups.size() - nhel) / 5), nhel, hpg, groups, pchunk, jamp_per_event, d_mom, n, d_out, d_hel, d_jamp, st);
+        rc = run_chunks(h, ME_FP64, d_all, helicity_groups_at(P, all_tables, d_tables, d_all + all.size()), nhel, hpg, groups, pchunk, jamp_per_event, d_mom, n, d_out, d_hel, d_jamp, st);
     if (rc == ME_OK) {
         if (hipMemcpyAsync(out.data(), d_out, n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipMemcpyAsync(hel.data(), d_hel, hel.size() * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -631,19 +664,22 @@ int helicity_prepass(me_handle* h, hipStream_t st)
     std::vector<int> index;
     for (int hh = 0; hh < nhel; ++hh)
         if (h->hel_ratio[hh] > PREPASS_THRESHOLD) index.push_back(hh);
-    const std::vector<int> groups_table = helicity_group_table(P, h->h_hel_good.data(), h->n_good);
-    h->n_hel_groups = ((int)groups_table.size() - nhel) / 5;
-    // the helicity index, the groups and the good helicities in one buffer
-    std::vector<char> tables((index.size() + groups_table.size()) * sizeof(int) + h->h_hel_good.size());
-    std::memcpy(tables.data(), index.data(), index.size() * sizeof(int));
-    std::memcpy(tables.data() + index.size() * sizeof(int), groups_table.data(), groups_table.size() * sizeof(int));
-    std::memcpy(tables.data() + (index.size() + groups_table.size()) * sizeof(int), h->h_hel_good.data(), h->h_hel_good.size());
-    if (hipMalloc(&h->d_hel_index, tables.size()) != hipSuccess) return fail(ME_ENOMEM, "hipMalloc of the helicity tables failed");
-    h->d_hel_groups = h->d_hel_index + index.size();
-    h->d_hel_good = reinterpret_cast<signed char*>(h->d_hel_groups + groups_table.size());
-    if (hipMemcpy(h->d_hel_index, tables.data(), tables.size(), hipMemcpyHostToDevice) != hipSuccess)
+    const HelicityTables ht = helicity_tables(P, h->h_hel_good.data(), h->n_good);
+    h->n_rows = h->precision == ME_FP64 && ht.n_rows ? ht.n_rows : h->n_good;
+    // one buffer: the members, rows and groups, the helicity index, then the signs
+    const size_t n_int = ht.ints.size() + index.size();
+    std::vector<char> tables(n_int * sizeof(int));
+    std::memcpy(tables.data(), ht.ints.data(), ht.ints.size() * sizeof(int));
+    std::memcpy(tables.data() + ht.ints.size() * sizeof(int), index.data(), index.size() * sizeof(int));
+    tables.insert(tables.end(), h->h_hel_good.begin(), h->h_hel_good.end());
+    tables.insert(tables.end(), ht.hel.begin(), ht.hel.end());
+    if (hipMalloc(&h->d_hel_tables, tables.size()) != hipSuccess) return fail(ME_ENOMEM, "hipMalloc of the helicity tables failed");
+    h->d_hel_index = h->d_hel_tables + ht.ints.size();
+    h->d_hel_good = reinterpret_cast<signed char*>(h->d_hel_tables + n_int);
+    h->hel_groups = helicity_groups_at(P, ht, h->d_hel_tables, h->d_hel_good + h->h_hel_good.size());
+    if (hipMemcpy(h->d_hel_tables, tables.data(), tables.size(), hipMemcpyHostToDevice) != hipSuccess)
         return fail(ME_EHIP, "upload of the helicity tables failed");
-    h->bytes_resident += h->h_hel_good.size() + (index.size() + groups_table.size()) * sizeof(int);
+    h->bytes_resident += tables.size();
     return ME_OK;
 }
 
@@ -699,14 +735,14 @@ me_handle* me_create(const char* process, const double* masses, int n_masses, co
         g_err = msg;
         return nullptr;
     }
-    h->jamp_bytes_per_event = jamp_scratch(P, precision, h->n_good);
+    h->jamp_bytes_per_event = jamp_scratch(P, precision, h->n_rows);
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) total_b = size_t(64) << 30;
     h->scratch_cap = std::max(SCRATCH_MIN, std::min<size_t>(SCRATCH_EVENTS * h->jamp_bytes_per_event, total_b / 8));
     int64_t chunk = (int64_t)(h->scratch_cap / h->jamp_bytes_per_event) / 64 * 64;
     h->chunk = std::max<int64_t>(64, chunk);
     // the helicity split is fixed per handle, so an event's result does not depend on the batch
-    helicity_groups(P, h->n_good, h->chunk, &h->groups, &h->hel_per_group);
+    helicity_groups(P, h->n_rows, h->chunk, &h->groups, &h->hel_per_group);
     h->bytes_per_event = h->jamp_bytes_per_event + (h->groups > 1 ? h->groups * sizeof(double) : 0);
     return h;
 }
@@ -823,7 +859,7 @@ int sigma_piped(me_handle* h, const double* momenta, int64_t n_evt, double* out,
     for (int64_t c0 = 0; c0 < n_evt && rc == ME_OK; c0 += chunk, ++k) {
         const int64_t nc = std::min(chunk, n_evt - c0);
         const int i = (int)(k & 1);
-        rc = run_chunks(h, h->precision, h->d_hel_good, helicity_groups_at(h->d_hel_groups, h->n_hel_groups), h->n_good, h->hel_per_group, h->groups, chunk,
+        rc = run_chunks(h, h->precision, h->d_hel_good, h->hel_groups, h->n_good, h->hel_per_group, h->groups, chunk,
                         h->jamp_bytes_per_event, momenta + c0 * npar * 4, nc, out + c0, nullptr, scr[i], hp->s[i],
                         h->profiling, nullptr, alphas ? alphas + c0 : nullptr);
     }
@@ -854,7 +890,7 @@ CallPlan plan_call(const me_handle* h, int64_t n_evt, bool plain, size_t extra)
     c.chunk = ((n_evt + n_chunks - 1) / n_chunks + 63) / 64 * 64;
     c.piped = plain && h->P->nslot > 0 && n_evt > h->chunk;
     const bool fused = plain && h->P->fused_colour && h->fuse_colour;
-    c.per_event = fused ? (size_t)h->n_good * sizeof(double) : h->bytes_per_event + extra;
+    c.per_event = fused ? (size_t)h->n_rows * sizeof(double) : h->bytes_per_event + extra;
     return c;
 }
 
@@ -877,8 +913,8 @@ int sigma_impl(me_handle* h, const double* momenta, int64_t n_evt, double* out_m
     hipStream_t st = static_cast<hipStream_t>(stream);
     // selection adds |M_h|^2 and the leading-colour weights of one chunk
     const size_t sel_bytes = sel_in ? (size_t)(h->n_good + h->P->nc) * sizeof(double) : 0;
-    // channel weights add two sums per (event, helicity)
-    const size_t sde_bytes = chan ? (size_t)2 * h->n_good * sizeof(double) : 0;
+    // channel weights add two sums per event and row
+    const size_t sde_bytes = chan ? (size_t)2 * h->n_rows * sizeof(double) : 0;
     const CallPlan plan = plan_call(h, n_evt, !sel_in && !out_hel && !chan, sel_bytes + sde_bytes);
     const int64_t chunk = plan.chunk;
     if (plan.piped) return sigma_piped(h, momenta, n_evt, out_me2, alphas, st, chunk);
@@ -893,7 +929,7 @@ int sigma_impl(me_handle* h, const double* momenta, int64_t n_evt, double* out_m
     double* sde = chan ? reinterpret_cast<double*>(static_cast<char*>(scratch) +
                                                    (size_t)chunk * (h->bytes_per_event + sel_bytes))
                        : nullptr;
-    return run_chunks(h, h->precision, h->d_hel_good, helicity_groups_at(h->d_hel_groups, h->n_hel_groups), h->n_good, h->hel_per_group, h->groups, chunk,
+    return run_chunks(h, h->precision, h->d_hel_good, h->hel_groups, h->n_good, h->hel_per_group, h->groups, chunk,
                       h->jamp_bytes_per_event, momenta, n_evt, out_me2, out_hel, scratch, st, h->profiling,
                       sel_in ? &sel : nullptr, alphas, chan, sde);
 }
@@ -1044,10 +1080,10 @@ int me_sigma_noalloc(me_handle* h, const double* momenta, int64_t n_evt, double*
     void* scr = static_scratch_ptr();
     if (!scr) return fail(ME_EHIP, "hipGetSymbolAddress of the static scratch failed");
     const me::ProcessDesc* P = h->P;
-    // scratch per event: D |M_h|^2 per good helicity where the amplitude kernel does the colour sum,
-    // else the jamps (and partial slots) of every good helicity plus the helicity-group sums
+    // scratch per event: D |M_h|^2 per row (good helicity or pair) where the amplitude kernel does the colour sum,
+    // else the jamps (and partial slots) of every row plus the helicity-group sums
     const bool fused = P->fused_colour && h->fuse_colour;
-    const size_t per_event = fused ? (size_t)h->n_good * sizeof(double) : h->bytes_per_event;
+    const size_t per_event = fused ? (size_t)h->n_rows * sizeof(double) : h->bytes_per_event;
     const int64_t fit = (int64_t)(ME_NOALLOC_SCRATCH_BYTES / per_event) / 64 * 64;
     if (fit < 64)
         return fail(ME_ENOMEM, std::string("me_sigma_noalloc: ") + P->name + " needs " +
@@ -1059,7 +1095,7 @@ int me_sigma_noalloc(me_handle* h, const double* momenta, int64_t n_evt, double*
     const int64_t n_chunks = (n_evt + cap - 1) / cap;
     const int64_t chunk = ((n_evt + n_chunks - 1) / n_chunks + 63) / 64 * 64;
     const size_t jamp_per_event = fused ? per_event : h->jamp_bytes_per_event;
-    return run_chunks(h, h->precision, h->d_hel_good, helicity_groups_at(h->d_hel_groups, h->n_hel_groups), h->n_good, h->hel_per_group, h->groups, chunk, jamp_per_event,
+    return run_chunks(h, h->precision, h->d_hel_good, h->hel_groups, h->n_good, h->hel_per_group, h->groups, chunk, jamp_per_event,
                       momenta, n_evt, out_me2, nullptr, scr, static_cast<hipStream_t>(stream));
 }
 

@@ -5,11 +5,12 @@
 
 namespace me {
 
-// chan == nullptr: plain kernels; otherwise chan[n_evt] channel ids and sde[n_good][2][ld] the
-// per-lane single-diagram sums (channel, all)
+// chan == nullptr: plain kernels; otherwise chan[n_evt] channel ids and sde[row][2][ld] the
+// per-lane single-diagram sums (channel, all).  A row of the jamps is a good helicity, or a pair of them
+// (HelicityGroups)
 // The colour sum inside the amplitude kernel (processes with fused_colour): the operand tables
 // of the separate colour-sum kernel of the same form.  With a FusedColour the kernel writes
-// D |M_h|^2 as doubles to ((double*)jamp)[h * n_evt + event] instead of the jamps.
+// D |M_h|^2 as doubles to ((double*)jamp)[row * n_evt + event] instead of the jamps.
 struct FusedColour {
     const void* aop;     // FP64 tiles (FP64 kernel) or FP16 / BF16 hi tiles (FP32 kernel)
     const void* aop_lo;  // BF16 lo tiles (BF16 form)
@@ -25,16 +26,35 @@ struct FusedColour {
     int hel_per_group;
 };
 
-// The good helicities of a quark-line process by gluon helicities, for kernels whose workgroup
-// evaluates the four quark spin configurations of one gluon configuration.  table (device):
-// n rows of 5: the gluons' signs (bit i: gluon i has helicity +), then the index among the good
-// helicities of the quark spins (-,-), (-,+), (+,-), (+,+), or -1 where that combination is not good.
-// index (device): for each helicity combination its index among the good ones, or -1.
+// The good helicities of a process with FP64 recursion, two by two.  Tree amplitudes of QED and QCD with
+// real couplings and masses obey J_f(-h) = phase conj(J_f(h)) for the combination -h of opposite
+// helicities, the phase common to all flows (reversing a helicity conjugates the polarisation vectors
+// and spinors, up to sign; the Feynman rules are real in a Majorana basis).  So |M|^2, the flow weights
+// and the channel weights of h and -h are equal, and one of the two is evaluated: a row of the jamps,
+// |M_h|^2 or channel sums per pair.  The pair is evaluated at the helicity of particle 0 being -.
+// All on the device:
+// table: n groups of 5 for the kernels whose workgroup evaluates the four quark spin configurations of
+//   one gluon configuration: the gluons' signs (bit i: gluon i has helicity +), then the row of the
+//   quark spins (-,-), (-,+), (+,-), (+,+), or -1 where neither helicity of that pair is good
+// row: for each helicity combination with particle 0 at - (the lower half) its row, or -1; then for
+//   each of them how many good helicities the row stands for (0, 1 or 2)
+// members: of each row the two helicities' indices among the good ones, -1 where not good
+// hel: of each row the signs of the evaluated combination
 struct HelicityGroups {
     const int* table;
     int n;
-    const int* index;
+    const int* row;
+    const int2* members;
+    const signed char* hel;
+    int n_rows;   // 0: no recursion, a row is a good helicity (members is null)
 };
+// how many good helicities row r stands for
+__device__ __forceinline__ double members_of(const int2* __restrict__ members, int r)
+{
+    if (!members) return 1.0;
+    const int2 m = members[r];
+    return (m.x >= 0 ? 1.0 : 0.0) + (m.y >= 0 ? 1.0 : 0.0);
+}
 
 // fc: null, or the fused colour sum (then chan must be null, but for channel_in_kernel)
 typedef hipError_t (*amp_launch_f64)(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel,
@@ -70,7 +90,7 @@ struct ProcessDesc {
     // batches from this size take the kernel with one lane per event, which also sums the helicities
     // (0: none): FP64, and mixed forms (of one flow)
     int64_t lane_min_f64, lane_min_mixed;
-    int64_t (*aux_doubles)(int n_hel);  // doubles per event that the FP64 launch needs after the jamps (null: none)
+    int64_t (*aux_doubles)(int n_rows);  // doubles per event that the FP64 launch needs after the jamps (null: none)
     int channel_in_kernel;     // the FP64 kernel that sums the helicities also applies the channel weight (chan with fc)
     int recursion;             // the FP64 jamps come from the recursion, without partial slots
     amp_launch_f64 launch_f64;
@@ -87,18 +107,18 @@ hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGr
                   double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st);
 }
 namespace rec3 {
-hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, int n_good, double mt, double gs,
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
                   double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st);
 }
 namespace rec4 {
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
                   double* jamp, const FusedColour* fc, hipStream_t st);
 }
-// gg -> tt~ggg: jamp is followed by aux_doubles(n_good) doubles per event of the padded batch (ld)
+// gg -> tt~ggg: jamp is followed by aux_doubles(n_rows) doubles per event of the padded batch (ld)
 namespace rec5 {
-int64_t aux_doubles(int n_good);
-hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, int n_good, double mt,
-                  double gs, double* jamp, hipStream_t st);
+int64_t aux_doubles(int n_rows);
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
+                  double* jamp, hipStream_t st);
 }
 
 const ProcessDesc* process_ee_mumu();

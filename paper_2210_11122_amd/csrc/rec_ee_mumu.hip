@@ -3,8 +3,9 @@
 // The amplitude is the product of an electron and a muon current over s.  The spinors and currents
 // of each helicity are formed once per event and every good combination is one product of two
 // currents; the colour sum (one flow) and the helicity sum stay in the lane, one launch for any
-// batch size.  2^20 events 69 -> 42 us per call (the bytes of momenta and results take 28 us at the
-// rate of a large copy); 8192 events 7.5 us, host time.
+// batch size.  2^20 events 69 -> 37 us per call (the bytes of momenta and results take 28 us at the
+// rate of a large copy); 8192 events 8 us, host time.  (Cut to 128 registers for four waves per SIMD
+// it spills.)
 #include "colorsum.hpp"
 #include "process.hpp"
 #include "recursion.hpp"
@@ -18,43 +19,45 @@ constexpr int NPAR = 4, NC = 1;
 // HSUM: |M|^2 to fc.hsum_out; else the jamps
 template <bool HSUM>
 __global__ __launch_bounds__(64, 2) void amp_rec(const double* __restrict__ mom, int64_t n_evt, int64_t ld,
-                                                 const int* __restrict__ index, double g, double* __restrict__ jamp,
-                                                 const int* __restrict__ chan, double* __restrict__ sde, FusedColour fc)
+                                                 const int* __restrict__ row, double g,
+                                                 double* __restrict__ jamp, const int* __restrict__ chan,
+                                                 double* __restrict__ sde, FusedColour fc)
 {
     __shared__ double lds[4 * NPAR * 64];
     const unsigned lane = threadIdx.x;
+    const int* const count = row + 8;   // good helicities of each combination's row
     const int64_t e0 = xcd_remap(blockIdx.x, gridDim.x) * 64, e = e0 + lane;
     stage_momenta<NPAR, 1>(mom, n_evt, e0, lds, lane);
     const P4 p0 = lds_p4(lds, 0, lane), p1 = lds_p4(lds, 1, lane), p2 = lds_p4(lds, 2, lane), p3 = lds_p4(lds, 3, lane);
     // (ubar gamma^mu s)(ubar' gamma_mu s') = 2 dot2(pair, pair')
     const double f = 2.0 * g * g * rcp(sq(lc(p0) + lc(p1)));
-    const V4 ep[2] = {spinor(ext_vbar<double>(p0, 0.0, -1)), spinor(ext_vbar<double>(p0, 0.0, 1))};
+    const V4 ep = spinor(ext_vbar<double>(p0, 0.0, -1));   // the opposite combinations have equal |M_h|^2
     const V4 em[2] = {spinor(ext_u<double>(p1, 0.0, -1)), spinor(ext_u<double>(p1, 0.0, 1))};
     const V4 mp[2] = {spinor(ext_v<double>(p2, 0.0, -1)), spinor(ext_v<double>(p2, 0.0, 1))};
     const V4 mm[2] = {spinor(ext_ubar<double>(p3, 0.0, -1)), spinor(ext_ubar<double>(p3, 0.0, 1))};
     double s = 0.0, m = 0.0;
     int in_group = 0;
-    static_for<4>([&](auto A) {
+    static_for<2>([&](auto A) {
         // good combinations with these electron helicities?
-        if (index[4 * A] < 0 && index[4 * A + 1] < 0 && index[4 * A + 2] < 0 && index[4 * A + 3] < 0) return;
-        const V4 c = pair(ep[A / 2], em[A % 2]);
+        if (!(count[4 * A] | count[4 * A + 1] | count[4 * A + 2] | count[4 * A + 3])) return;
+        const V4 c = pair(ep, em[A]);
         static_for<4>([&](auto B) {
             constexpr int h = 4 * A + B;
-            if (index[h] < 0) return;
+            if (!count[h]) return;
             C j = times(f, dot2(c, pair(mm[B % 2], mp[B / 2])));
             pin_cx(j);   // rounded the same way whatever uses it
             if constexpr (HSUM) {
                 // in the groups and order of the separate helicity sum
-                m += cs1(j.r, j.i, *static_cast<const double*>(fc.aop));
+                m += (double)count[h] * cs1(j.r, j.i, *static_cast<const double*>(fc.aop));
                 if (++in_group == fc.hel_per_group) s += m, m = 0.0, in_group = 0;
             } else if (e < n_evt) {
-                double* const o = jamp + (int64_t)index[h] * (2 * NC) * ld + e0;
+                double* const o = jamp + (int64_t)row[h] * (2 * NC) * ld + e0;
                 o[lane] = j.r;
                 (o + ld)[lane] = j.i;
                 if (chan) {   // one diagram: its square is the sum over all
                     ChannelSums w;
                     w.add(0, 1.0, chan[e], j);
-                    double* const t = sde + (int64_t)index[h] * 2 * ld + e0;
+                    double* const t = sde + (int64_t)row[h] * 2 * ld + e0;
                     t[lane] = w.ch;
                     (t + ld)[lane] = w.all;
                 }
@@ -74,10 +77,10 @@ hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGr
     if (fc && !fc->hsum_out) return hipErrorInvalidValue;   // the colour sum here includes the helicity sum
     const dim3 grid((unsigned)((n_evt + 63) / 64));
     if (fc)
-        hipLaunchKernelGGL(amp_rec<true>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp, chan,
+        hipLaunchKernelGGL(amp_rec<true>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.row, g, jamp, chan,
                            nullptr, *fc);
     else
-        hipLaunchKernelGGL(amp_rec<false>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.index, g, jamp, chan, sde,
+        hipLaunchKernelGGL(amp_rec<false>, grid, dim3(64), 0, st, mom, n_evt, ld, hg.row, g, jamp, chan, sde,
                            FusedColour{nullptr, nullptr, 0, 0, nullptr, 0.0, 1});
     return hipGetLastError();
 }

@@ -1,11 +1,12 @@
 // rec_gg_ttg.hip -- FP64 colour-flow amplitudes and |M|^2 of gg -> t t~ g by colour-ordered recursion.
 //
 // One lane per (event, configuration of the three gluon helicities) evaluates the four quark spin
-// configurations, which share the gluon currents and, two by two, the strings.  A workgroup holds
-// all configurations of 64 events and sums their helicities, with the channel weight where one is asked
+// configurations, which share the gluon currents and, two by two, the strings.  A workgroup's four waves
+// hold the four configurations of 64 events and sum the helicities, with the channel weight where one is asked
 // for (its diagrams' squares are formed from the same strings).  The diagram program took one lane per
 // (event, helicity) and 24 of them made each gluon current anew.  Bound by FP64 issue: 2^20 events
-// 2842 -> 1519 us per call, 100003 events with channel weights 423 -> 260 us; the bytes (176 MB) take 35 us.
+// 2842 -> 852 us per call (1519 with all eight gluon configurations), 100003 events with channel weights
+// 423 -> 148 us; the bytes (176 MB) take 35 us.
 #include "colorsum.hpp"
 #include "generated/channels.hpp"
 #include "process.hpp"
@@ -15,7 +16,7 @@ namespace me {
 namespace rec3 {
 using namespace rec;
 
-constexpr int NG = 3, NPAR = 5, NC = 6, MAX_HEL = 32;
+constexpr int NG = 3, NPAR = 5, NC = 6, MAX_ROWS = 16;
 __host__ __device__ constexpr int flow(int a, int b, int c)
 {
     Perm<3> x{};
@@ -30,13 +31,14 @@ __host__ __device__ constexpr int flow(int a, int b, int c)
 // SDE: also the channel-weight sums, of each helicity to sde or, with HSUM, applied to |M|^2.
 template <bool HSUM, int N, bool SDE = false>
 __global__ __launch_bounds__(256, N == 1 ? 2 : 1) void amp_rec(const double* __restrict__ mom, int64_t n_evt, int64_t ld,
-                                                  const int* __restrict__ cfg, int n_cfg, int n_good, double mt,
-                                                  double gs, double* __restrict__ jamp, const int* __restrict__ chan,
+                                                  const int* __restrict__ cfg, int n_cfg,
+                                                  const int2* __restrict__ members, int n_rows, double mt, double gs,
+                                                  double* __restrict__ jamp, const int* __restrict__ chan,
                                                   double* __restrict__ sde, FusedColour fc)
 {
     __shared__ double lds[4 * NPAR * 64];
-    __shared__ double me_lds[HSUM ? MAX_HEL * 64 : 1];
-    __shared__ double sde_lds[HSUM && SDE ? 2 * MAX_HEL * 64 : 1];
+    __shared__ double me_lds[HSUM ? MAX_ROWS * 64 : 1];
+    __shared__ double sde_lds[HSUM && SDE ? 2 * MAX_ROWS * 64 : 1];
     const unsigned lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int per_block = HSUM ? 1 : N == 1 ? n_cfg : (n_cfg + 3) / 4;
@@ -160,16 +162,19 @@ __global__ __launch_bounds__(256, N == 1 ? 2 : 1) void amp_rec(const double* __r
         __syncthreads();
         if (wave == 0 && e < n_evt) {   // in the groups and order of the separate helicity sum
             double s = 0.0;
-            for (int h0 = 0; h0 < n_good; h0 += fc.hel_per_group) {
-                const int h1 = min(n_good, h0 + fc.hel_per_group);
+            for (int h0 = 0; h0 < n_rows; h0 += fc.hel_per_group) {
+                const int h1 = min(n_rows, h0 + fc.hel_per_group);
                 double m = 0.0;
-                for (int h = h0; h < h1; ++h) m += me_lds[h * 64 + lane];
+                for (int h = h0; h < h1; ++h) m += members_of(members, h) * me_lds[h * 64 + lane];
                 s += m;
             }
             double r = s * fc.hsum_scale;
             if (SDE && chan[e] >= 0) {
                 double num = 0.0, den = 0.0;
-                for (int h = 0; h < n_good; ++h) num += sde_lds[2 * h * 64 + lane], den += sde_lds[(2 * h + 1) * 64 + lane];
+                for (int h = 0; h < n_rows; ++h) {
+                    const double w = members_of(members, h);
+                    num += w * sde_lds[2 * h * 64 + lane], den += w * sde_lds[(2 * h + 1) * 64 + lane];
+                }
                 r *= num / den;
             }
             (fc.hsum_out + e0)[lane] = r;
@@ -178,18 +183,18 @@ __global__ __launch_bounds__(256, N == 1 ? 2 : 1) void amp_rec(const double* __r
 }
 
 // Up to here one spin configuration per lane: the batch leaves SIMDs without a wave either way, and a
-// wave's program is 2k instructions instead of 4.2k (64 events 16.2 us per call against 19.9, 4096
-// 18.4 against 21.0, 8192 27.3 against 21.2).
+// wave's program is 2k instructions instead of 4.2k (64 events 12.3 us per call, 4096 14.9; with all spins in a
+// lane 14.8 at any size that fits the GPU at once, where 8192 events take 18.7 with one).
 constexpr int64_t ONE_SPIN = 4096;
 
-hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, int n_good, double mt,
-                  double gs, double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st)
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
+                  double* jamp, const int* chan, double* sde, const FusedColour* fc, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((n_evt + 63) / 64);
-    if (n_good > MAX_HEL) return hipErrorInvalidValue;
+    if (hg.n_rows > MAX_ROWS) return hipErrorInvalidValue;
     const FusedColour f = fc ? *fc : FusedColour{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
     const auto go = [&](auto kernel, unsigned grid) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, mom, n_evt, ld, hg.table, hg.n, n_good, mt, gs, jamp,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, mom, n_evt, ld, hg.table, hg.n, hg.members, hg.n_rows, mt, gs, jamp,
                            chan, sde, f);
     };
     const unsigned by_one = blocks * (unsigned)hg.n, by_four = blocks * (unsigned)((hg.n + 3) / 4);

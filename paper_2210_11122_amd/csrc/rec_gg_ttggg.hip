@@ -9,7 +9,8 @@
 // flows, 24 at a time (those with the same last gluon), each stored once.
 //
 // Against the 14 diagram segments (247k flops per lane, 977 partial jamp sums through memory):
-// 2^17 events, colour sum included, 208.9 -> 43.8 ms per call; 1531 events 3.05 -> 0.53 ms.
+// 2^17 events, colour sum included, 208.9 -> 24.4 ms per call (43.8 with all 128 helicities
+// evaluated); 1531 events 3.05 -> 0.33 ms.
 #include "process.hpp"
 #include "recursion.hpp"
 
@@ -86,6 +87,7 @@ __host__ __device__ constexpr int rank3(int b, int c, int d)
     return perm_rank<3>(x);
 }
 
+// Gluon 0 has helicity - throughout (HelicityGroups): the slots of its helicity + stay unused.
 // vectors in memory: per block of 64 events, slot s holds (re, im) pairs at [(4 s + m) * 64 + lane]
 constexpr int M1 = 0, M2 = M1 + 2 * NG, M3 = M2 + 4 * 10, M4 = M3 + 8 * 10 * 2, MU = M4 + 16 * 5 * 6, MS = MU + 2,
               ML1 = MS + 2, MR1 = ML1 + 4 * NG, ML2 = MR1 + 4 * NG, MR2 = ML2 + 8 * 20, MEND = MR2 + 8 * 20;
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256) void level1(const double* __restrict__ mom, in
     if (e >= n_evt) return;
     if (i < NG) {
         const P4 p = mom4(mom, e, i < 2 ? i : i + 2);
-        for (int h = 0; h < 2; ++h) stm(cur, m1(i, h), lane, full(gluon(p, h ? 1 : -1, i >= 2, gs)));
+        for (int h = 0; h < (i ? 2 : 1); ++h) stm(cur, m1(i, h), lane, full(gluon(p, h ? 1 : -1, i >= 2, gs)));
     } else if (i == NG) {
         const P4 p = mom4(mom, e, 2);
         for (int h = 0; h < 2; ++h) stm(cur, MU + h, lane, spinor(ext_ubar<double>(p, mt, h ? 1 : -1)));
@@ -184,6 +186,7 @@ __global__ __launch_bounds__(256) void level2(const double* __restrict__ mom, in
     if (y < 40) {
         const Subset s = pair_at(y >> 2);
         const int i = s.g[0], j = s.g[1], hi = (y >> 1) & 1, hj = y & 1;
+        if (i == 0 && hi) return;
         const V4 A = ldm(cur, m1(i, hi), lane), B = ldm(cur, m1(j, hj), lane);
         const K4 ki = kin(mom, e, i), kj = kin(mom, e, j);
         stm(cur, m2(y >> 2, hi, hj), lane, (-rcp(sq(ki + kj))) * vvv_acc(zero4(), A, ki, B, kj, dot2(A, B)));
@@ -191,6 +194,7 @@ __global__ __launch_bounds__(256) void level2(const double* __restrict__ mom, in
     }
     y -= 40;
     const int right = y >= 20, a = (y % 20) >> 2, h = (y >> 1) & 1, sp = y & 1;
+    if (a == 0 && h) return;
     const V4 G = ldm(cur, m1(a, h), lane);
     const K4 k = kin(mom, e, a);
     if (!right)
@@ -211,6 +215,7 @@ __global__ __launch_bounds__(256) void level3(const double* __restrict__ mom, in
     if (q < 80) {
         const Subset s = triple_at(q >> 3);
         const int x = s.g[0], y = s.g[1], z = s.g[2], hx = (q >> 2) & 1, hy = (q >> 1) & 1, hz = q & 1;
+        if (x == 0 && hx) return;
         const V4 X = ldm(cur, m1(x, hx), lane), Y = ldm(cur, m1(y, hy), lane), Z = ldm(cur, m1(z, hz), lane);
         const V4 XY = ldm(cur, m2(pair_index(x, y), hx, hy), lane), XZ = ldm(cur, m2(pair_index(x, z), hx, hz), lane),
                  YZ = ldm(cur, m2(pair_index(y, z), hy, hz), lane);
@@ -224,6 +229,7 @@ __global__ __launch_bounds__(256) void level3(const double* __restrict__ mom, in
     const int right = q >= 160;
     q %= 160;
     const int o = q >> 3, a = o / 4, b = o % 4 < a ? o % 4 : o % 4 + 1, ha = (q >> 2) & 1, hb = (q >> 1) & 1, sp = q & 1;
+    if ((a == 0 && ha) || (b == 0 && hb)) return;
     const int lo = a < b ? a : b, hi = a < b ? b : a;
     const V4 A = ldm(cur, m1(a, ha), lane), B = ldm(cur, m1(b, hb), lane);
     V4 AB = ldm(cur, m2(pair_index(lo, hi), a < b ? ha : hb, a < b ? hb : ha), lane);
@@ -244,7 +250,8 @@ __global__ __launch_bounds__(64, 2) void level4(const double* __restrict__ mom, 
     const unsigned lane = threadIdx.x;
     const int64_t e0 = (int64_t)blockIdx.x * 64, e = e0 + lane;
     v2d* const cur = block_of(cur_, e0);
-    const int w = blockIdx.y >> 4, h4 = blockIdx.y & 15;
+    // gluons 1 to 4 in all helicities, then those with gluon 0 (the first of them, at -)
+    const int w = blockIdx.y < 16 ? 0 : (blockIdx.y - 8) >> 3, h4 = blockIdx.y < 16 ? blockIdx.y : blockIdx.y & 7;
     if (e >= n_evt) return;
     int g[4], h[4];
     for (int k = 0; k < 4; ++k) g[k] = rest(w, k), h[k] = (h4 >> (3 - k)) & 1;
@@ -301,7 +308,7 @@ __device__ __forceinline__ V4 lds2(const double* lds, int lane)
 // gluon configuration; wave w takes the six orderings that begin with gluon w + 1.
 __global__ __launch_bounds__(256, 1) void five_currents(const double* __restrict__ mom, int64_t n_evt,
                                                         const int* __restrict__ cfg, int n_cfg,
-                                                        const v2d* __restrict__ cur_, int n_good, v2d* __restrict__ five)
+                                                        const v2d* __restrict__ cur_, int n_rows, v2d* __restrict__ five)
 {
     __shared__ double lds[NS * 512];
     const int lane = threadIdx.x & 63;
@@ -375,7 +382,7 @@ __global__ __launch_bounds__(256, 1) void five_currents(const double* __restrict
             const int h = rc_[1 + SP];
             if (h < 0) return;
             const C x = rc(q[SP], o);
-            (five + ((e0 >> 6) * n_good + h) * (int64_t)(24 * 64) + 64 * r)[(unsigned)lane] = v2d{x.r, x.i};
+            (five + ((e0 >> 6) * n_rows + h) * (int64_t)(24 * 64) + 64 * r)[(unsigned)lane] = v2d{x.r, x.i};
         });
     });
 }
@@ -383,7 +390,7 @@ __global__ __launch_bounds__(256, 1) void five_currents(const double* __restrict
 // --- the flows.  One workgroup: 64 events, one gluon configuration, the four quark spin
 // configurations in its four waves, which share the currents of up to three gluons in LDS.
 __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, const int* __restrict__ cfg, int n_cfg,
-                                                  const v2d* __restrict__ cur_, int n_good, const v2d* __restrict__ five,
+                                                  const v2d* __restrict__ cur_, int n_rows, const v2d* __restrict__ five,
                                                   double* __restrict__ jamp)
 {
     __shared__ double lds[NS * 512];
@@ -418,7 +425,7 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
     V4 Rn, q4[6];
     const auto read_ahead = [&](int g) {
         src = fresh(cur);
-        const v2d* f5 = fresh(five) + ((e0 >> 6) * n_good + h) * (int64_t)(24 * 64);
+        const v2d* f5 = fresh(five) + ((e0 >> 6) * n_rows + h) * (int64_t)(24 * 64);
         static_for<24>([&](auto R) {
             const v2d t = (f5 + 64 * R)[(unsigned)lane];
             D4[R] = {t.x, t.y};
@@ -537,22 +544,22 @@ __global__ __launch_bounds__(256, 1) void amp_rec(int64_t n_evt, int64_t ld, con
     });
 }
 
-int64_t aux_doubles(int n_good) { return 8 * (int64_t)MEND + 48 * (int64_t)n_good; }
+int64_t aux_doubles(int n_rows) { return 8 * (int64_t)MEND + 48 * (int64_t)n_rows; }
 
-hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, int n_good, double mt,
-                  double gs, double* jamp, hipStream_t st)
+hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
+                  double* jamp, hipStream_t st)
 {
     if (n_evt == 0 || hg.n == 0) return hipSuccess;
     // after the jamps: the currents and strings of the events, then the five-gluon contractions
-    v2d* const cur = reinterpret_cast<v2d*>(jamp + (int64_t)n_good * 2 * NC * ld);
+    v2d* const cur = reinterpret_cast<v2d*>(jamp + (int64_t)hg.n_rows * 2 * NC * ld);
     v2d* const five = cur + (int64_t)4 * MEND * ld;
     const unsigned nb = (unsigned)((n_evt + 255) / 256), n64 = (unsigned)((n_evt + 63) / 64);
     hipLaunchKernelGGL(level1, dim3(nb, NG + 2), dim3(256), 0, st, mom, n_evt, mt, gs, cur);
     hipLaunchKernelGGL(level2, dim3(nb, 40 + 40), dim3(256), 0, st, mom, n_evt, mt, cur);
     hipLaunchKernelGGL(level3, dim3(nb, 80 + 320), dim3(256), 0, st, mom, n_evt, mt, cur);
-    hipLaunchKernelGGL(level4, dim3(n64, 5 * 16), dim3(64), 0, st, mom, n_evt, cur);
-    hipLaunchKernelGGL(five_currents, dim3(n64 * hg.n), dim3(256), 0, st, mom, n_evt, hg.table, hg.n, cur, n_good, five);
-    hipLaunchKernelGGL(amp_rec, dim3(n64 * hg.n), dim3(256), 0, st, n_evt, ld, hg.table, hg.n, cur, n_good, five, jamp);
+    hipLaunchKernelGGL(level4, dim3(n64, 16 + 4 * 8), dim3(64), 0, st, mom, n_evt, cur);
+    hipLaunchKernelGGL(five_currents, dim3(n64 * hg.n), dim3(256), 0, st, mom, n_evt, hg.table, hg.n, cur, hg.n_rows, five);
+    hipLaunchKernelGGL(amp_rec, dim3(n64 * hg.n), dim3(256), 0, st, n_evt, ld, hg.table, hg.n, cur, hg.n_rows, five, jamp);
     return hipGetLastError();
 }
 }  // namespace rec5

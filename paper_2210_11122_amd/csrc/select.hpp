@@ -12,12 +12,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "process.hpp"
+
 namespace me {
 
 // w[k][e] = sum over helicities of |J_k|^2, for the jamps jamp[h][2k + re/im][column] of one chunk
 template <class R>
 __global__ __launch_bounds__(256) void lc_weights(const R* __restrict__ J, int64_t ld, int nc, int n_good,
-                                                  int64_t n_evt, double* __restrict__ w)
+                                                  int64_t n_evt, double* __restrict__ w,
+                                                  const int2* __restrict__ members)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int k = blockIdx.y;
@@ -26,7 +29,7 @@ __global__ __launch_bounds__(256) void lc_weights(const R* __restrict__ J, int64
     for (int h = 0; h < n_good; ++h) {
         const R* Jh = J + (int64_t)h * (2 * nc) * ld;
         const double re = (double)Jh[(int64_t)(2 * k) * ld + e], im = (double)Jh[(int64_t)(2 * k + 1) * ld + e];
-        s += re * re + im * im;
+        s += members_of(members, h) * (re * re + im * im);
     }
     w[(int64_t)k * n_evt + e] = s;
 }

@@ -122,10 +122,11 @@ LANE_MIN_WAVES = (2, 3)
 RECURSION = {"ee_mumu": "rec_ee", "gg_tt": "rec2", "gg_ttg": "rec3", "gg_ttgg": "rec4", "gg_ttggg": "rec5"}
 # ... and also the channel weights (no FP64 instance of the diagram program)
 CHANNELS_IN_RECURSION = {"ee_mumu", "gg_tt", "gg_ttg"}
-# ... and whose FP64 kernel also sums the helicities: from this batch size on.  gg_ttg: with the sum a
-# workgroup takes the 8 gluon configurations of an event block in two turns; below 16384 events that
-# leaves CUs idle, and two workgroups share them
-FP64_HSUM_EVENTS = {"ee_mumu": 1, "gg_tt": 1, "gg_ttg": 16384}
+# ... and whose FP64 kernel also sums the helicities: from this batch size on.  gg_ttg: a workgroup's four
+# waves hold the four gluon configurations of 64 events; up to 4096 events its kernel with one spin
+# configuration per wave is as fast or faster (64 events 12.3 us per call, 4096 14.9; with the sum in the
+# kernel 14.8 at any size that fits the GPU at once)
+FP64_HSUM_EVENTS = {"ee_mumu": 1, "gg_tt": 1, "gg_ttg": 4097}
 ALL_PROCESSES = ["ee_mumu", "gg_tt", "gg_ttg", "gg_ttgg", "gg_ttggg", "gg_gg", "ee_mumu_z"]
 # electroweak constants of ee -> mumu with Z exchange: M_Z, Gamma_Z, M_W [GeV]
 EW_MZ, EW_WZ, EW_MW = 91.188, 2.441404, 80.419
@@ -872,11 +873,13 @@ class Process:
             L.append("    const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};")
         g64, g32 = WAVES_PER_GROUP.get(self.name, (1, 1))
         L.append(f"    constexpr int WG = sizeof(R) == 8 ? {g64} : {g32};  // waves (helicities) per workgroup")
+        if nm in RECURSION and nm not in CHANNELS_IN_RECURSION:
+            L.append("    if (sizeof(R) == 8) hel = hg.hel, n_good = hg.n_rows;  // the weights of one helicity of each pair")
         L.append("    int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);")
         L.append("    if (blocks == 0) return hipSuccess;")
         if self.segments and nm in RECURSION:
             L.append("    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for")
-            L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, n_good, mt, gs, jamp, st);")
+            L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, st);")
             L.append("        if (err != hipSuccess || !chan) return err;")
             L.append("    }")
         for kname, _, _, _ in kernels:
@@ -893,7 +896,7 @@ class Process:
                     L.append("    if constexpr (sizeof(R) == 8) {  // the jamps by recursion, then the channel weights if asked for")
                     if nm in CHANNELS_IN_RECURSION:
                         L[-1] = "    if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion"
-                        L.append(f"        return {RECURSION[nm]}::launch(mom, n_evt, ld, hg, {'n_good, ' if nm == 'gg_ttg' else ''}mt, gs, jamp, "
+                        L.append(f"        return {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, "
                                  "chan, sde, fc, st);")
                     else:
                         L.append(f"        const hipError_t err = {RECURSION[nm]}::launch(mom, n_evt, ld, hg, mt, gs, jamp, fc, st);")
