@@ -249,19 +249,26 @@ __device__ __forceinline__ double colour_blocks_part(const Get& x)
     });
     return sign_blocks<NG, S>(y);
 }
-template <int NG>
-__device__ __forceinline__ double colour_blocks(const cx<double> (&J)[factorial(NG)])
+// the blocks of all signs of the real or the imaginary parts, and D |M_h|^2 from both
+template <int NG, class Get>
+__device__ __forceinline__ double colour_blocks_signs(const Get& x)
 {
 #pragma clang fp contract(off)
-    const auto re = [&](auto F) { return J[F].r; };
-    const auto im = [&](auto F) { return J[F].i; };
-    const double r = (colour_blocks_part<NG, 0>(re) + colour_blocks_part<NG, 1>(re)) +
-                     (colour_blocks_part<NG, 2>(re) + colour_blocks_part<NG, 3>(re));
-    const double i = (colour_blocks_part<NG, 0>(im) + colour_blocks_part<NG, 1>(im)) +
-                     (colour_blocks_part<NG, 2>(im) + colour_blocks_part<NG, 3>(im));
+    return (colour_blocks_part<NG, 0>(x) + colour_blocks_part<NG, 1>(x)) +
+           (colour_blocks_part<NG, 2>(x) + colour_blocks_part<NG, 3>(x));
+}
+__device__ __forceinline__ double colour_blocks_total(double r, double i)
+{
     double v = (r + i) * (1.0 / 64.0);
     asm volatile("" : "+v"(v));
     return v;
+}
+template <int NG>
+__device__ __forceinline__ double colour_blocks(const cx<double> (&J)[factorial(NG)])
+{
+    const auto re = [&](auto F) { return J[F].r; };
+    const auto im = [&](auto F) { return J[F].i; };
+    return colour_blocks_total(colour_blocks_signs<NG>(re), colour_blocks_signs<NG>(im));
 }
 
 // |M_h|^2 of row h to the helicities that it stands for

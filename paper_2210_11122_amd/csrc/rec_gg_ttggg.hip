@@ -256,14 +256,24 @@ __global__ __launch_bounds__(64, 2) void level4(const double* __restrict__ mom, 
     int g[4], h[4];
     for (int k = 0; k < 4; ++k) g[k] = rest(w, k), h[k] = (h4 >> (3 - k)) & 1;
     const auto j1 = [&](int i) { return ldm(cur, m1(g[i], h[i]), lane); };
-    const auto j2 = [&](int i, int j) { return ldm(cur, m2(pair_index(g[i], g[j]), h[i], h[j]), lane); };
-    const auto j3 = [&](int x, int y, int z, int k) {
-        return ldm(cur, m3(triple_index(g[x], g[y], g[z]), h[x], h[y], h[z], k), lane);
+    const auto j2 = [&](int i, int j) {
+        const int a = min(i, j), b = max(i, j);
+        const V4 v = ldm(cur, m2(pair_index(g[a], g[b]), h[a], h[b]), lane);
+        return i < j ? v : -v;
+    };
+    const auto j3 = [&](int x, int y, int z) {
+        const int a = min(x, min(y, z)), c = max(x, max(y, z)), b = x + y + z - a - c;
+        const int s = m3(triple_index(g[a], g[b], g[c]), h[a], h[b], h[c], 0);
+        return three_ordered(x, y, z, [&] { return ldm(cur, s, lane); }, [&] { return ldm(cur, s + 1, lane); });
     };
     K4 k[4];
     for (int i = 0; i < 4; ++i) k[i] = kin(mom, e, g[i]);
     const double f = -rcp(sq(k[0] + k[1] + k[2] + k[3]));
-    static_for<6>([&](auto R) { stm(cur, m4(w, h4, R), lane, f * four_numerator<R>(j1, j2, j3, k)); });
+    static_for<6>([&](auto R) {
+        constexpr Perm<3> s = perm_at<3>(R);
+        stm(cur, m4(w, h4, R), lane, f * four_numerator(s.p[0] + 1, s.p[1] + 1, s.p[2] + 1, j1, j2, j3, k[0], k[s.p[0] + 1],
+                                                         k[s.p[1] + 1], k[s.p[2] + 1]));
+    });
 }
 
 // the currents of one helicity configuration in LDS: one to three gluons

@@ -267,26 +267,26 @@ __device__ __forceinline__ V4x2 three_currents(const T& X, const K4& kx, const T
     const V4 b = vvvv_acc(vvv_acc(-v, XZ, kx + kz, Y, ky, dot2(XZ, Y)), X, Z, Y, xz, yz, xy);
     return {{f * a, f * b}};
 }
-// -P^2 J(0 s) for the R-th ordering s of three others among four gluons 0 < 1 < 2 < 3, from the
-// currents j1(i), j2(i, j) with i < j, j3(x, y, z, k) = J(xyz), J(xzy) with x < y < z, and momenta k
-template <int R, class F1, class F2, class F3>
-__device__ __forceinline__ V4 four_numerator(const F1& j1, const F2& j2, const F3& j3, const K4 (&k)[4])
+// J(x y z) of three gluons in any order from the two independent ones, a = J(lo mid hi), b = J(lo hi mid)
+template <class FA, class FB>
+__device__ __forceinline__ V4 three_ordered(int x, int y, int z, const FA& a, const FB& b)
 {
-    constexpr Perm<3> s = perm_at<3>(R);
-    constexpr int b = s.p[0] + 1, c = s.p[1] + 1, d = s.p[2] + 1;
-    const V4 A = j1(0), B = j1(b), Cc = j1(c), D = j1(d), AB = j2(0, b);
-    const V4 BC = b < c ? j2(b, c) : -j2(c, b), CD = c < d ? j2(c, d) : -j2(d, c);
-    const V4 ABC = b < c ? j3(0, b, c, 0) : j3(0, c, b, 1);
-    constexpr int k0 = kk_table<3>.c[R][0], k1 = kk_table<3>.c[R][1];
-    static_assert((k0 == 1 && k1 == 0) || (k0 == 0 && k1 == 1) || (k0 == -1 && k1 == -1), "");
-    V4 BCD;
-    if constexpr (k1 == 0) BCD = j3(1, 2, 3, 0);
-    else if constexpr (k0 == 0) BCD = j3(1, 2, 3, 1);
-    else BCD = -(j3(1, 2, 3, 0) + j3(1, 2, 3, 1));
-    const K4 kab = k[0] + k[b], kcd = k[c] + k[d];
-    V4 o = vvv_acc(zero4(), A, k[0], BCD, k[b] + kcd, dot2(A, BCD));
+    const int lo = min(x, min(y, z)), hi = max(x, max(y, z));
+    if (y == lo) return -(a() + b());
+    return y == hi ? b() : a();
+}
+// -P^2 J(0 b c d) of four gluons 0 .. 3 from the currents j1(i), j2(i, j), j3(x, y, z) in any order, and
+// the momenta
+template <class F1, class F2, class F3>
+__device__ __forceinline__ V4 four_numerator(int b, int c, int d, const F1& j1, const F2& j2, const F3& j3, const K4& ka,
+                                             const K4& kb, const K4& kc, const K4& kd)
+{
+    const auto A = j1(0), B = j1(b), Cc = j1(c), D = j1(d);
+    const V4 AB = j2(0, b), BC = j2(b, c), CD = j2(c, d), ABC = j3(0, b, c), BCD = j3(b, c, d);
+    const K4 kab = ka + kb, kcd = kc + kd;
+    V4 o = vvv_acc(zero4(), A, ka, BCD, kb + kcd, dot2(A, BCD));
     o = vvv_acc(o, AB, kab, CD, kcd, dot2(AB, CD));
-    o = vvv_acc(o, ABC, kab + k[c], D, k[d], dot2(ABC, D));
+    o = vvv_acc(o, ABC, kab + kc, D, kd, dot2(ABC, D));
     o = vvvv_acc(o, A, B, CD, dot2(A, B), dot2(B, CD), dot2(A, CD));
     o = vvvv_acc(o, A, BC, D, dot2(A, BC), dot2(BC, D), dot2(A, D));
     return vvvv_acc(o, AB, Cc, D, dot2(AB, Cc), dot2(Cc, D), dot2(AB, D));
@@ -330,6 +330,26 @@ __device__ __forceinline__ V4 ld_v(const double* base, int k, int lane)
     lds_v2d* p = (lds_v2d*)base + 4 * k * 64 + lane;
     const v2d a = p[0], b = p[64], c = p[128], d = p[192];
     return {{a.x, a.y}, {b.x, b.y}, {c.x, c.y}, {d.x, d.y}};
+}
+
+// polarisation vectors in LDS: five numbers each, slot k at [5 k * 64]
+__device__ __forceinline__ void st_e(double* base, int k, int lane, const E4& v)
+{
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    double* const p = base + 5 * k * 64;
+    p[lane] = v.a;
+    reinterpret_cast<v2d*>(p + 64)[lane] = {v.c.r, v.c.i};
+    reinterpret_cast<v2d*>(p + 192)[lane] = {v.d.r, v.d.i};
+}
+__device__ __forceinline__ E4 ld_e(const double* base, int k, int lane)
+{
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) const volatile v2d lds_v2d;
+    typedef __attribute__((address_space(3))) const volatile double lds_d;
+    lds_d* const p = (lds_d*)base + 5 * k * 64;
+    const double a = p[lane];
+    const v2d c = ((lds_v2d*)(p + 64))[lane], d = ((lds_v2d*)(p + 192))[lane];
+    return {a, {c.x, c.y}, {d.x, d.y}};
 }
 
 }  // namespace rec
