@@ -66,6 +66,8 @@ def kernel_source_hash(process):
     with open(os.path.join(csrc, "generated", f"proc_{process}.hip"), "rb") as fh:
         gen = fh.read().split(b"const ProcessDesc* process_")[0]
     heads = ["helas.hpp"] + (["colorsum.hpp"] if b'#include "../colorsum.hpp"' in gen else [])
+    if os.path.exists(os.path.join(csrc, f"rec_{process}.hip")):   # the FP64 kernel
+        heads += [f"rec_{process}.hip", "recursion.hpp", "flows.hpp"]
     for name in heads:
         with open(os.path.join(csrc, name), "rb") as fh:
             h.update(fh.read())
@@ -398,7 +400,7 @@ def main():
         "latency_ms": {"p50": quantile(lat64, 0.5), "p99": quantile(lat64, 0.99), "unit": "ms per me_sigma call"},
         "roofline": {
             "bound": "alu",
-            "kernel": ("amplitude kernel with the colour sum (FP64 VALU, FP64 MFMA)" if fused
+            "kernel": ("amplitude kernel with the colour sum (FP64 VALU)" if fused
                        else "amplitude kernel (FP64 VALU)"),
             "achieved": achieved_tflops,
             "peak": FP64_VALU_PEAK_TFLOPS,
@@ -457,7 +459,8 @@ def main():
             outm, msm, latm, ms_amp_m, ms_cs_m, n_amp_m, _ = timed_steps(pm, x, args.steps, args.warmup, torch)
             rel = (outm / out64 - 1).abs().cpu().numpy()
             mesm = n_evt / (msm / 1e3)
-            ach_m = flops_amp_step * args.steps / (ms_amp_m / 1e3) / 1e12
+            flops_amp_m = pm.info["flops_amp_lane"] * lanes
+            ach_m = flops_amp_m * args.steps / (ms_amp_m / 1e3) / 1e12
             result[prec] = {
                 "value": mesm, "unit": "MEs/s", "ms_per_step": msm, "dtype": dt_name,
                 "rel_err_vs_fp64": {"max": float(rel.max()), "median": float(np.median(rel)),
@@ -470,7 +473,7 @@ def main():
             }
             if pm.info["n_partial_slots"] > 0 and n_evt > pm.info["chunk_events"]:
                 # two streams: per-launch times overlap (as for FP64 above)
-                result[prec]["amplitude_kernel_tflops_per_step_time"] = flops_amp_step / (msm / 1e3) / 1e12
+                result[prec]["amplitude_kernel_tflops_per_step_time"] = flops_amp_m / (msm / 1e3) / 1e12
             log(f"{prec}: {msm:.3f} ms/step, {mesm:.4g} MEs/s, rel err max {rel.max():.2e} "
                 f"median {np.median(rel):.2e}, colour sum {ms_cs_m / args.steps:.3f} ms/step")
             del pm

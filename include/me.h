@@ -3,11 +3,12 @@
  * The library computes, for every phase-space event independently, the tree-level
  * matrix element of a fixed process, summed over helicities and colours and averaged
  * over the initial states (the per-event ME calculation of the paper, Sec. 1 and 2; the
- * process set ee->mumu, gg->tt~ + 0..3 gluons of Sec. 2).  The GPU path evaluates every
- * Feynman diagram with HELAS-style wavefunctions, accumulates the colour-flow amplitudes,
- * contracts them with the colour matrix (on the matrix cores; in FP64 with up to six flows,
- * as scalar fused multiply-adds in each lane) and sums the helicities that a pre-pass found
- * to contribute.
+ * process set ee->mumu, gg->tt~ + 0..3 gluons of Sec. 2).  The GPU path forms the colour-flow
+ * amplitudes from HELAS-style wavefunctions (in FP64 by colour-ordered recursion, one
+ * helicity combination of each opposite pair, whose squares are equal; in the mixed forms,
+ * and for gg_gg and ee_mumu_z, from every Feynman diagram), contracts them with the colour
+ * matrix (FP64: fused multiply-adds in each lane; mixed: on the matrix cores) and sums the
+ * helicities that a pre-pass found to contribute.
  *
  * Conventions.  Units GeV; momenta (E, px, py, pz), metric (+,-,-,-).  Particle order:
  *   ee_mumu  (e+, e-, mu+, mu-)
@@ -173,12 +174,13 @@ int me_colour_flows(const me_handle *h, int *out);
 typedef struct {
     int n_par, n_diagrams, n_amplitudes, n_colors, n_hel, n_good_hel, precision;
     double avg_factor, sym_factor;
-    double flops_amp_lane;     /* algorithmic flops of the amplitude kernel per (event, helicity) */
-    double flops_amp_exec_lane;/* flops it executes (above when segment kernels recompute currents) */
+    double flops_amp_lane;     /* flops of the amplitude kernels per (event, good helicity): those of the
+                                  diagram program's algorithm; in FP64 with the recursion those executed */
+    double flops_amp_exec_lane;/* flops they execute (above when segment kernels recompute currents) */
     int n_partial_slots;       /* partial jamp slots per (event, helicity) of the segment kernels (mixed forms;
                                   0: none).  Processes that have them run batches of more than one chunk on
                                   two internal streams, in every precision */
-    double flops_colour_lane;  /* algorithmic flops of the colour sum per (event, helicity) */
+    double flops_colour_lane;  /* flops of the colour sum per (event, good helicity) */
     int64_t bytes_resident;    /* device bytes held by the handle (tables) */
     int64_t bytes_per_event_scratch; /* jamp scratch per event (per stream in use) */
     int64_t chunk_events;      /* events per amplitude/colour-sum launch pair */
@@ -217,11 +219,12 @@ int me_profile(me_handle *h, int enable, double *ms_amp, double *ms_colour, int6
  * ME_OPT_FUSED_COLOUR (default 1): for the plain |M|^2 (me_sigma, me_sigma_alphas) of a
  * process whose amplitude kernel ends holding all jamps of its lanes (every process but
  * gg_ttggg, whose jamps come out of a window of partial sums), in every precision, the
- * kernel contracts them with the colour matrix itself (the same matrix-core tiles, or scalar
- * forms, operand splits, sums and order as the separate colour-sum kernel of that precision,
+ * kernel contracts them with the colour matrix itself (the same matrix-core tiles, or FP64
+ * forms in the lane, operand splits, sums and order as the separate colour-sum kernel of that precision,
  * so each helicity's |M_h|^2 is bitwise the same) and writes one FP64 value per (event,
- * helicity) instead of the jamps; a second kernel sums the helicities in the separate
- * kernel's groups and order (the e+e- processes sum them in the same kernel).  0: always the separate colour-sum kernel.  Both settings, and the calls that
+ * evaluated helicity combination) instead of the jamps; a second kernel sums the helicities in the
+ * separate kernel's groups and order (ee_mumu, ee_mumu_z, and in FP64 gg_tt and gg_ttg above 4096
+ * events, sum them in the same kernel, which also applies the channel weights of me_sigma_channel).  0: always the separate colour-sum kernel.  Both settings, and the calls that
  * need the jamps (me_sigma_hel, me_sigma_select), give bitwise the same |M|^2.
  * ME_EINVAL for an unknown option or a value other than 0 or 1. */
 enum { ME_OPT_FUSED_COLOUR = 1 };

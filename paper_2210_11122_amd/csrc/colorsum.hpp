@@ -1,14 +1,15 @@
-// colorsum.hpp -- the colour-matrix contraction on the matrix cores, batched over events.
+// colorsum.hpp -- the colour-matrix contraction, batched over events: on the matrix cores in the mixed
+// forms, as fused multiply-adds in the lane in FP64.
 //
 // For every (event, helicity) column the amplitude kernel leaves the colour-flow
 // amplitudes J_c (c < NC, real and imaginary rows) in HBM, layout
 // jamp[h][2c + re/im][column], column = event within the chunk, row stride ld.  Here
 //     ME_h = (1/D) sum_{c,c'} (Re J_c Chat_{cc'} Re J_c' + Im J_c Chat_{cc'} Im J_c')
-// with Chat = D * C the integer colour matrix, as the matrix product Chat x J over 16
-// event columns per wavefront, followed by the column dot product and the sum over the
+// with Chat = D * C the integer colour matrix; in the mixed forms as the matrix product Chat x J
+// over 16 event columns per wavefront, followed by the column dot product and the sum over the
 // filtered helicities in FP64.
 //
-// Symmetry: Chat is symmetric, so with the colour index cut into blocks of 16 the
+// Symmetry (mixed forms): Chat is symmetric, so with the colour index cut into blocks of 16 the
 // contraction equals J^T A J for the block upper-triangular A with A = Chat on diagonal
 // blocks, 2 Chat above them and 0 below; only the tiles of A that touch the upper triangle
 // are multiplied (36 of 64 blocks for 120 flows).  The host prepares A in that form.
@@ -18,7 +19,9 @@
 // sum to part[group][event] and hel_reduce adds the groups in a fixed order, so every
 // event's result is independent of the batch it came in.
 //
-// FP64 form: v_mfma_f64_16x16x4f64 (A tile 16x4, B tile 4x16, D 16x16, all FP64).
+// FP64 form: up to six flows as row chains, 24 and 120 flows through the block-diagonal form below.
+// (The FP64 matrix cores run at the rate of the FP64 vector units, and the block form leaves 52 and 964
+// of the 576 and 14400 products.)
 // Mixed forms: the FP32 real (imaginary) rows of one (event, helicity) column are scaled by
 // a power of two so that their largest |J| lies in [1/2, 1), split exactly into two 16-bit
 // terms hi + lo * 2^-p (p = 11 for FP16, 8 for BF16), and contracted with
@@ -29,7 +32,6 @@
 // are skipped by a per-tile mask.
 //
 // MFMA operand layouts (lane l, i = l % 16, g = l / 16):
-//   f64 16x16x4:   A[i][g], B[g][i], D[g + 4r][i] (r = 0..3)
 //   16x16x32:      A[i][8g + t], B[8g + t][i] (t = 0..7), D[4g + r][i]
 // In the 16x16x32 form the k slot (kb, 8g + t) carries colour 16 (2 kb + t / 4) + 4 g + t % 4,
 // so that the B elements a lane holds are exactly the D rows it receives (the dot product

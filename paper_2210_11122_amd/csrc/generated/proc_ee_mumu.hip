@@ -217,7 +217,7 @@ const ProcessDesc* process_ee_mumu()
     static const ProcessDesc d = {
         "ee_mumu", proc_ee_mumu::NPAR, proc_ee_mumu::NC, 16, 4, 1, 0,
         proc_ee_mumu::colour_num, 1, proc_ee_mumu::final_massive, proc_ee_mumu::orderings, 0,
-        1, 1, 295.0, 295.0, proc_ee_mumu::NSLOT,
+        1, 1, 295.0, 295.0, 598.0, 9.0, proc_ee_mumu::NSLOT,
         proc_ee_mumu::diagram_lines, 1, 1, 1, 1, 1, 65536,
         nullptr, 1, 1,
         proc_ee_mumu::launch<double>, proc_ee_mumu::launch<float>,

@@ -175,7 +175,7 @@ const ProcessDesc* process_gg_gg()
     static const ProcessDesc d = {
         "gg_gg", proc_gg_gg::NPAR, proc_gg_gg::NC, 16, 256, 2, 1,
         proc_gg_gg::colour_num, 6, proc_gg_gg::final_massive, proc_gg_gg::orderings, 3,
-        4, 6, 1462.0, 1462.0, proc_gg_gg::NSLOT,
+        4, 6, 1462.0, 1462.0, 0.0, 0.0, proc_gg_gg::NSLOT,
         proc_gg_gg::diagram_lines, 1, 0, 1, 0, 0, 0,
         nullptr, 0, 0,
         proc_gg_gg::launch<double>, proc_gg_gg::launch<float>,

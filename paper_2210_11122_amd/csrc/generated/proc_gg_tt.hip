@@ -157,7 +157,7 @@ const ProcessDesc* process_gg_tt()
     static const ProcessDesc d = {
         "gg_tt", proc_gg_tt::NPAR, proc_gg_tt::NC, 16, 256, 1, 1,
         proc_gg_tt::colour_num, 3, proc_gg_tt::final_massive, proc_gg_tt::orderings, 2,
-        3, 3, 835.0, 835.0, proc_gg_tt::NSLOT,
+        3, 3, 835.0, 835.0, 2451.0, 25.0, proc_gg_tt::NSLOT,
         proc_gg_tt::diagram_lines, 1, 1, 1, 0, 1, 0,
         nullptr, 1, 1,
         proc_gg_tt::launch<double>, proc_gg_tt::launch<float>,

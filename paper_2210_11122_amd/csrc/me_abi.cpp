@@ -551,8 +551,8 @@ int upload_colour(me_handle* h)
         if (r >= NC || c >= NC || c / 16 < r / 16) return 0.0;
         return (c / 16 == r / 16 ? 1.0 : 2.0) * P->colour_num[r * NC + c];
     };
-    std::vector<double> a64;
-    for (int mt = 0; mt < MT; ++mt)
+    std::vector<double> a64;   // more flows: the block form, compiled in
+    for (int mt = 0; mt < MT && NC <= 6; ++mt)
         for (int kt = 4 * mt; kt < KT; ++kt)
             for (int l = 0; l < 64; ++l) a64.push_back(A(16 * mt + l % 16, 4 * kt + l / 16));
     std::vector<_Float16> a16;
@@ -584,10 +584,10 @@ int upload_colour(me_handle* h)
         }
     h->lo_mask_b16 = lo_mask;
     const size_t b64 = a64.size() * sizeof(double), b16 = a16.size() * sizeof(_Float16), bb = ab.size() * sizeof(__bf16);
-    if (hipMalloc(&h->d_aop64, b64) != hipSuccess || hipMalloc(&h->d_aop16, b16) != hipSuccess ||
+    if ((b64 && hipMalloc(&h->d_aop64, b64) != hipSuccess) || hipMalloc(&h->d_aop16, b16) != hipSuccess ||
         hipMalloc(&h->d_aopb, bb) != hipSuccess || hipMalloc(&h->d_aopb_lo, bb) != hipSuccess)
         return fail(ME_ENOMEM, "hipMalloc of the colour tables failed");
-    if (hipMemcpy(h->d_aop64, a64.data(), b64, hipMemcpyHostToDevice) != hipSuccess ||
+    if ((b64 && hipMemcpy(h->d_aop64, a64.data(), b64, hipMemcpyHostToDevice) != hipSuccess) ||
         hipMemcpy(h->d_aop16, a16.data(), b16, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(h->d_aopb, ab.data(), bb, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(h->d_aopb_lo, ablo.data(), bb, hipMemcpyHostToDevice) != hipSuccess)
@@ -771,10 +771,11 @@ int me_info(const me_handle* h, me_info_t* out)
     out->precision = h->precision;
     out->avg_factor = P->avg;
     out->sym_factor = P->sym;
-    out->flops_amp_lane = P->flops_lane;
-    out->flops_amp_exec_lane = P->flops_exec_lane;
+    const bool recursion = P->recursion && h->precision == ME_FP64;
+    out->flops_amp_lane = recursion ? P->flops_recursion / h->n_good : P->flops_lane;
+    out->flops_amp_exec_lane = recursion ? out->flops_amp_lane : P->flops_exec_lane;
     out->n_partial_slots = P->nslot;
-    out->flops_colour_lane = 4.0 * P->nc * P->nc + 4.0 * P->nc + 1.0;
+    out->flops_colour_lane = recursion ? P->flops_colour_row * h->n_rows / h->n_good : 4.0 * P->nc * P->nc + 4.0 * P->nc + 1.0;
     out->bytes_resident = (int64_t)h->bytes_resident;
     out->bytes_per_event_scratch = (int64_t)h->bytes_per_event;
     out->chunk_events = h->chunk;

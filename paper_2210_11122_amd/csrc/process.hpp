@@ -12,7 +12,7 @@ namespace me {
 // of the separate colour-sum kernel of the same form.  With a FusedColour the kernel writes
 // D |M_h|^2 as doubles to ((double*)jamp)[row * n_evt + event] instead of the jamps.
 struct FusedColour {
-    const void* aop;     // FP64 tiles (FP64 kernel) or FP16 / BF16 hi tiles (FP32 kernel)
+    const void* aop;     // FP64 numerators (FP64 kernels of up to six flows) or FP16 / BF16 hi tiles (FP32 kernel)
     const void* aop_lo;  // BF16 lo tiles (BF16 form)
     uint64_t lo_mask;    // tiles with a non-zero lo part (BF16 form)
     int form;            // ME_FP64, ME_MIXED_FP16 or ME_MIXED_BF16 (me.h)
@@ -81,6 +81,8 @@ struct ProcessDesc {
     int n_amplitudes;          // vertex contractions (four-gluon vertices count 3)
     double flops_lane;         // algorithmic flops of the amplitude kernel per (event, helicity)
     double flops_exec_lane;    // flops it executes (more when segments recompute currents)
+    double flops_recursion;    // FP64 recursion: flops of an event's jamps, and of the colour sum of a row (0: none)
+    double flops_colour_row;
     int nslot;                 // partial jamp slots per (event, helicity); 0: jamps written directly
     const int* diagram_lines;  // n_diagrams x lines_per_diagram internal-line masks (0-padded)
     int lines_per_diagram;

@@ -204,7 +204,7 @@ __device__ __forceinline__ void finish(double* lds, unsigned lane, int wave, int
 
 __global__ __launch_bounds__(512, 2) void amp_rec(const double* __restrict__ mom, int64_t n_evt, int64_t ld,
                                                   const int* __restrict__ cfg, int n_cfg, double mt, double gs,
-                                                  double* __restrict__ jamp, FusedColour fc)
+                                                  double* __restrict__ jamp, bool me)
 {
     __shared__ double lds[CUR + NSLOT * 512];
     double* const cur = lds + CUR;
@@ -280,18 +280,17 @@ __global__ __launch_bounds__(512, 2) void amp_rec(const double* __restrict__ mom
     }
     __syncthreads();
     const int sp = wave >> 1, h = row_cfg[1 + sp];   // the row of this wave's spins, or -1
-    if (wave & 1) finish<1>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, fc.aop);
-    else finish<0>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, fc.aop);
+    if (wave & 1) finish<1>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, me);
+    else finish<0>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, me);
 }
 
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
                   double* jamp, const FusedColour* fc, hipStream_t st)
 {
-    const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
     const int64_t blocks = ((n_evt + 63) / 64) * hg.n;
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL(amp_rec, dim3((unsigned)blocks), dim3(512), 0, st, mom, n_evt, ld, hg.table, hg.n, mt, gs, jamp,
-                       fc ? *fc : none);
+                       fc != nullptr);
     return hipGetLastError();
 }
 }  // namespace rec4

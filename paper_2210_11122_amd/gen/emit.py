@@ -61,10 +61,8 @@ MIN_WAVES = {"gg_tt": (4, 6), "gg_ttg": (2, 3), "gg_ttgg": (1, 2), "gg_ttggg": (
 # name -> waves per workgroup (FP64, FP32 kernels): consecutive helicities of one 64-event block
 # that share the staged momenta (less LDS per wave where LDS, not registers, limits the waves).
 # With several waves per group, FP32 kernels with register jamps stage them for the colour sum in
-# an LDS area of their own (a single wave reuses the momentum area).  gg_tt FP64 per 2^19 events
-# 0.197 -> 0.182 ms, mixed (six waves per SIMD) 0.272 -> 0.252 ms; gg_ttg FP64 per 2^20 3.14 ->
-# 2.77 ms (its three LDS externals and shared momenta then fit two waves per SIMD), mixed 2.86 ->
-# 2.62 ms (2.59 ms with its top spinors in LDS as well)
+# an LDS area of their own (a single wave reuses the momentum area).  gg_tt mixed per 2^19 events (six
+# waves per SIMD) 0.272 -> 0.252 ms; gg_ttg mixed per 2^20 2.86 -> 2.62 ms.
 # The test process gg_gg has six good helicities, so its second group of four carries two spare
 # waves: its parity tests cover that path.
 WAVES_PER_GROUP = {"gg_tt": (4, 4), "gg_ttg": (4, 4), "gg_ttgg": (4, 4), "gg_ttggg": (4, 8), "gg_gg": (4, 4)}
@@ -79,18 +77,12 @@ GLUONS_FROM_LDS = set()
 # "EXT_G:<j>" for gluon j) that the kernel keeps in LDS, private to each lane, instead of in
 # registers across the program: computed once, read ahead of each step that uses them (as the
 # momenta).  Only for processes without segment kernels.
-# * gg_ttgg FP64: the top spinors, 4 KB per wave each, room made by four waves per workgroup
-#   sharing the staged momenta (143 KB per workgroup, one per CU); per 2^19 events 24.89 -> 24.17
-#   ms (four waves alone: 24.59 ms; a third slot, a gluon, removes every scratch spill but
-#   measured 24.8 ms).
+# * gg_ttgg FP64 (only the channel weights run there): the top spinors, 4 KB per wave each, with four
+#   waves per workgroup sharing the staged momenta.
 # * gg_ttgg FP32: the same two, 2 KB per wave each, with four waves per workgroup (78 KB, two per
 #   CU); per 2^19 events 14.54 -> 14.20 ms (four waves alone: 14.33 ms; one spinor: 14.45 ms).
-# * gg_ttg FP64: the top spinors and a gluon (no spill left); per 2^20 events 4.01 -> 3.48 ms
-#   with one wave per workgroup (the spinors alone 3.64 ms; a fourth slot, 4.11 ms, left LDS
-#   for fewer than two waves per SIMD; with four waves per group a fourth slot gives 2.94 ms
-#   against 2.77 ms for three).
-EXT_IN_LDS = {"gg_ttgg": (("EXT_U", "EXT_V"), ("EXT_U", "EXT_V")),
-              "gg_ttg": (("EXT_U", "EXT_V", "EXT_G:1"), ("EXT_U", "EXT_V"))}
+# * gg_ttg FP32: the top spinors, per 2^20 events 2.62 -> 2.59 ms.
+EXT_IN_LDS = {"gg_ttgg": (("EXT_U", "EXT_V"), ("EXT_U", "EXT_V")), "gg_ttg": ((), ("EXT_U", "EXT_V"))}
 # read those ahead of the step that uses them (else at each use), and pin the copies
 PREFETCH_EXT = True
 PIN_EXT = True
@@ -98,7 +90,7 @@ PIN_EXT = True
 # workgroup holds every good helicity of an event block (64 lanes each), and its first wave adds
 # their D |M_h|^2 from LDS after the colour sum, so one launch gives |M|^2.  Only the tiny
 # e+e- processes, where a call is bound by launches: ee_mumu at 8192 events 29.7 -> 17.8 us per
-# call; gg_tt at 2^19 was slower (2.36e9 -> 2.20e9 MEs/s FP64, 1.98e9 -> 1.68e9 mixed), its
+# call; gg_tt mixed at 2^19 was slower (1.98e9 -> 1.68e9 MEs/s), its
 # 16-wave workgroups waiting for each other at the barriers
 HEL_SUM_IN_KERNEL = {"ee_mumu", "ee_mumu_z"}
 # ... and whose |M|^2 comes from a kernel with one lane per event that evaluates the event's
@@ -120,6 +112,11 @@ LANE_MIN_WAVES = (2, 3)
 # processes whose FP64 colour-flow amplitudes come from the colour-ordered recursion (csrc/rec_*.hip,
 # namespace): the FP64 diagram program then runs for the channel weights alone and keeps no jamps
 RECURSION = {"ee_mumu": "rec_ee", "gg_tt": "rec2", "gg_ttg": "rec3", "gg_ttgg": "rec4", "gg_ttggg": "rec5"}
+# ... the flops that those kernels execute: per event for the colour-flow amplitudes of all good
+# helicities (one of each opposite pair; counted by the hardware, an FMA as two), and per pair for the
+# colour sum
+RECURSION_FLOPS = {"ee_mumu": (598, 9), "gg_tt": (2451, 25), "gg_ttg": (24330, 169), "gg_ttgg": (343968, 400),
+                   "gg_ttggg": (3018503, 4466)}
 # ... and also the channel weights (no FP64 instance of the diagram program)
 CHANNELS_IN_RECURSION = {"ee_mumu", "gg_tt", "gg_ttg"}
 # ... and whose FP64 kernel also sums the helicities: from this batch size on.  gg_ttg: a workgroup's four
@@ -868,7 +865,8 @@ class Process:
             L.append("    if (fc) return hipErrorInvalidValue;  // no fused colour sum for this process")
         else:
             no_chan = "(chan && sizeof(R) == 4)" if nm in CHANNELS_IN_RECURSION else "chan"
-            L.append(f"    if (fc && ({no_chan} || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) "
+            no_table = "(!fc->aop && sizeof(R) == 4)" if nm in RECURSION and nc > 6 else "!fc->aop"
+            L.append(f"    if (fc && ({no_chan} || {no_table} || (sizeof(R) == 8) != (fc->form == ME_FP64))) "
                      "return hipErrorInvalidValue;")
             L.append("    const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};")
         g64, g32 = WAVES_PER_GROUP.get(self.name, (1, 1))
@@ -947,7 +945,8 @@ class Process:
                  f"{self.avg}, {self.sym}, {1 if self.coupling == 'alpha_s' else 0},")
         L.append(f"        proc_{nm}::colour_num, {self.cden}, proc_{nm}::final_massive, proc_{nm}::orderings, "
                  f"{n_order},")
-        L.append(f"        {self.n_diagrams}, {self.n_amplitudes}, {fl}.0, {self.flops_exec}.0, proc_{nm}::NSLOT,")
+        rf, cf = RECURSION_FLOPS.get(nm, (0, 0))
+        L.append(f"        {self.n_diagrams}, {self.n_amplitudes}, {fl}.0, {self.flops_exec}.0, {rf}.0, {cf}.0, proc_{nm}::NSLOT,")
         L.append(f"        proc_{nm}::diagram_lines, {nlines}, {0 if self.lines is None else 1}, {1 if fused else 0}, "
                  f"{1 if fused and nm in HEL_SUM_IN_KERNEL else 0}, {FP64_HSUM_EVENTS[nm] if nm in FP64_HSUM_EVENTS else LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0}, {LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0},")
         L.append(f"        {'rec5::aux_doubles' if nm == 'gg_ttggg' else 'nullptr'}, "
