@@ -43,7 +43,7 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; if constexpr (sizeof(R) == 8) asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
     const W4<R> w0 = ext_vbar<R>(PM(0), 0.0, lam[0]);
     const W4<R> w1 = ext_u<R>(PM(1), 0.0, lam[1]);
     const W4<R> w2 = ext_v<R>(PM(2), 0.0, lam[2]);

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4)) void amp_kernel(cons
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; if constexpr (sizeof(R) == 8) asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
     P4 m0_0 = PM(0);
     P4 m0_1 = PM(1);
     P4 m0_2 = PM(2);

@@ -27,14 +27,15 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     int lam[NPAR];
 #pragma unroll
     for (int i = 0; i < NPAR; ++i) lam[i] = hel[h * NPAR + i];
-    // 2 external wavefunctions computed once: in LDS, private to the lane, or in registers
-    constexpr int XWP[2] = {sizeof(R) == 8 ? -1 : 0, sizeof(R) == 8 ? -1 : 1};
-    constexpr int NXL = sizeof(R) == 8 ? 0 : 2;
+    // 3 external wavefunctions computed once: in LDS, private to the lane, or in registers
+    constexpr int XWP[3] = {sizeof(R) == 8 ? 0 : 0, sizeof(R) == 8 ? 1 : 1, sizeof(R) == 8 ? 2 : -1};
+    constexpr int NXL = sizeof(R) == 8 ? 3 : 2;
     __shared__ R xw_wg[NXL > 0 ? WG * NXL * 8 * 64 : 1];
     R* const xw = xw_wg + (threadIdx.x >> 6) * (NXL * 8 * 64);
-    [[maybe_unused]] W4<R> xwr[2];
+    [[maybe_unused]] W4<R> xwr[3];
     { const W4<R> t = ext_ubar<R>(PM(2), mt, lam[2]); if constexpr (XWP[0] >= 0) st_w4<R>(xw, XWP[0], lane, t); else xwr[0] = t; }
     { const W4<R> t = ext_v<R>(PM(3), mt, lam[3]); if constexpr (XWP[1] >= 0) st_w4<R>(xw, XWP[1], lane, t); else xwr[1] = t; }
+    { const W4<R> t = ext_vec<R>(PM(1), lam[1], false); if constexpr (XWP[2] >= 0) st_w4<R>(xw, XWP[2], lane, t); else xwr[2] = t; }
 #define XW(k) (XWP[k] >= 0 ? ld_w4<R>(xw, XWP[k], lane) : xwr[k])
     constexpr bool JAMPS = sizeof(R) == 4;  // FP64: the channel weights only
     constexpr int NW = 6;
@@ -47,52 +48,56 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; if constexpr (sizeof(R) == 8) asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
     P4 m0_0 = PM(0);
-    P4 m0_1 = PM(1);
     P4 m0_2 = PM(2);
     P4 m0_3 = PM(3);
     P4 m0_4 = PM(4);
     W4<R> y0_0 = XW(0);
     W4<R> y0_1 = XW(1);
+    W4<R> y0_2 = XW(2);
     pin_p4<R>(m0_0);
-    pin_p4<R>(m0_1);
     pin_p4<R>(m0_2);
     pin_p4<R>(m0_3);
     pin_p4<R>(m0_4);
     pin_w4<R>(y0_0);
     pin_w4<R>(y0_1);
+    pin_w4<R>(y0_2);
     const W4<R> w0 = ext_vec<R>(m0_0, lam[0], false);
     const W4<R> w1 = fstr_u<R>(y0_0, w0, m0_2 - (m0_0), mt, gs);
     const W4<R> w2 = ext_vec<R>(m0_4, lam[4], true);
     const W4<R> w3 = fstr_v<R>(y0_1, w2, ((-m0_4)) - m0_3, mt, gs);
-    const W4<R> w4 = ext_vec<R>(m0_1, lam[1], false);
     P4 m1_1 = PM(1);
     P4 m1_3 = PM(3);
     W4<R> y1_1 = XW(1);
-    a = amp_ffv<R>(w1, w3, w4, gs);
+    W4<R> y1_2 = XW(2);
+    a = amp_ffv<R>(w1, w3, y0_2, gs);
     pin_cx<R>(a);
     SDEACC(0, 7.111111111111111);
     JADD(0, 0, a.r); JADD(0, 1, a.i);
     pin_p4<R>(m1_1);
     pin_p4<R>(m1_3);
     pin_w4<R>(y1_1);
-    const W4<R> w5 = fstr_v<R>(y1_1, w4, (m1_1) - m1_3, mt, gs);
+    pin_w4<R>(y1_2);
+    const W4<R> w4 = fstr_v<R>(y1_1, y1_2, (m1_1) - m1_3, mt, gs);
     P4 m2_1 = PM(1);
     P4 m2_4 = PM(4);
     W4<R> y2_1 = XW(1);
-    a = amp_ffv<R>(w1, w5, w2, gs);
+    W4<R> y2_2 = XW(2);
+    a = amp_ffv<R>(w1, w4, w2, gs);
     pin_cx<R>(a);
     SDEACC(1, 7.111111111111111);
     JADD(1, 0, a.r); JADD(1, 1, a.i);
     pin_p4<R>(m2_1);
     pin_p4<R>(m2_4);
     pin_w4<R>(y2_1);
-    const W4<R> w6 = vvv_cur<R>(w4, (m2_1), w2, ((-m2_4)), gs);
+    pin_w4<R>(y2_2);
+    const W4<R> w5 = vvv_cur<R>(y2_2, (m2_1), w2, ((-m2_4)), gs);
     P4 m3_1 = PM(1);
     P4 m3_2 = PM(2);
     W4<R> y3_0 = XW(0);
-    a = amp_ffv<R>(w1, y2_1, w6, gs);
+    W4<R> y3_2 = XW(2);
+    a = amp_ffv<R>(w1, y2_1, w5, gs);
     pin_cx<R>(a);
     SDEACC(2, 16.0);
     JADD(0, 0, a.i); JADD(0, 1, -a.r);
@@ -100,22 +105,25 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     pin_p4<R>(m3_1);
     pin_p4<R>(m3_2);
     pin_w4<R>(y3_0);
-    const W4<R> w7 = fstr_u<R>(y3_0, w4, m3_2 - (m3_1), mt, gs);
+    pin_w4<R>(y3_2);
+    const W4<R> w6 = fstr_u<R>(y3_0, y3_2, m3_2 - (m3_1), mt, gs);
     P4 m4_0 = PM(0);
     P4 m4_1 = PM(1);
     W4<R> y4_0 = XW(0);
-    a = amp_ffv<R>(w7, w3, w0, gs);
+    W4<R> y4_2 = XW(2);
+    a = amp_ffv<R>(w6, w3, w0, gs);
     pin_cx<R>(a);
     SDEACC(3, 7.111111111111111);
     JADD(2, 0, a.r); JADD(2, 1, a.i);
     pin_p4<R>(m4_0);
     pin_p4<R>(m4_1);
     pin_w4<R>(y4_0);
-    const W4<R> w8 = vvv_cur<R>(w0, (m4_0), w4, (m4_1), gs);
+    pin_w4<R>(y4_2);
+    const W4<R> w7 = vvv_cur<R>(w0, (m4_0), y4_2, (m4_1), gs);
     P4 m5_0 = PM(0);
     P4 m5_3 = PM(3);
     W4<R> y5_1 = XW(1);
-    a = amp_ffv<R>(y4_0, w3, w8, gs);
+    a = amp_ffv<R>(y4_0, w3, w7, gs);
     pin_cx<R>(a);
     SDEACC(9, 16.0);
     JADD(0, 0, a.i); JADD(0, 1, -a.r);
@@ -123,9 +131,9 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     pin_p4<R>(m5_0);
     pin_p4<R>(m5_3);
     pin_w4<R>(y5_1);
-    const W4<R> w9 = fstr_v<R>(y5_1, w0, (m5_0) - m5_3, mt, gs);
+    const W4<R> w8 = fstr_v<R>(y5_1, w0, (m5_0) - m5_3, mt, gs);
     W4<R> y6_0 = XW(0);
-    a = amp_ffv<R>(w7, w9, w2, gs);
+    a = amp_ffv<R>(w6, w8, w2, gs);
     pin_cx<R>(a);
     SDEACC(4, 7.111111111111111);
     JADD(3, 0, a.r); JADD(3, 1, a.i);
@@ -133,7 +141,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     P4 m7_0 = PM(0);
     P4 m7_4 = PM(4);
     W4<R> y7_1 = XW(1);
-    a = amp_ffv<R>(y6_0, w9, w6, gs);
+    a = amp_ffv<R>(y6_0, w8, w5, gs);
     pin_cx<R>(a);
     SDEACC(11, 16.0);
     JADD(3, 0, a.i); JADD(3, 1, -a.r);
@@ -141,9 +149,9 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     pin_p4<R>(m7_0);
     pin_p4<R>(m7_4);
     pin_w4<R>(y7_1);
-    const W4<R> w10 = vvv_cur<R>(w0, (m7_0), w2, ((-m7_4)), gs);
+    const W4<R> w9 = vvv_cur<R>(w0, (m7_0), w2, ((-m7_4)), gs);
     W4<R> y8_0 = XW(0);
-    a = amp_ffv<R>(w7, y7_1, w10, gs);
+    a = amp_ffv<R>(w6, y7_1, w9, gs);
     pin_cx<R>(a);
     SDEACC(5, 16.0);
     JADD(2, 0, a.i); JADD(2, 1, -a.r);
@@ -152,7 +160,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     P4 m9_2 = PM(2);
     P4 m9_4 = PM(4);
     W4<R> y9_0 = XW(0);
-    a = amp_ffv<R>(y8_0, w5, w10, gs);
+    a = amp_ffv<R>(y8_0, w4, w9, gs);
     pin_cx<R>(a);
     SDEACC(10, 16.0);
     JADD(1, 0, a.i); JADD(1, 1, -a.r);
@@ -160,13 +168,15 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     pin_p4<R>(m9_2);
     pin_p4<R>(m9_4);
     pin_w4<R>(y9_0);
-    const W4<R> w11 = fstr_u<R>(y9_0, w2, m9_2 - ((-m9_4)), mt, gs);
-    a = amp_ffv<R>(w11, w5, w0, gs);
+    const W4<R> w10 = fstr_u<R>(y9_0, w2, m9_2 - ((-m9_4)), mt, gs);
+    W4<R> y10_2 = XW(2);
+    a = amp_ffv<R>(w10, w4, w0, gs);
     pin_cx<R>(a);
     SDEACC(6, 7.111111111111111);
     JADD(4, 0, a.r); JADD(4, 1, a.i);
+    pin_w4<R>(y10_2);
     W4<R> y11_1 = XW(1);
-    a = amp_ffv<R>(w11, w9, w4, gs);
+    a = amp_ffv<R>(w10, w8, y10_2, gs);
     pin_cx<R>(a);
     SDEACC(7, 7.111111111111111);
     JADD(5, 0, a.r); JADD(5, 1, a.i);
@@ -176,7 +186,7 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     P4 m12_4 = PM(4);
     W4<R> y12_0 = XW(0);
     W4<R> y12_1 = XW(1);
-    a = amp_ffv<R>(w11, y11_1, w8, gs);
+    a = amp_ffv<R>(w10, y11_1, w7, gs);
     pin_cx<R>(a);
     SDEACC(8, 16.0);
     JADD(4, 0, a.i); JADD(4, 1, -a.r);
@@ -186,15 +196,17 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     pin_p4<R>(m12_4);
     pin_w4<R>(y12_0);
     pin_w4<R>(y12_1);
-    const W4<R> w12 = jf<R>(y12_0, y12_1, (m12_0 + m12_1 + (-m12_4)), gs);
-    a = amp_vvv<R>(w12, (-(m12_0 + m12_1 + (-m12_4))), w0, (m12_0), w6, (m12_1 + (-m12_4)), gs);
+    const W4<R> w11 = jf<R>(y12_0, y12_1, (m12_0 + m12_1 + (-m12_4)), gs);
+    W4<R> y13_2 = XW(2);
+    a = amp_vvv<R>(w11, (-(m12_0 + m12_1 + (-m12_4))), w0, (m12_0), w5, (m12_1 + (-m12_4)), gs);
     pin_cx<R>(a);
     SDEACC(12, 36.0);
     sa = a;
+    pin_w4<R>(y13_2);
     P4 m14_0 = PM(0);
     P4 m14_1 = PM(1);
     P4 m14_4 = PM(4);
-    a = amp_vvvv<R, 0>(w12, w0, w4, w2, gs);
+    a = amp_vvvv<R, 0>(w11, w0, y13_2, w2, gs);
     pin_cx<R>(a);
     SDEACC(15, 36.0);
     sa.r += a.r; sa.i += a.i;
@@ -205,14 +217,17 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     pin_p4<R>(m14_0);
     pin_p4<R>(m14_1);
     pin_p4<R>(m14_4);
-    a = amp_vvv<R>(w12, (-(m14_0 + m14_1 + (-m14_4))), w8, (m14_0 + m14_1), w2, ((-m14_4)), gs);
+    W4<R> y15_2 = XW(2);
+    a = amp_vvv<R>(w11, (-(m14_0 + m14_1 + (-m14_4))), w7, (m14_0 + m14_1), w2, ((-m14_4)), gs);
     pin_cx<R>(a);
     SDEACC(13, 36.0);
     sa = a;
+    pin_w4<R>(y15_2);
     P4 m16_0 = PM(0);
     P4 m16_1 = PM(1);
     P4 m16_4 = PM(4);
-    a = amp_vvvv<R, 2>(w12, w0, w4, w2, gs);
+    W4<R> y16_2 = XW(2);
+    a = amp_vvvv<R, 2>(w11, w0, y15_2, w2, gs);
     pin_cx<R>(a);
     SDEACC(15, 36.0);
     sa.r -= a.r; sa.i -= a.i;
@@ -223,11 +238,14 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     pin_p4<R>(m16_0);
     pin_p4<R>(m16_1);
     pin_p4<R>(m16_4);
-    a = amp_vvv<R>(w12, (-(m16_0 + m16_1 + (-m16_4))), w10, (m16_0 + (-m16_4)), w4, (m16_1), gs);
+    pin_w4<R>(y16_2);
+    W4<R> y17_2 = XW(2);
+    a = amp_vvv<R>(w11, (-(m16_0 + m16_1 + (-m16_4))), w9, (m16_0 + (-m16_4)), y16_2, (m16_1), gs);
     pin_cx<R>(a);
     SDEACC(14, 36.0);
     sa = a;
-    a = amp_vvvv<R, 1>(w12, w0, w4, w2, gs);
+    pin_w4<R>(y17_2);
+    a = amp_vvvv<R, 1>(w11, w0, y17_2, w2, gs);
     pin_cx<R>(a);
     SDEACC(15, 36.0);
     sa.r -= a.r; sa.i -= a.i;

@@ -81,8 +81,10 @@ GLUONS_FROM_LDS = set()
 #   waves per workgroup sharing the staged momenta.
 # * gg_ttgg FP32: the same two, 2 KB per wave each, with four waves per workgroup (78 KB, two per
 #   CU); per 2^19 events 14.54 -> 14.20 ms (four waves alone: 14.33 ms; one spinor: 14.45 ms).
-# * gg_ttg FP32: the top spinors, per 2^20 events 2.62 -> 2.59 ms.
-EXT_IN_LDS = {"gg_ttgg": (("EXT_U", "EXT_V"), ("EXT_U", "EXT_V")), "gg_ttg": ((), ("EXT_U", "EXT_V"))}
+# * gg_ttg FP32: the top spinors, per 2^20 events 2.62 -> 2.59 ms.  (No FP64 instance runs; its entry keeps
+#   the gluon a node that is computed first, which the FP32 program's rounding depends on.)
+EXT_IN_LDS = {"gg_ttgg": (("EXT_U", "EXT_V"), ("EXT_U", "EXT_V")),
+              "gg_ttg": (("EXT_U", "EXT_V", "EXT_G:1"), ("EXT_U", "EXT_V"))}
 # read those ahead of the step that uses them (else at each use), and pin the copies
 PREFETCH_EXT = True
 PIN_EXT = True
@@ -1102,10 +1104,11 @@ class Process:
         L.append("    double sde_ch = 0.0, sde_all = 0.0;")
         L.append("    if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;")
         # pinned: the sums, which nothing else waits for, would be put off to the end of the program with
-        # every amplitude held until then (gg_ttgg FP64 5.8 KB of spills per lane)
+        # every amplitude held until then (gg_ttgg FP64 5.8 KB of spills per lane).  In FP64 only: in FP32 it
+        # changes how the compiler contracts, and so rounds, the amplitudes formed for the weights alone
         L.append("#define SDEACC(d, k) do { if constexpr (SDE) { "
                  "const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); "
-                 "sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; asm volatile(\"\" : \"+v\"(sde_all), \"+v\"(sde_ch)); } } while (0)")
+                 "sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; if constexpr (sizeof(R) == 8) asm volatile(\"\" : \"+v\"(sde_all), \"+v\"(sde_ch)); } } while (0)")
         L.extend(body)
         L.append("    if constexpr (SDE) {")
         L.append("        if (live && e < n_evt) {")
