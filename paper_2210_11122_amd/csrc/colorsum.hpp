@@ -473,11 +473,13 @@ __device__ __forceinline__ double colour_sum_lds_h16(const float* Jl, const type
 // The helicity sum after the fused colour sum, in the order of the separate colour-sum kernel
 // with the same helicity groups: within each group of hel_per_group consecutive rows from
 // zero, then the groups in order (so the result is bitwise that of the separate kernels).
-// part_h[row][e] = D |M_h|^2.
+// part_h[row][e] = D |M_h|^2.  out_hel: also the helicities' own |M_h|^2.
 static __global__ __launch_bounds__(256) void hel_reduce_grouped(const double* __restrict__ part_h, int n_good,
                                                                  int hel_per_group, int64_t n_evt, double scale,
                                                                  double* __restrict__ out,
-                                                                 const int2* __restrict__ members)
+                                                                 const int2* __restrict__ members,
+                                                                 double* __restrict__ out_hel = nullptr, int n_hel = 0,
+                                                                 double scale_hel = 0.0)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= n_evt) return;
@@ -485,7 +487,11 @@ static __global__ __launch_bounds__(256) void hel_reduce_grouped(const double* _
     for (int h0 = 0; h0 < n_good; h0 += hel_per_group) {
         const int h1 = min(n_good, h0 + hel_per_group);
         double m = 0.0;
-        for (int h = h0; h < h1; ++h) m += members_of(members, h) * part_h[(int64_t)h * n_evt + e];
+        for (int h = h0; h < h1; ++h) {
+            const double v = part_h[(int64_t)h * n_evt + e];
+            if (out_hel) store_hel(out_hel + e * n_hel, members, h, v * scale_hel);
+            m += members_of(members, h) * v;
+        }
         s += m;
     }
     out[e] = s * scale;

@@ -219,7 +219,7 @@ const ProcessDesc* process_ee_mumu()
         proc_ee_mumu::colour_num, 1, proc_ee_mumu::final_massive, proc_ee_mumu::orderings, 0,
         1, 1, 295.0, 295.0, 598.0, 9.0, proc_ee_mumu::NSLOT,
         proc_ee_mumu::diagram_lines, 1, 1, 1, 1, 1, 65536,
-        nullptr, 1, 1,
+        nullptr, 1, 0, 0, 1,
         proc_ee_mumu::launch<double>, proc_ee_mumu::launch<float>,
     };
     return &d;

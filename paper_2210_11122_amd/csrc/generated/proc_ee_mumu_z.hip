@@ -220,7 +220,7 @@ const ProcessDesc* process_ee_mumu_z()
         proc_ee_mumu_z::colour_num, 1, proc_ee_mumu_z::final_massive, proc_ee_mumu_z::orderings, 0,
         2, 2, 534.0, 534.0, 0.0, 0.0, proc_ee_mumu_z::NSLOT,
         proc_ee_mumu_z::diagram_lines, 1, 1, 1, 1, 65536, 65536,
-        nullptr, 0, 0,
+        nullptr, 0, 0, 0, 0,
         proc_ee_mumu_z::launch<double>, proc_ee_mumu_z::launch<float>,
     };
     return &d;

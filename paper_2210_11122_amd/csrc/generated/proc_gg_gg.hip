@@ -177,7 +177,7 @@ const ProcessDesc* process_gg_gg()
         proc_gg_gg::colour_num, 6, proc_gg_gg::final_massive, proc_gg_gg::orderings, 3,
         4, 6, 1462.0, 1462.0, 0.0, 0.0, proc_gg_gg::NSLOT,
         proc_gg_gg::diagram_lines, 1, 0, 1, 0, 0, 0,
-        nullptr, 0, 0,
+        nullptr, 0, 0, 0, 0,
         proc_gg_gg::launch<double>, proc_gg_gg::launch<float>,
     };
     return &d;

@@ -159,7 +159,7 @@ const ProcessDesc* process_gg_tt()
         proc_gg_tt::colour_num, 3, proc_gg_tt::final_massive, proc_gg_tt::orderings, 2,
         3, 3, 835.0, 835.0, 2451.0, 25.0, proc_gg_tt::NSLOT,
         proc_gg_tt::diagram_lines, 1, 1, 1, 0, 1, 0,
-        nullptr, 1, 1,
+        nullptr, 1, 0, 0, 1,
         proc_gg_tt::launch<double>, proc_gg_tt::launch<float>,
     };
     return &d;

@@ -337,7 +337,7 @@ const ProcessDesc* process_gg_ttg()
         proc_gg_ttg::colour_num, 9, proc_gg_ttg::final_massive, proc_gg_ttg::orderings, 3,
         16, 18, 3647.0, 3647.0, 24330.0, 169.0, proc_gg_ttg::NSLOT,
         proc_gg_ttg::diagram_lines, 2, 1, 1, 0, 4097, 0,
-        nullptr, 1, 1,
+        nullptr, 1, 1, 0, 1,
         proc_gg_ttg::launch<double>, proc_gg_ttg::launch<float>,
     };
     return &d;

@@ -438,6 +438,9 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
     // mixed forms of one flow whose colour operand the 16-bit type holds exactly)
     const bool hsum_waves = fused_any && P->hel_sum_in_kernel && n_good <= 16;
     const int64_t lane_min = precision == ME_FP64 ? P->lane_min_f64 : P->lane_min_mixed;
+    // the per-helicity output, and the selection: |M_h|^2 (and the flow weights) from the kernel
+    const bool rows_form = fp64 && P->rows_in_kernel && h->fuse_colour && !chan &&
+                           (sel ? P->flow_weights_in_kernel != 0 : out_hel != nullptr);
     const bool lane_form = fused_any && lane_min > 0 && (precision == ME_FP64 || !(fcol.lo_mask & 1));
     void* jamp = scratch;
     double* part = reinterpret_cast<double*>(static_cast<char*>(scratch) + (size_t)chunk * jamp_bytes_per_event);
@@ -448,7 +451,8 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
         TimedLaunch ta(h, st, 0, timed);
         const int* ch = chan ? chan + c0 : nullptr;
         const bool hsum = hsum_waves || (lane_form && nc >= lane_min);
-        const bool fused = fused_any && (hsum || !chan);   // with a channel weight: only where it is applied in the kernel
+        double* const oh = sel ? sel->hel_me : (out_hel ? out_hel + c0 * n_good : nullptr);
+        const bool fused = rows_form || (fused_any && (hsum || !chan));   // with a channel weight: only where it is applied in the kernel
         hipError_t e;
         if (fused && hsum) {
             // the amplitude kernel ends with the colour sum and the helicity sum
@@ -463,6 +467,7 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
         } else if (fused) {
             // the amplitude kernel ends with the colour sum: D |M_h|^2 per (helicity, event) in the
             // jamp scratch, then the helicity sum in the separate kernels' order (same groups)
+            if (sel) fcol.flow_weights = static_cast<double*>(jamp) + (size_t)n_rows * nc;
             e = fp64 ? P->launch_f64(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<double*>(jamp), nullptr,
                                      nullptr, &fcol, hg, st)
                      : P->launch_f32(m, nc, ld, hel, n_good, h->mt, h->g, static_cast<float*>(jamp), nullptr,
@@ -472,7 +477,8 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             TimedLaunch tc(h, st, 1, timed);
             hipLaunchKernelGGL(me::hel_reduce_grouped, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st,
                                static_cast<const double*>(jamp), n_rows, hel_per_group, nc,
-                               1.0 / ((double)P->colour_den * P->avg), out + c0, members);
+                               1.0 / ((double)P->colour_den * P->avg), out + c0, members, oh, n_good,
+                               1.0 / P->colour_den);
             e = hipGetLastError();
             tc.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("helicity-sum kernel: ") + hipGetErrorString(e));
@@ -482,7 +488,6 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             ta.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("amplitude kernel: ") + hipGetErrorString(e));
             TimedLaunch tc(h, st, 1, timed);
-            double* oh = sel ? sel->hel_me : (out_hel ? out_hel + c0 * n_good : nullptr);
             e = colour_sum(h, precision, jamp, ld, n_rows, hel_per_group, groups, nc, out + c0, oh, part, members, n_good, st);
             tc.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("colour-sum kernel: ") + hipGetErrorString(e));
@@ -501,7 +506,10 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
         }
         if (sel) {
             const dim3 grid((unsigned)((nc + 255) / 256), (unsigned)P->nc);
-            if (fp64)
+            if (rows_form)
+                hipLaunchKernelGGL(me::lc_weights_grouped, dim3((unsigned)((nc * P->nc + 255) / 256)), dim3(256), 0, st,
+                                   fcol.flow_weights, hg.n, nc * P->nc, sel->w);
+            else if (fp64)
                 hipLaunchKernelGGL(me::lc_weights<double>, grid, dim3(256), 0, st, static_cast<const double*>(jamp), ld,
                                    P->nc, n_rows, nc, sel->w, members);
             else

@@ -24,6 +24,9 @@ struct FusedColour {
     double* hsum_out;
     double hsum_scale;
     int hel_per_group;
+    // processes with flow_weights_in_kernel: if set, the kernel also writes for every group of
+    // HelicityGroups::table sum |J_f|^2 over the good helicities of the group, [group][flow][event]
+    double* flow_weights = nullptr;
 };
 
 // The good helicities of a process with FP64 recursion, two by two.  Tree amplitudes of QED and QCD with
@@ -94,6 +97,8 @@ struct ProcessDesc {
     int64_t lane_min_f64, lane_min_mixed;
     int64_t (*aux_doubles)(int n_rows);  // doubles per event that the FP64 launch needs after the jamps (null: none)
     int channel_in_kernel;     // the FP64 kernel that sums the helicities also applies the channel weight (chan with fc)
+    int rows_in_kernel;        // the FP64 kernel writes D |M_h|^2 of every row (a FusedColour without hsum_out) ...
+    int flow_weights_in_kernel;  // ... and the flow weights (FusedColour.flow_weights)
     int recursion;             // the FP64 jamps come from the recursion, without partial slots
     amp_launch_f64 launch_f64;
     amp_launch_f32 launch_f32;

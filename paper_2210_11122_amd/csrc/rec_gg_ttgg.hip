@@ -5,8 +5,10 @@
 // flows that have gluon 0 among the first two, or among the last two, for one of the four quark spin
 // configurations.  Bound by FP64 issue (3.4k vector instructions per wave; the issue slots are 63 % full)
 // with two waves per SIMD, for which the 158 KB of LDS leave room.  2^19 events: the diagram program
-// 20.6 ms per call, 4.95 with four waves that made their strings themselves, 4.85 now; with the
-// per-helicity output (20000 events) 279 -> 260 us.
+// 20.6 ms per call, 4.95 with four waves that made their strings themselves, 4.85 now.  The
+// kernel also gives the helicities' |M_h|^2 and the flows' weights, so neither call takes the jamps through
+// memory: 20000 events with the per-helicity output 260 -> 216 us, with selection 326 -> 265 us (9973
+// events 192 -> 151).
 #include "colorsum.hpp"
 #include "process.hpp"
 #include "recursion.hpp"
@@ -21,8 +23,10 @@ constexpr int NG = 4, NPAR = 6, NC = 24;
 // without w, and the strings of one gluon from the quark and from the antiquark end
 constexpr int EPS = 4 * NPAR * 64, CUR = EPS + 5 * NG * 64;
 constexpr int SU = 0, SV = 2, S2 = 4, S3 = 10, SL = 18, SR = 26, NSLOT = 34;
-// once the strings are used: J(0 s) times the quark currents, and the parts of the flows that waves exchange
-constexpr int FOUR = CUR + 512 * S2, XCH = CUR + 512 * SL;
+// once the strings are used: J(0 s) times the quark currents, |J|^2 of the flows, and the parts of the flows
+// that waves exchange
+constexpr int FOUR = CUR + 512 * S2, LCW = FOUR + 6 * 4 * 128, XCH = LCW + 8 * 12 * 64;
+static_assert(XCH + 8 * 12 * 64 <= CUR + 512 * NSLOT, "");
 
 __host__ __device__ constexpr int s2(int i, int j) { return S2 + i * (2 * NG - i - 1) / 2 + j - i - 1; }   // i < j
 // the gluons without w in ascending order
@@ -148,7 +152,8 @@ __device__ __forceinline__ Flows quark_line(const double* lds, unsigned lane, in
 // the rest of a wave's work, with barriers: the flows of half H of spin configuration sp, |M_h|^2 or the jamps
 template <int H>
 __device__ __forceinline__ void finish(double* lds, unsigned lane, int wave, int sp, const C (&four)[4], int64_t n_evt,
-                                       int64_t ld, int64_t e0, int h, double mt, double* __restrict__ jamp, bool me)
+                                       int64_t ld, int64_t e0, int h, double mt, double* __restrict__ jamp, bool me,
+                                       double members, double* __restrict__ flow_weights)
 {
     const int64_t e = e0 + lane;
     Flows J = quark_line<H>(lds, lane, sp >> 1, sp & 1, mt);
@@ -186,7 +191,17 @@ __device__ __forceinline__ void finish(double* lds, unsigned lane, int wave, int
     }
     // half 0 takes the real parts of all flows through the colour sum, half 1 the imaginary parts
     static_for<NC / 2>([&](auto F_) { lds[XCH + (12 * wave + F_) * 64 + lane] = H == 0 ? J.v[F_].i : J.v[F_].r; });
+    if (flow_weights)
+        static_for<NC / 2>([&](auto F_) {
+            lds[LCW + (12 * wave + F_) * 64 + lane] = members * fma(J.v[F_].r, J.v[F_].r, J.v[F_].i * J.v[F_].i);
+        });
     __syncthreads();
+    if (flow_weights && e < n_evt)   // three flows per wave, over the spin configurations
+        static_for<NC>([&](auto F_) {
+            if (F_ / 3 != wave) return;
+            lds_d* const x = (lds_d*)(lds + LCW) + (12 * half_of(F_) + in_half(F_)) * 64 + lane;
+            (flow_weights + F_ * n_evt)[e] = (x[0] + x[24 * 64]) + (x[48 * 64] + x[72 * 64]);
+        });
     lds_d* const other = (lds_d*)(lds + XCH) + 12 * (wave ^ 1) * 64;
     double all[NC];
     static_for<NC>([&](auto F_) {
@@ -204,7 +219,8 @@ __device__ __forceinline__ void finish(double* lds, unsigned lane, int wave, int
 
 __global__ __launch_bounds__(512, 2) void amp_rec(const double* __restrict__ mom, int64_t n_evt, int64_t ld,
                                                   const int* __restrict__ cfg, int n_cfg, double mt, double gs,
-                                                  double* __restrict__ jamp, bool me)
+                                                  double* __restrict__ jamp, bool me,
+                                                  const int2* __restrict__ members, double* __restrict__ flow_weights)
 {
     __shared__ double lds[CUR + NSLOT * 512];
     double* const cur = lds + CUR;
@@ -280,8 +296,10 @@ __global__ __launch_bounds__(512, 2) void amp_rec(const double* __restrict__ mom
     }
     __syncthreads();
     const int sp = wave >> 1, h = row_cfg[1 + sp];   // the row of this wave's spins, or -1
-    if (wave & 1) finish<1>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, me);
-    else finish<0>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, me);
+    const double count = h >= 0 ? members_of(members, h) : 0.0;
+    if (flow_weights) flow_weights += (w % n_cfg) * NC * n_evt;
+    if (wave & 1) finish<1>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, me, count, flow_weights);
+    else finish<0>(lds, lane, wave, sp, four, n_evt, ld, e0, h, mt, jamp, me, count, flow_weights);
 }
 
 hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGroups& hg, double mt, double gs,
@@ -290,7 +308,7 @@ hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const HelicityGr
     const int64_t blocks = ((n_evt + 63) / 64) * hg.n;
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL(amp_rec, dim3((unsigned)blocks), dim3(512), 0, st, mom, n_evt, ld, hg.table, hg.n, mt, gs, jamp,
-                       fc != nullptr);
+                       fc != nullptr, hg.members, fc ? fc->flow_weights : nullptr);
     return hipGetLastError();
 }
 }  // namespace rec4

@@ -34,6 +34,17 @@ __global__ __launch_bounds__(256) void lc_weights(const R* __restrict__ J, int64
     w[(int64_t)k * n_evt + e] = s;
 }
 
+// the same from the amplitude kernel's sums part[group][k][e] over the helicities of each of n groups
+static __global__ __launch_bounds__(256) void lc_weights_grouped(const double* __restrict__ part, int n, int64_t size,
+                                                                 double* __restrict__ w)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= size) return;
+    double s = 0.0;
+    for (int g = 0; g < n; ++g) s += part[g * size + i];
+    w[i] = s;
+}
+
 // index drawn from the weights x[0..n) (stride `stride` between consecutive weights) with uniform r
 __device__ __forceinline__ int draw(const double* x, int n, int64_t stride, double r)
 {

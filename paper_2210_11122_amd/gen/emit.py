@@ -952,7 +952,8 @@ class Process:
         L.append(f"        proc_{nm}::diagram_lines, {nlines}, {0 if self.lines is None else 1}, {1 if fused else 0}, "
                  f"{1 if fused and nm in HEL_SUM_IN_KERNEL else 0}, {FP64_HSUM_EVENTS[nm] if nm in FP64_HSUM_EVENTS else LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0}, {LANE_MIN_EVENTS if fused and nm in LANE_PER_EVENT else 0},")
         L.append(f"        {'rec5::aux_doubles' if nm == 'gg_ttggg' else 'nullptr'}, "
-                 f"{1 if nm in CHANNELS_IN_RECURSION else 0}, {1 if nm in RECURSION else 0},")
+                 f"{1 if nm in CHANNELS_IN_RECURSION else 0}, {1 if nm in ('gg_ttg', 'gg_ttgg') else 0}, "
+                 f"{1 if nm == 'gg_ttgg' else 0}, {1 if nm in RECURSION else 0},")
         L.append(f"        proc_{nm}::launch<double>, proc_{nm}::launch<float>,")
         L.append("    };")
         L.append("    return &d;")

@@ -85,3 +85,20 @@ def test_massless_tops_leave_spin_configurations_out(name, n):
     assert all(len(s) < 4 for s in spins.values())
     p = oracle.rambo(33, W.sqrt_s(name), [0.0] * (W.n_par(name) - 2), n)
     check(name, p, proc.sigma(torch.from_numpy(p).cuda()).cpu().numpy(), params)
+
+
+@pytest.mark.parametrize("name,n", [("gg_ttg", 65), ("gg_ttg", 4161), ("gg_ttgg", 1), ("gg_ttgg", 1000)])
+def test_rows_and_flow_weights_from_the_kernel(name, n):
+    """the per-helicity output and the draws from the values that the amplitude kernel writes, against those
+    from the jamps in memory (the separate colour sum): |M_h|^2 bitwise, and the draws the same (their weights
+    differ by the order of a sum, 1e-15, so a uniform would have to lie that close to a boundary)"""
+    from paper_2210_11122_amd import Process
+    proc = Process(name, m_top=W.M_TOP, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
+    x = proc.rambo(7, W.sqrt_s(name), n)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    u = torch.rand((2, n), generator=g, dtype=torch.float64, device="cuda")
+    got = [(*proc.sigma(x, per_helicity=True), *proc.select(x, u[0].contiguous(), u[1].contiguous()))]
+    proc.set_fused_colour(False)
+    got.append((*proc.sigma(x, per_helicity=True), *proc.select(x, u[0].contiguous(), u[1].contiguous())))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
