@@ -233,7 +233,8 @@ __global__ __launch_bounds__(512, 2) void amp_rec(const double* __restrict__ mom
     stage_momenta<NPAR, 8>(mom, n_evt, e0, lds, threadIdx.x);
     const auto P = [&](int i) { return lc(lds_p4(lds, i, lane)); };
     // incoming momentum of gluon i
-    const auto kin = [&](int i) { return i < 2 ? P(i) : -P(i + 2); };
+    const auto pin = [&](int i) { return i < 2 ? lds_p4(lds, i, lane) : -lds_p4(lds, i + 2, lane); };
+    const auto kin = [&](int i) { return lc(pin(i)); };
     const auto G1 = [&](int i) { return ld_e(lds + EPS, i, lane); };
 
     // external states, one per wave
@@ -262,8 +263,9 @@ __global__ __launch_bounds__(512, 2) void amp_rec(const double* __restrict__ mom
     if (wave < 6) {
         const int i = pair_i(wave), j = pair_j(wave);
         const E4 A = G1(i), B = G1(j);
-        const K4 ki = kin(i), kj = kin(j);
-        st_v(cur, S2 + wave, lane, (-rcp(sq(ki + kj))) * vvv_acc(zero4(), A, ki, B, kj, dot2(A, B)));
+        const P4 pi = pin(i), pj = pin(j);
+        const K4 ki = lc(pi), kj = lc(pj);
+        st_v(cur, S2 + wave, lane, pair_prop(pi, pj) * vvv_acc(zero4(), A, ki, B, kj, dot2(A, B)));
     } else {
         string(wave - 6);
     }

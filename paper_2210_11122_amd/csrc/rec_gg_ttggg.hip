@@ -148,11 +148,12 @@ __device__ __forceinline__ P4 mom4(const double* __restrict__ mom, int64_t e, in
     return {a.x, a.y, b.x, b.y};
 }
 // incoming momentum of gluon i
-__device__ __forceinline__ K4 kin(const double* __restrict__ mom, int64_t e, int i)
+__device__ __forceinline__ P4 pin(const double* __restrict__ mom, int64_t e, int i)
 {
-    const K4 k = lc(mom4(mom, e, i < 2 ? i : i + 2));
-    return i < 2 ? k : -k;
+    const P4 p = mom4(mom, e, i < 2 ? i : i + 2);
+    return i < 2 ? p : -p;
 }
+__device__ __forceinline__ K4 kin(const double* __restrict__ mom, int64_t e, int i) { return lc(pin(mom, e, i)); }
 
 // --- level 1: external states; y: gluon, or 5: quark, 6: antiquark; both helicities
 __global__ __launch_bounds__(256) void level1(const double* __restrict__ mom, int64_t n_evt, double mt, double gs,
@@ -188,8 +189,9 @@ __global__ __launch_bounds__(256) void level2(const double* __restrict__ mom, in
         const int i = s.g[0], j = s.g[1], hi = (y >> 1) & 1, hj = y & 1;
         if (i == 0 && hi) return;
         const V4 A = ldm(cur, m1(i, hi), lane), B = ldm(cur, m1(j, hj), lane);
-        const K4 ki = kin(mom, e, i), kj = kin(mom, e, j);
-        stm(cur, m2(y >> 2, hi, hj), lane, (-rcp(sq(ki + kj))) * vvv_acc(zero4(), A, ki, B, kj, dot2(A, B)));
+        const P4 pi = pin(mom, e, i), pj = pin(mom, e, j);
+        const K4 ki = lc(pi), kj = lc(pj);
+        stm(cur, m2(y >> 2, hi, hj), lane, pair_prop(pi, pj) * vvv_acc(zero4(), A, ki, B, kj, dot2(A, B)));
         return;
     }
     y -= 40;
