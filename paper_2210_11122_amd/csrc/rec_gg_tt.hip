@@ -6,7 +6,8 @@
 // took about 1k for each of the 12 good combinations).  The colour sum and the helicity sum stay in the
 // lane: one launch, also for the smallest batch.  2^19 events 118.7 -> 38.1 us per call (67.4 with all
 // 16 evaluated; the bytes of momenta and results take 14 us), 256 events 11.2 -> 8.1 us (host time).
-// The channel weight is applied in the same launch: 65000 events 43.5 -> 12.3 us per call.
+// The channel weight is applied in the same launch: 65000 events 43.5 -> 12.3 us per call (its sums are kept per row
+// and added in the rows' order at the end; 2^19 events 43.8 us, 43.7 added as they came).
 #include "colorsum.hpp"
 #include "generated/channels.hpp"
 #include "process.hpp"
@@ -49,7 +50,7 @@ __global__ __launch_bounds__(64, 2) void amp_rec(const double* __restrict__ mom,
     const V4 U[2] = {spinor(ext_ubar<double>(pt, mt, -1)), spinor(ext_ubar<double>(pt, mt, 1))};
     const Prop q0 = prop(k0 - lc(pu), mt), q1 = prop(k1 - lc(pu), mt);
     double me[8];
-    [[maybe_unused]] double num = 0.0, den = 0.0;
+    [[maybe_unused]] ChannelSums weights[8];
     [[maybe_unused]] const int channel = SDE && e < n_evt ? chan[e] : -1;
     static_for<2>([&](auto SV) {
         // (formed here, so that only one antiquark spin's strings are held)
@@ -85,12 +86,7 @@ __global__ __launch_bounds__(64, 2) void amp_rec(const double* __restrict__ mom,
                 constexpr int h = 4 * I + 2 * SU + SV;
                 pin_cx(j0[I]), pin_cx(j1[I]);   // rounded the same way whatever uses them
                 if constexpr (HSUM) {
-                    if constexpr (SDE) {
-                        if (count[h]) {
-                            const double w = (double)count[h];
-                            num += w * sums[I].ch, den += w * sums[I].all;
-                        }
-                    }
+                    if constexpr (SDE) weights[h] = sums[I];
                     me[h] = cs2(j0[I].r, j0[I].i, j1[I].r, j1[I].i, static_cast<const double*>(fc.aop));
                 } else if (count[h] && e < n_evt) {
                     double* const o = jamp + (int64_t)row[h] * (2 * NC) * ld + e0;
@@ -118,7 +114,14 @@ __global__ __launch_bounds__(64, 2) void amp_rec(const double* __restrict__ mom,
     });
     if (in_group) s += m;
     double r = s * fc.hsum_scale;
-    if (SDE && channel >= 0) r *= num / den;
+    if (SDE && channel >= 0) {   // the rows in order, as where the weights are summed by a kernel of their own
+        double num = 0.0, den = 0.0;
+        static_for<8>([&](auto H) {
+            const double w = (double)count[H];
+            if (count[H]) num += w * weights[H].ch, den += w * weights[H].all;
+        });
+        r *= num / den;
+    }
     (fc.hsum_out + e0)[lane] = r;
 }
 

@@ -126,3 +126,21 @@ def test_near_beam_events_keep_their_values():
             assert np.all(np.abs(got / want - 1) < 1e-11), (name, i, n, np.abs(got / want - 1).max())
         ok, rel, spread = referee.judge(name, p, got[0], W.PARAMS)
         assert ok, (name, i, rel, spread)
+
+
+@pytest.mark.parametrize("name,n", [("ee_mumu", 257), ("gg_tt", 1), ("gg_tt", 4161)])
+def test_channel_weights_do_not_depend_on_the_route(name, n):
+    """The channel weights of a batch, of slices of it and with the separate colour sum: the same bits, with every
+    diagram's id among the events, none (-1) and one past the last."""
+    from paper_2210_11122_amd import Process
+    print(f"case channel routes {name} n={n}", flush=True)
+    proc = Process(name, m_top=W.M_TOP, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
+    x = proc.rambo(9, W.sqrt_s(name), n)
+    nd = proc.info["n_diagrams"]
+    ch = (torch.arange(n, device="cuda") % (nd + 2) - 1).to(torch.int32)
+    whole = proc.sigma_channel(x, ch)
+    slices = [proc.sigma_channel(x[i:i + 1387].contiguous(), ch[i:i + 1387].contiguous()) for i in range(0, n, 1387)]
+    assert torch.isfinite(whole).all() and bool((whole[ch >= nd] == 0).all())
+    assert torch.equal(torch.cat(slices), whole)
+    proc.set_fused_colour(False)
+    assert torch.equal(proc.sigma_channel(x, ch), whole)
