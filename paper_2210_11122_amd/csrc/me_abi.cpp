@@ -193,9 +193,13 @@ hipError_t launch_cs64(const double* J, const double* aop, const ColourArgs& a, 
                            a.part, a.members, a.n_hel);
     } else {
         constexpr int T = NC > 6 ? 64 : 256;
-        hipLaunchKernelGGL((me::colour_sum_f64<NC>), dim3((unsigned)((a.n + T - 1) / T), (unsigned)a.groups), dim3(T),
-                           0, st, J, a.ld, a.n_good, a.hel_per_group, a.n, aop, a.scale_hel, a.scale_avg, a.out,
-                           a.out_hel, a.part, a.members, a.n_hel);
+        const auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((a.n + T - 1) / T), (unsigned)a.groups), dim3(T), 0, st, J, a.ld,
+                               a.n_good, a.hel_per_group, a.n, aop, a.scale_hel, a.scale_avg, a.out, a.out_hel, a.part,
+                               a.members, a.n_hel);
+        };
+        if (a.members) go(me::colour_sum_f64<NC, true>);
+        else go(me::colour_sum_f64<NC, false>);
     }
     return hipGetLastError();
 }
@@ -338,7 +342,9 @@ __global__ __launch_bounds__(256) void scale_alphas(double* __restrict__ out, co
 }
 
 // single-diagram enhancement: out[e] *= (sum_h W_chan,h) / (sum_h sum_d W_d,h) from the
-// per-lane sums sde[h][0: channel, 1: all][column] of the amplitude kernel; chan[e] < 0: no factor
+// per-lane sums sde[h][0: channel, 1: all][column] of the amplitude kernel; chan[e] < 0: no factor.
+// PAIRS: the rows stand for one or two helicities
+template <bool PAIRS>
 __global__ __launch_bounds__(256) void sde_apply(double* __restrict__ out, const double* __restrict__ sde,
                                                  const int* __restrict__ chan, int n_rows, int64_t ld, int64_t n,
                                                  const int2* __restrict__ members)
@@ -347,7 +353,7 @@ __global__ __launch_bounds__(256) void sde_apply(double* __restrict__ out, const
     if (e >= n || chan[e] < 0) return;
     double num = 0.0, den = 0.0;
     for (int h = 0; h < n_rows; ++h) {
-        const double w = me::members_of(members, h);
+        const double w = me::members_of<PAIRS>(members, h);
         num += w * sde[(int64_t)(2 * h) * ld + e];
         den += w * sde[(int64_t)(2 * h + 1) * ld + e];
     }
@@ -475,10 +481,15 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             ta.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("amplitude kernel: ") + hipGetErrorString(e));
             TimedLaunch tc(h, st, 1, timed);
-            hipLaunchKernelGGL(me::hel_reduce_grouped, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st,
-                               static_cast<const double*>(jamp), n_rows, hel_per_group, nc,
-                               1.0 / ((double)P->colour_den * P->avg), out + c0, members, oh, n_good,
-                               1.0 / P->colour_den);
+            const auto reduce = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st,
+                                   static_cast<const double*>(jamp), n_rows, hel_per_group, nc,
+                                   1.0 / ((double)P->colour_den * P->avg), out + c0, members, oh, n_good,
+                                   1.0 / P->colour_den);
+            };
+            if (!members) reduce(me::hel_reduce_grouped<false, false>);   // (per-helicity output only from pairs)
+            else if (oh) reduce(me::hel_reduce_grouped<true, true>);
+            else reduce(me::hel_reduce_grouped<true, false>);
             e = hipGetLastError();
             tc.done();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("helicity-sum kernel: ") + hipGetErrorString(e));
@@ -493,8 +504,8 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
             if (e != hipSuccess) return fail(ME_EHIP, std::string("colour-sum kernel: ") + hipGetErrorString(e));
         }
         if (chan && !fused) {
-            hipLaunchKernelGGL(sde_apply, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, out + c0, sde, ch,
-                               n_rows, ld, nc, members);
+            hipLaunchKernelGGL(members ? sde_apply<true> : sde_apply<false>, dim3((unsigned)((nc + 255) / 256)), dim3(256),
+                               0, st, out + c0, sde, ch, n_rows, ld, nc, members);
             e = hipGetLastError();
             if (e != hipSuccess) return fail(ME_EHIP, std::string("channel-weight kernel: ") + hipGetErrorString(e));
         }
@@ -506,15 +517,17 @@ int run_chunks(me_handle* h, int precision, const signed char* hel, const me::He
         }
         if (sel) {
             const dim3 grid((unsigned)((nc + 255) / 256), (unsigned)P->nc);
-            if (rows_form)
+            if (rows_form) {
                 hipLaunchKernelGGL(me::lc_weights_grouped, dim3((unsigned)((nc * P->nc + 255) / 256)), dim3(256), 0, st,
                                    fcol.flow_weights, hg.n, nc * P->nc, sel->w);
-            else if (fp64)
-                hipLaunchKernelGGL(me::lc_weights<double>, grid, dim3(256), 0, st, static_cast<const double*>(jamp), ld,
-                                   P->nc, n_rows, nc, sel->w, members);
-            else
-                hipLaunchKernelGGL(me::lc_weights<float>, grid, dim3(256), 0, st, static_cast<const float*>(jamp), ld,
-                                   P->nc, n_rows, nc, sel->w, members);
+            } else if (fp64) {
+                const auto kernel = members ? me::lc_weights<double, true> : me::lc_weights<double, false>;
+                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, static_cast<const double*>(jamp), ld, P->nc, n_rows,
+                                   nc, sel->w, members);
+            } else {
+                hipLaunchKernelGGL((me::lc_weights<float, false>), grid, dim3(256), 0, st,
+                                   static_cast<const float*>(jamp), ld, P->nc, n_rows, nc, sel->w, members);
+            }
             hipLaunchKernelGGL(me::select_events, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, sel->hel_me,
                                n_good, sel->w, P->nc, nc, h->d_hel_index, sel->r_hel + c0, sel->r_col + c0,
                                sel->out_hel + c0, sel->out_col + c0);

@@ -51,10 +51,11 @@ struct HelicityGroups {
     const signed char* hel;
     int n_rows;   // 0: no recursion, a row is a good helicity (members is null)
 };
-// how many good helicities row r stands for
+// how many good helicities row r stands for; PAIRS: whether the rows are pairs (else members is null)
+template <bool PAIRS = true>
 __device__ __forceinline__ double members_of(const int2* __restrict__ members, int r)
 {
-    if (!members) return 1.0;
+    if constexpr (!PAIRS) return 1.0;
     const int2 m = members[r];
     return (m.x >= 0 ? 1.0 : 0.0) + (m.y >= 0 ? 1.0 : 0.0);
 }

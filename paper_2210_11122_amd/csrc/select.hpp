@@ -16,9 +16,10 @@
 
 namespace me {
 
-// w[k][e] = sum over helicities of |J_k|^2, for the jamps jamp[h][2k + re/im][column] of one chunk
-template <class R>
-__global__ __launch_bounds__(256) void lc_weights(const R* __restrict__ J, int64_t ld, int nc, int n_good,
+// w[k][e] = sum over helicities of |J_k|^2, for the jamps jamp[row][2k + re/im][column] of one chunk (PAIRS:
+// the rows stand for one or two helicities)
+template <class R, bool PAIRS>
+__global__ __launch_bounds__(256) void lc_weights(const R* __restrict__ J, int64_t ld, int nc, int n_rows,
                                                   int64_t n_evt, double* __restrict__ w,
                                                   const int2* __restrict__ members)
 {
@@ -26,10 +27,10 @@ __global__ __launch_bounds__(256) void lc_weights(const R* __restrict__ J, int64
     const int k = blockIdx.y;
     if (e >= n_evt) return;
     double s = 0.0;
-    for (int h = 0; h < n_good; ++h) {
+    for (int h = 0; h < n_rows; ++h) {
         const R* Jh = J + (int64_t)h * (2 * nc) * ld;
         const double re = (double)Jh[(int64_t)(2 * k) * ld + e], im = (double)Jh[(int64_t)(2 * k + 1) * ld + e];
-        s += members_of(members, h) * (re * re + im * im);
+        s += members_of<PAIRS>(members, h) * (re * re + im * im);
     }
     w[(int64_t)k * n_evt + e] = s;
 }

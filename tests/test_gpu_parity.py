@@ -391,3 +391,26 @@ def test_info_counts():
         assert (i["n_diagrams"], i["n_colors"], i["n_hel"]) == (nd, nc, nh)
         assert i["fused_colour"] == (0 if name == "gg_ttggg" else 1)
     assert make_process("gg_ttggg", "mixed_fp16").info["fused_colour"] == 0
+
+
+@pytest.mark.parametrize("name,precision", [("gg_gg", "fp64"), ("ee_mumu_z", "fp64"), ("gg_tt", "mixed_fp16"),
+                                            ("gg_ttg", "mixed_bf16"), ("gg_ttg", "fp64"), ("gg_ttgg", "fp64")])
+def test_calls_agree_with_and_without_pairs(name, precision):
+    """The sums over helicities have one instance for rows that are helicities and one for pairs of them: plain,
+    per-helicity and drawn calls of a ragged batch give the same |M|^2, bit by bit, and the helicities' values add up
+    to it."""
+    proc = make_process(name, precision)
+    n = 321
+    print(f"case pairs {name} {precision}", flush=True)
+    x = proc.rambo(17, W.sqrt_s(name), n)
+    u = torch.rand((2, n), generator=torch.Generator(device="cuda").manual_seed(3), dtype=torch.float64, device="cuda")
+    me = proc.sigma(x)
+    for fused in (True, False):
+        proc.set_fused_colour(fused)
+        tot, hel = proc.sigma(x, per_helicity=True)
+        assert torch.equal(proc.sigma(x), me) and torch.equal(tot, me)
+        assert torch.allclose(hel.sum(1) / proc.info["avg_factor"], me, rtol=1e-13, atol=0)
+        sel, h, c = proc.select(x, u[0].contiguous(), u[1].contiguous())
+        assert torch.equal(sel, me)
+        good = torch.tensor(proc.good_helicities_index(), device="cuda")
+        assert bool(torch.isin(h, good).all()) and bool(((c >= 0) & (c < proc.info["n_colors"])).all())
