@@ -35,3 +35,22 @@ def test_noalloc_equals_sigma(name, precision, n1, n2):
         assert torch.isfinite(got).all()
         assert torch.equal(got, want), (name, precision, n, (got - want).abs().max().item())
     proc.close()
+
+
+@pytest.mark.gpu
+def test_noalloc_chunks_cut_by_the_static_scratch():
+    """gg_ttggg in FP64 is the process whose chunks the static array cuts (the handle's own are larger): a batch of
+    two such chunks and 70 events takes three, of which the last is shorter and ragged."""
+    import torch
+    from paper_2210_11122_amd import Process
+
+    proc = Process("gg_ttggg")
+    fit = (256 << 20) // proc.info["bytes_per_event_scratch"] // 64 * 64
+    assert 64 <= fit < proc.info["chunk_events"]
+    n = 2 * fit + 70
+    print(f"noalloc gg_ttggg fp64 n={n}, chunks of at most {fit}", flush=True)
+    x = proc.rambo(13, W.sqrt_s("gg_ttggg"), n)
+    got = torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+    proc.sigma_noalloc(x, got)
+    assert torch.isfinite(got).all() and torch.equal(got, proc.sigma(x))
+    proc.close()
