@@ -145,3 +145,26 @@ def test_channel_weights_ee_mumu_z():
             wz = sum(abs(oracle.ee_z_amplitude(p[e], h, 2, W.PARAMS)) ** 2 for h in range(16))
             assert got[e, 0] == pytest.approx(me[e] * wg / (wg + wz), rel=1e-12)
             assert got[e, 1] == pytest.approx(me[e] * wz / (wg + wz), rel=1e-12)
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("name", ["gg_tt", "gg_ttg"])
+def test_channel_weights_of_a_large_batch_match_oracle(name, fused):
+    """every channel of three events, repeated to 4161: gg_ttg then takes the kernel that sums the helicities and
+    applies the weight itself or, with the separate colour sum, the one with all spins in a lane"""
+    print(f"case channel weights {name} large batch, fused={fused}", flush=True)
+    proc = make_process(name)
+    proc.set_fused_colour(fused)
+    lines = proc.diagrams()
+    p = oracle.rambo(41, W.sqrt_s(name), W.final_masses(name), 3)
+    i = np.arange(4161)
+    ev, ch = i % 3, (i // 3 % len(lines)).astype(np.int32)
+    got = proc.sigma_channel(torch.from_numpy(p[ev]).cuda(), torch.from_numpy(ch).cuda()).cpu().numpy()
+    me = proc.sigma(torch.from_numpy(p).cuda()).cpu().numpy()
+    K = Dg.colour_weights_K(name)
+    good = oracle.good_helicities(name, W.sqrt_s(name), W.final_masses(name), W.PARAMS)
+    want = np.empty((3, len(lines)))
+    for e in range(3):
+        Wd = Dg.diagram_weights(name, p[e], W.PARAMS, K, helicities=good)
+        want[e] = [me[e] * Wd[l] / sum(Wd.values()) for l in lines]
+    assert np.all(np.abs(got / want[ev, ch] - 1) < 1e-12)

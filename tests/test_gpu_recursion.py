@@ -128,7 +128,7 @@ def test_near_beam_events_keep_their_values():
         assert ok, (name, i, rel, spread)
 
 
-@pytest.mark.parametrize("name,n", [("ee_mumu", 257), ("gg_tt", 1), ("gg_tt", 4161)])
+@pytest.mark.parametrize("name,n", [("ee_mumu", 257), ("gg_tt", 1), ("gg_tt", 4161), ("gg_ttg", 4096), ("gg_ttg", 4161)])
 def test_channel_weights_do_not_depend_on_the_route(name, n):
     """The channel weights of a batch, of slices of it and with the separate colour sum: the same bits, with every
     diagram's id among the events, none (-1) and one past the last."""
