@@ -144,3 +144,22 @@ def test_channel_weights_do_not_depend_on_the_route(name, n):
     assert torch.equal(torch.cat(slices), whole)
     proc.set_fused_colour(False)
     assert torch.equal(proc.sigma_channel(x, ch), whole)
+
+
+@pytest.mark.parametrize("name,m_top,n", [("gg_ttg", 0.0, 65), ("gg_ttgg", 0.0, 65), ("gg_ttgg", W.M_TOP, 0)])
+def test_rows_and_flow_weights_massless_and_over_chunks(name, m_top, n):
+    """as test_rows_and_flow_weights_from_the_kernel, with massless tops, where some quark spins have no row and must
+    neither store one nor add to the flow weights, and (n = 0) for a batch of one chunk and a ragged one"""
+    from paper_2210_11122_amd import Process
+    proc = Process(name, m_top=m_top, alpha_em=W.ALPHA_EM, alpha_s=W.ALPHA_S)
+    n = n or proc.info["chunk_events"] + 37
+    print(f"case rows {name} m_top={m_top} n={n}", flush=True)
+    x = proc.rambo(8, W.sqrt_s(name), n)
+    u = torch.rand((2, n), generator=torch.Generator(device="cuda").manual_seed(6), dtype=torch.float64, device="cuda")
+    got = []
+    for fused in (True, False):
+        proc.set_fused_colour(fused)
+        got.append((proc.sigma(x), *proc.sigma(x, per_helicity=True), *proc.select(x, u[0].contiguous(), u[1].contiguous())))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    assert torch.equal(got[0][0], got[0][1]) and torch.equal(got[0][0], got[0][3])
