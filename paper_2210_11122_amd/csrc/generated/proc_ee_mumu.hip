@@ -12,7 +12,7 @@ constexpr int NSLOT = 0;
 template <class R, bool SDE, bool HS = false>
 __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mom, int64_t n_evt, int64_t ld, const signed char* __restrict__ hel, int n_good, double mt, double gs, R* __restrict__ jamp, const int* __restrict__ chan, double* __restrict__ sde, FusedColour fc)
 {
-    constexpr int WG = sizeof(R) == 8 ? 1 : 1;  // waves per workgroup
+    constexpr int WG = 1;  // waves per workgroup
     __shared__ double lds[4 * NPAR * 64];
     const int lane = threadIdx.x & 63;
     const int64_t w = xcd_remap(blockIdx.x, gridDim.x);
@@ -33,18 +33,17 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
     int lam[NPAR];
 #pragma unroll
     for (int i = 0; i < NPAR; ++i) lam[i] = hel[h * NPAR + i];
-    constexpr bool JAMPS = sizeof(R) == 4;  // FP64: the channel weights only
     constexpr int NW = 1;
     R Jr[2 * NW];
 #pragma unroll
     for (int s = 0; s < 2 * NW; ++s) Jr[s] = (R)0;
-#define JADD(s, ri, v) do { if constexpr (JAMPS) Jr[2 * (s) + (ri)] += (v); } while (0)
+#define JADD(s, ri, v) (Jr[2 * (s) + (ri)] += (v))
 #define JGET(s, ri) Jr[2 * (s) + (ri)]
     cx<R> a, sa;
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; if constexpr (sizeof(R) == 8) asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; } } while (0)
     const W4<R> w0 = ext_vbar<R>(PM(0), 0.0, lam[0]);
     const W4<R> w1 = ext_u<R>(PM(1), 0.0, lam[1]);
     const W4<R> w2 = ext_v<R>(PM(2), 0.0, lam[2]);
@@ -60,12 +59,8 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
             so[ld] = sde_all;
         }
     }
-    if constexpr (JAMPS) {
     if (fc.aop) {  // colour sum here: D |M_h|^2 of this lane's event, to [h][event]
         double me_h;
-        if constexpr (sizeof(R) == 8) {
-            me_h = colour_sum_regs<NC>(Jr, static_cast<const double*>(fc.aop));
-        } else {
         __syncthreads();
         R* Js = reinterpret_cast<R*>(lds);
         if constexpr (hsum) {
@@ -79,7 +74,6 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
             me_h = colour_sum_lds_h16<NC, Bf16Terms>(Js, static_cast<const __bf16*>(fc.aop), static_cast<const __bf16*>(fc.aop_lo), fc.lo_mask, lane);
         else
             me_h = colour_sum_lds_h16<NC, Fp16Terms>(Js, static_cast<const _Float16*>(fc.aop), static_cast<const _Float16*>(fc.aop), 0, lane);
-        }
         if constexpr (hsum) {  // the helicity sum: the separate kernel's groups and order
             __shared__ double red[16 * 64];
             red[hr * 64 + lane] = me_h;
@@ -110,7 +104,6 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
 #pragma unroll
         for (int s = 0; s < 2 * NC; ++s) o[s * ld] = jo[s];
     }
-    }
 #undef PM
 #undef GB
 #undef XW
@@ -123,7 +116,7 @@ __global__ __launch_bounds__(1024) void amp_kernel(const double* __restrict__ mo
 #undef SDEACC
 }
 template <class R>
-__global__ __launch_bounds__(64, sizeof(R) == 8 ? 2 : 3) void amp_lanes(const double* __restrict__ mom, int64_t n_evt, const signed char* __restrict__ hel, int n_good, double mt, double gs, FusedColour fc)
+__global__ __launch_bounds__(64, 3) void amp_lanes(const double* __restrict__ mom, int64_t n_evt, const signed char* __restrict__ hel, int n_good, double mt, double gs, FusedColour fc)
 {
     __shared__ double lds[4 * NPAR * 64];
     const int lane = threadIdx.x;
@@ -158,9 +151,7 @@ __global__ __launch_bounds__(64, sizeof(R) == 8 ? 2 : 3) void amp_lanes(const do
         JADD(0, 0, a.r); JADD(0, 1, a.i);
 #pragma unroll
         for (int k = 0; k < 2 * NC; ++k) asm volatile("" : "+v"(Jr[k]));  // the jamps as the other paths hold them
-        if constexpr (sizeof(R) == 8)
-            m += colour_sum_regs<NC>(Jr, static_cast<const double*>(fc.aop));
-        else if constexpr (NC == 1) {  // the 16-bit forms: one flow only
+        if constexpr (NC == 1) {  // the 16-bit forms: one flow only
             if (fc.form == ME_MIXED_BF16)
                 m += cs1_h16<Bf16Terms>(Jr[0], Jr[1], static_cast<const __bf16*>(fc.aop));
             else
@@ -187,7 +178,7 @@ static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const sig
 {
     if (fc && ((chan && sizeof(R) == 4) || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
     const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
-    constexpr int WG = sizeof(R) == 8 ? 1 : 1;  // waves (helicities) per workgroup
+    constexpr int WG = 1;  // waves (helicities) per workgroup
     int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);
     if (blocks == 0) return hipSuccess;
     if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion
@@ -196,7 +187,7 @@ static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const sig
     if (fc && fc->hsum_out) {  // the kernel also sums the helicities
         // batches large enough to fill the GPU with one lane per event (the mixed forms when
         // their one colour operand is exact in the 16-bit type, as the scalar form assumes)
-        if (n_evt >= 65536 && (sizeof(R) == 8 || (NC == 1 && !(fc->lo_mask & 1)))) {
+        if (n_evt >= 65536 && !(fc->lo_mask & 1)) {
             hipLaunchKernelGGL((amp_lanes<R>), dim3((unsigned)((n_evt + 63) / 64)), dim3(64), 0, st, mom, n_evt, hel, n_good, mt, gs, *fc);
             return hipGetLastError();
         }

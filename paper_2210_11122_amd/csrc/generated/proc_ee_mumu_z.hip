@@ -198,7 +198,7 @@ static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const sig
     if (fc && fc->hsum_out) {  // the kernel also sums the helicities
         // batches large enough to fill the GPU with one lane per event (the mixed forms when
         // their one colour operand is exact in the 16-bit type, as the scalar form assumes)
-        if (n_evt >= 65536 && (sizeof(R) == 8 || (NC == 1 && !(fc->lo_mask & 1)))) {
+        if (n_evt >= 65536 && (sizeof(R) == 8 || !(fc->lo_mask & 1))) {
             hipLaunchKernelGGL((amp_lanes<R>), dim3((unsigned)((n_evt + 63) / 64)), dim3(64), 0, st, mom, n_evt, hel, n_good, mt, gs, *fc);
             return hipGetLastError();
         }

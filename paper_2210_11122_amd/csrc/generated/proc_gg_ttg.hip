@@ -10,9 +10,9 @@ constexpr int NPAR = 5;
 constexpr int NC = 6;
 constexpr int NSLOT = 0;
 template <class R, bool SDE>
-__global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 : 3)) void amp_kernel(const double* __restrict__ mom, int64_t n_evt, int64_t ld, const signed char* __restrict__ hel, int n_good, double mt, double gs, R* __restrict__ jamp, const int* __restrict__ chan, double* __restrict__ sde, FusedColour fc)
+__global__ __launch_bounds__(64 * 4, 3) void amp_kernel(const double* __restrict__ mom, int64_t n_evt, int64_t ld, const signed char* __restrict__ hel, int n_good, double mt, double gs, R* __restrict__ jamp, const int* __restrict__ chan, double* __restrict__ sde, FusedColour fc)
 {
-    constexpr int WG = sizeof(R) == 8 ? 4 : 4;  // waves per workgroup
+    constexpr int WG = 4;  // waves per workgroup
     __shared__ double lds[4 * NPAR * 64];
     const int lane = threadIdx.x & 63;
     const int64_t w = xcd_remap(blockIdx.x, gridDim.x);
@@ -28,8 +28,8 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
 #pragma unroll
     for (int i = 0; i < NPAR; ++i) lam[i] = hel[h * NPAR + i];
     // 3 external wavefunctions computed once: in LDS, private to the lane, or in registers
-    constexpr int XWP[3] = {sizeof(R) == 8 ? 0 : 0, sizeof(R) == 8 ? 1 : 1, sizeof(R) == 8 ? 2 : -1};
-    constexpr int NXL = sizeof(R) == 8 ? 3 : 2;
+    constexpr int XWP[3] = {0, 1, -1};
+    constexpr int NXL = 2;
     __shared__ R xw_wg[NXL > 0 ? WG * NXL * 8 * 64 : 1];
     R* const xw = xw_wg + (threadIdx.x >> 6) * (NXL * 8 * 64);
     [[maybe_unused]] W4<R> xwr[3];
@@ -37,18 +37,17 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
     { const W4<R> t = ext_v<R>(PM(3), mt, lam[3]); if constexpr (XWP[1] >= 0) st_w4<R>(xw, XWP[1], lane, t); else xwr[1] = t; }
     { const W4<R> t = ext_vec<R>(PM(1), lam[1], false); if constexpr (XWP[2] >= 0) st_w4<R>(xw, XWP[2], lane, t); else xwr[2] = t; }
 #define XW(k) (XWP[k] >= 0 ? ld_w4<R>(xw, XWP[k], lane) : xwr[k])
-    constexpr bool JAMPS = sizeof(R) == 4;  // FP64: the channel weights only
     constexpr int NW = 6;
     R Jr[2 * NW];
 #pragma unroll
     for (int s = 0; s < 2 * NW; ++s) Jr[s] = (R)0;
-#define JADD(s, ri, v) do { if constexpr (JAMPS) Jr[2 * (s) + (ri)] += (v); } while (0)
+#define JADD(s, ri, v) (Jr[2 * (s) + (ri)] += (v))
 #define JGET(s, ri) Jr[2 * (s) + (ri)]
     cx<R> a, sa;
     int ch = -1;
     double sde_ch = 0.0, sde_all = 0.0;
     if constexpr (SDE) ch = (e < n_evt) ? chan[e] : -1;
-#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; if constexpr (sizeof(R) == 8) asm volatile("" : "+v"(sde_all), "+v"(sde_ch)); } } while (0)
+#define SDEACC(d, k) do { if constexpr (SDE) { const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; } } while (0)
     P4 m0_0 = PM(0);
     P4 m0_2 = PM(2);
     P4 m0_3 = PM(3);
@@ -260,12 +259,8 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
             so[ld] = sde_all;
         }
     }
-    if constexpr (JAMPS) {
     if (fc.aop) {  // colour sum here: D |M_h|^2 of this lane's event, to [h][event]
         double me_h;
-        if constexpr (sizeof(R) == 8) {
-            me_h = colour_sum_regs<NC>(Jr, static_cast<const double*>(fc.aop));
-        } else {
         __syncthreads();
         R* Js = reinterpret_cast<R*>(lds);
         if constexpr (WG > 1) {  // the momentum area is shared: a staging area per wave
@@ -279,7 +274,6 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
             me_h = colour_sum_lds_h16<NC, Bf16Terms>(Js, static_cast<const __bf16*>(fc.aop), static_cast<const __bf16*>(fc.aop_lo), fc.lo_mask, lane);
         else
             me_h = colour_sum_lds_h16<NC, Fp16Terms>(Js, static_cast<const _Float16*>(fc.aop), static_cast<const _Float16*>(fc.aop), 0, lane);
-        }
         if (live && e < n_evt) reinterpret_cast<double*>(jamp)[(int64_t)h * n_evt + e] = me_h;
         return;
     }
@@ -293,7 +287,6 @@ __global__ __launch_bounds__(64 * (sizeof(R) == 8 ? 4 : 4), (sizeof(R) == 8 ? 2 
         R* o = jamp + (int64_t)h * (2 * NC) * ld + e;
 #pragma unroll
         for (int s = 0; s < 2 * NC; ++s) o[s * ld] = jo[s];
-    }
     }
 #undef PM
 #undef GB
@@ -316,7 +309,7 @@ static hipError_t launch(const double* mom, int64_t n_evt, int64_t ld, const sig
 {
     if (fc && ((chan && sizeof(R) == 4) || !fc->aop || (sizeof(R) == 8) != (fc->form == ME_FP64))) return hipErrorInvalidValue;
     const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};
-    constexpr int WG = sizeof(R) == 8 ? 4 : 4;  // waves (helicities) per workgroup
+    constexpr int WG = 4;  // waves (helicities) per workgroup
     int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);
     if (blocks == 0) return hipSuccess;
     if constexpr (sizeof(R) == 8) {  // the jamps and the channel weights by recursion

@@ -120,13 +120,13 @@ __device__ __forceinline__ K4 half_plus(const K4& k, const K4& q)
 {
     return {fma(0.5, k.a, q.a), fma(0.5, k.b, q.b), fma(0.5, k.x, q.x), fma(0.5, k.y, q.y)};
 }
-// acc + V(A, B); AB = 2 A.B.  SGN = -1: acc - V(A, B)
-template <int SGN = 1, class TA, class TB>
+// acc + V(A, B); AB = 2 A.B
+template <class TA, class TB>
 __device__ __forceinline__ V4 vvv_acc(const V4& acc, const TA& A, const K4& ka, const TB& B, const K4& kb, C AB)
 {
     const K4 k = ka - kb;
-    const C h = (SGN * 0.5) * AB, s = dot2(A, half_plus(ka, kb)), t = dot2(B, half_plus(kb, ka));
-    V4 o = SGN > 0 ? axmy(axpy(acc, s, B), t, A) : axpy(axmy(acc, s, B), t, A);
+    const C h = 0.5 * AB, s = dot2(A, half_plus(ka, kb)), t = dot2(B, half_plus(kb, ka));
+    V4 o = axmy(axpy(acc, s, B), t, A);
     o.a = cadd_s(o.a, k.a, h);
     o.b = cadd_s(o.b, k.b, h);
     // c: h (x + i y), d: h (x - i y)
@@ -134,12 +134,11 @@ __device__ __forceinline__ V4 vvv_acc(const V4& acc, const TA& A, const K4& ka, 
     o.d = {fma(h.i, k.y, fma(h.r, k.x, o.d.r)), fma(-h.r, k.y, fma(h.i, k.x, o.d.i))};
     return o;
 }
-// acc + Q(A, B, D) from AB = 2 A.B, BD = 2 B.D, AD = 2 A.D; SGN as above
-template <int SGN = 1, class TA, class TB, class TD>
+// acc + Q(A, B, D) from AB = 2 A.B, BD = 2 B.D, AD = 2 A.D
+template <class TA, class TB, class TD>
 __device__ __forceinline__ V4 vvvv_acc(const V4& acc, const TA& A, const TB& B, const TD& D, C AB, C BD, C AD)
 {
-    const V4 o = axpy(axpy(acc, (SGN * 0.5) * BD, A), (SGN * 0.5) * AB, D);
-    return SGN > 0 ? axmy(o, AD, B) : axpy(o, AD, B);
+    return axmy(axpy(axpy(acc, 0.5 * BD, A), 0.5 * AB, D), AD, B);
 }
 __device__ __forceinline__ V4 operator-(const V4& x) { return {neg(x.a), neg(x.b), neg(x.c), neg(x.d)}; }
 __device__ __forceinline__ V4 zero4() { return {{0, 0}, {0, 0}, {0, 0}, {0, 0}}; }
@@ -155,29 +154,21 @@ __device__ __forceinline__ E4 gluon(const P4& p, int lam, bool outgoing, double 
 }
 __device__ __forceinline__ V4 spinor(const W4<double>& w) { return {w.c[0], w.c[1], w.c[2], w.c[3]}; }
 
-// acc + u gamma.G for a row spinor, acc + gamma.G s for a column spinor (SGN = -1: minus)
-template <int SGN = 1>
+// acc + u gamma.G for a row spinor, acc + gamma.G s for a column spinor
 __device__ __forceinline__ V4 row_acc(const V4& o, const V4& u, const V4& G)
 {
-    if (SGN > 0)
-        return {cfma(u.d, G.c, cfma(u.c, G.a, o.a)), cfma(u.d, G.b, cfma(u.c, G.d, o.b)),
-                cfms(u.b, G.c, cfma(u.a, G.b, o.c)), cfms(u.a, G.d, cfma(u.b, G.a, o.d))};
-    return {cfms(u.d, G.c, cfms(u.c, G.a, o.a)), cfms(u.d, G.b, cfms(u.c, G.d, o.b)),
-            cfma(u.b, G.c, cfms(u.a, G.b, o.c)), cfma(u.a, G.d, cfms(u.b, G.a, o.d))};
+    return {cfma(u.d, G.c, cfma(u.c, G.a, o.a)), cfma(u.d, G.b, cfma(u.c, G.d, o.b)),
+            cfms(u.b, G.c, cfma(u.a, G.b, o.c)), cfms(u.a, G.d, cfma(u.b, G.a, o.d))};
 }
 __device__ __forceinline__ V4 row(const V4& u, const V4& G)
 {
     return {cfma(u.d, G.c, cmul(u.c, G.a)), cfma(u.d, G.b, cmul(u.c, G.d)), cfms(u.b, G.c, cmul(u.a, G.b)),
             cfms(u.a, G.d, cmul(u.b, G.a))};
 }
-template <int SGN = 1>
 __device__ __forceinline__ V4 col_acc(const V4& o, const V4& G, const V4& s)
 {
-    if (SGN > 0)
-        return {cfms(G.d, s.d, cfma(G.b, s.c, o.a)), cfms(G.c, s.c, cfma(G.a, s.d, o.b)),
-                cfma(G.d, s.b, cfma(G.a, s.a, o.c)), cfma(G.b, s.b, cfma(G.c, s.a, o.d))};
-    return {cfma(G.d, s.d, cfms(G.b, s.c, o.a)), cfma(G.c, s.c, cfms(G.a, s.d, o.b)),
-            cfms(G.d, s.b, cfms(G.a, s.a, o.c)), cfms(G.b, s.b, cfms(G.c, s.a, o.d))};
+    return {cfms(G.d, s.d, cfma(G.b, s.c, o.a)), cfms(G.c, s.c, cfma(G.a, s.d, o.b)),
+            cfma(G.d, s.b, cfma(G.a, s.a, o.c)), cfma(G.b, s.b, cfma(G.c, s.a, o.d))};
 }
 __device__ __forceinline__ V4 col(const V4& G, const V4& s)
 {
@@ -185,14 +176,10 @@ __device__ __forceinline__ V4 col(const V4& G, const V4& s)
             cfma(G.b, s.b, cmul(G.c, s.a))};
 }
 // the same with a polarisation vector
-template <int SGN = 1>
 __device__ __forceinline__ V4 row_acc(const V4& o, const V4& u, const E4& G)
 {
-    if (SGN > 0)
-        return {cfma(u.d, G.c, scaled_add(o.a, G.a, u.c)), cfma(u.c, G.d, scaled_add(o.b, -G.a, u.d)),
-                cfms(u.b, G.c, scaled_add(o.c, -G.a, u.a)), cfms(u.a, G.d, scaled_add(o.d, G.a, u.b))};
-    return {cfms(u.d, G.c, scaled_add(o.a, -G.a, u.c)), cfms(u.c, G.d, scaled_add(o.b, G.a, u.d)),
-            cfma(u.b, G.c, scaled_add(o.c, G.a, u.a)), cfma(u.a, G.d, scaled_add(o.d, -G.a, u.b))};
+    return {cfma(u.d, G.c, scaled_add(o.a, G.a, u.c)), cfma(u.c, G.d, scaled_add(o.b, -G.a, u.d)),
+            cfms(u.b, G.c, scaled_add(o.c, -G.a, u.a)), cfms(u.a, G.d, scaled_add(o.d, G.a, u.b))};
 }
 __device__ __forceinline__ C times(double f, C x) { return {f * x.r, f * x.i}; }
 __device__ __forceinline__ V4 row(const V4& u, const E4& G)
@@ -200,14 +187,10 @@ __device__ __forceinline__ V4 row(const V4& u, const E4& G)
     return {cfma(u.d, G.c, times(G.a, u.c)), cfma(u.c, G.d, times(-G.a, u.d)), cfms(u.b, G.c, times(-G.a, u.a)),
             cfms(u.a, G.d, times(G.a, u.b))};
 }
-template <int SGN = 1>
 __device__ __forceinline__ V4 col_acc(const V4& o, const E4& G, const V4& s)
 {
-    if (SGN > 0)
-        return {cfms(G.d, s.d, scaled_add(o.a, -G.a, s.c)), cfms(G.c, s.c, scaled_add(o.b, G.a, s.d)),
-                cfma(G.d, s.b, scaled_add(o.c, G.a, s.a)), cfma(G.c, s.a, scaled_add(o.d, -G.a, s.b))};
-    return {cfma(G.d, s.d, scaled_add(o.a, G.a, s.c)), cfma(G.c, s.c, scaled_add(o.b, -G.a, s.d)),
-            cfms(G.d, s.b, scaled_add(o.c, -G.a, s.a)), cfms(G.c, s.a, scaled_add(o.d, G.a, s.b))};
+    return {cfms(G.d, s.d, scaled_add(o.a, -G.a, s.c)), cfms(G.c, s.c, scaled_add(o.b, G.a, s.d)),
+            cfma(G.d, s.b, scaled_add(o.c, G.a, s.a)), cfma(G.c, s.a, scaled_add(o.d, -G.a, s.b))};
 }
 __device__ __forceinline__ V4 col(const E4& G, const V4& s)
 {

@@ -56,8 +56,9 @@ PREFETCH_MOMENTA = True
 # and keep the compiler from summing them before the step that uses them
 PIN_MOMENTA = True
 # name -> minimum waves per SIMD asked of the compiler for the (FP64, FP32) amplitude kernels
-# (the second __launch_bounds__ argument: it caps the registers per lane at 512 / waves)
-MIN_WAVES = {"gg_tt": (4, 6), "gg_ttg": (2, 3), "gg_ttgg": (1, 2), "gg_ttggg": (1, 2)}
+# (the second __launch_bounds__ argument: it caps the registers per lane at 512 / waves; None, here and
+# below: there is no FP64 instance)
+MIN_WAVES = {"gg_tt": (None, 6), "gg_ttg": (None, 3), "gg_ttgg": (1, 2), "gg_ttggg": (1, 2)}
 # name -> waves per workgroup (FP64, FP32 kernels): consecutive helicities of one 64-event block
 # that share the staged momenta (less LDS per wave where LDS, not registers, limits the waves).
 # With several waves per group, FP32 kernels with register jamps stage them for the colour sum in
@@ -65,7 +66,7 @@ MIN_WAVES = {"gg_tt": (4, 6), "gg_ttg": (2, 3), "gg_ttgg": (1, 2), "gg_ttggg": (
 # waves per SIMD) 0.272 -> 0.252 ms; gg_ttg mixed per 2^20 2.86 -> 2.62 ms.
 # The test process gg_gg has six good helicities, so its second group of four carries two spare
 # waves: its parity tests cover that path.
-WAVES_PER_GROUP = {"gg_tt": (4, 4), "gg_ttg": (4, 4), "gg_ttgg": (4, 4), "gg_ttggg": (4, 8), "gg_gg": (4, 4)}
+WAVES_PER_GROUP = {"gg_tt": (None, 4), "gg_ttg": (None, 4), "gg_ttgg": (4, 4), "gg_ttggg": (4, 8), "gg_gg": (4, 4)}
 # processes whose programs keep no external gluon wavefunction in registers: the workgroup
 # stages each event's gluon bases in LDS once (helas.hpp, stage_gluon_basis) and every use
 # rebuilds the polarisation vector from there.  It removes the FP64 kernels' spills but costs
@@ -563,7 +564,7 @@ class Process:
                 out.append(f"    a = {fn}({', '.join(args)});")
                 flops[0] += amp_flops(fn)
                 # a shared vertex feeds the jamps only: unpinned, it is left out where none are kept
-                shared = len(grp) > 1 and self.name in RECURSION
+                shared = len(grp) > 1 and self.name in RECURSION and self.name not in CHANNELS_IN_RECURSION
                 out.append("    if constexpr (JAMPS) pin_cx<R>(a);" if shared else "    pin_cx<R>(a);")
                 if self.fd_index is not None:
                     if len(grp) == 1:
@@ -872,7 +873,7 @@ class Process:
                      "return hipErrorInvalidValue;")
             L.append("    const FusedColour none{nullptr, nullptr, 0, 0, nullptr, 0.0, 1};")
         g64, g32 = WAVES_PER_GROUP.get(self.name, (1, 1))
-        L.append(f"    constexpr int WG = sizeof(R) == 8 ? {g64} : {g32};  // waves (helicities) per workgroup")
+        L.append(f"    constexpr int WG = {self._by_precision(g64, g32)};  // waves (helicities) per workgroup")
         if nm in RECURSION and nm not in CHANNELS_IN_RECURSION:
             L.append("    if (sizeof(R) == 8) hel = hg.hel, n_good = hg.n_rows;  // the weights of one helicity of each pair")
         L.append("    int64_t blocks = ((n_evt + 63) / 64) * ((n_good + WG - 1) / WG);")
@@ -909,7 +910,10 @@ class Process:
                     if nm in LANE_PER_EVENT:
                         L.append("        // batches large enough to fill the GPU with one lane per event (the mixed forms when")
                         L.append("        // their one colour operand is exact in the 16-bit type, as the scalar form assumes)")
-                        L.append(f"        if (n_evt >= {LANE_MIN_EVENTS} && (sizeof(R) == 8 || (NC == 1 && !(fc->lo_mask & 1)))) {{")
+                        exact = "!(fc->lo_mask & 1)" if nc == 1 else "false"
+                        if nm not in CHANNELS_IN_RECURSION:
+                            exact = f"(sizeof(R) == 8 || {exact})"
+                        L.append(f"        if (n_evt >= {LANE_MIN_EVENTS} && {exact}) {{")
                         L.append("            hipLaunchKernelGGL((amp_lanes<R>), dim3((unsigned)((n_evt + 63) / 64)), dim3(64), 0, st, "
                                  "mom, n_evt, hel, n_good, mt, gs, *fc);")
                         L.append("            return hipGetLastError();")
@@ -961,6 +965,10 @@ class Process:
         L.append("}  // namespace me")
         return "\n".join(L) + "\n"
 
+    def _by_precision(self, fp64, fp32):
+        """a constant of the kernel templates that differs by precision; one value where no FP64 instance exists"""
+        return str(fp32) if self.name in CHANNELS_IN_RECURSION else f"sizeof(R) == 8 ? {fp64} : {fp32}"
+
     def _kernel_text(self, kname, body, nwin, mode, jamps_in_lds, jamp_mode, first=True, fused=False):
         """one amplitude kernel: momenta staging, helicity signs, jamp storage, body, output.
         mode 'jamps': the NC jamps are written at the end, layout [h][2c + re/im][column];
@@ -972,8 +980,9 @@ class Process:
         sums of the segments before them."""
         L = []
         hsum = fused and self.name in HEL_SUM_IN_KERNEL
-        # the FP64 jamps come from the recursion: the FP64 instance sums the channel weights only
-        rec = self.name in RECURSION
+        # the FP64 jamps come from the recursion: the FP64 instance, if there is one, sums the channel weights only
+        no_fp64 = self.name in CHANNELS_IN_RECURSION
+        rec = self.name in RECURSION and not no_fp64
         # HS: the instance that also sums the helicities (its workgroup holds an event block's
         # good helicities; the LDS it needs for that is only in this instance)
         L.append("template <class R, bool SDE, bool HS = false>" if hsum else "template <class R, bool SDE>")
@@ -981,16 +990,17 @@ class Process:
         g64, g32 = WAVES_PER_GROUP.get(self.name, (1, 1))
         if hsum and (g64, g32) != (1, 1):
             raise ValueError("the helicity sum in the kernel sizes the workgroup by the good helicities")
-        threads = "64" if (g64, g32) == (1, 1) else f"64 * (sizeof(R) == 8 ? {g64} : {g32})"
+        term = self._by_precision if no_fp64 else (lambda a, b: f"({self._by_precision(a, b)})")
+        threads = "64" if (g64, g32) == (1, 1) else f"64 * {term(g64, g32)}"
         if hsum:
             threads = "1024"   # up to 16 helicity waves of one event block
-        bounds = threads if (w64, w32) == (1, 1) else f"{threads}, (sizeof(R) == 8 ? {w64} : {w32})"
+        bounds = threads if (w64, w32) == (1, 1) else f"{threads}, {term(w64, w32)}"
         L.append(f"__global__ __launch_bounds__({bounds}) void {kname}(const double* __restrict__ mom, int64_t n_evt, "
                  "int64_t ld, const signed char* __restrict__ hel, int n_good, double mt, double gs, "
                  "R* __restrict__ jamp, const int* __restrict__ chan, double* __restrict__ sde"
                  + (", FusedColour fc)" if fused else ")"))
         L.append("{")
-        L.append(f"    constexpr int WG = sizeof(R) == 8 ? {g64} : {g32};  // waves per workgroup")
+        L.append(f"    constexpr int WG = {self._by_precision(g64, g32)};  // waves per workgroup")
         L.append("    __shared__ double lds[4 * NPAR * 64];")
         L.append("    const int lane = threadIdx.x & 63;")
         L.append("    const int64_t w = xcd_remap(blockIdx.x, gridDim.x);")
@@ -1035,10 +1045,10 @@ class Process:
                     pos[prec].append(n if item[j] else -1)
                     n += 1 if item[j] else 0
                 pos[prec + "n"] = n
-            xwp = ", ".join(f"sizeof(R) == 8 ? {a} : {b}" for a, b in zip(pos["64"], pos["32"]))
+            xwp = ", ".join(self._by_precision(a, b) for a, b in zip(pos["64"], pos["32"]))
             L.append(f"    // {nx} external wavefunctions computed once: in LDS, private to the lane, or in registers")
             L.append(f"    constexpr int XWP[{nx}] = {{{xwp}}};")
-            L.append(f"    constexpr int NXL = sizeof(R) == 8 ? {pos['64n']} : {pos['32n']};")
+            L.append(f"    constexpr int NXL = {self._by_precision(pos['64n'], pos['32n'])};")
             L.append("    __shared__ R xw_wg[NXL > 0 ? WG * NXL * 8 * 64 : 1];")
             L.append("    R* const xw = xw_wg + (threadIdx.x >> 6) * (NXL * 8 * 64);")
             L.append(f"    [[maybe_unused]] W4<R> xwr[{nx}];")
@@ -1109,7 +1119,9 @@ class Process:
         # changes how the compiler contracts, and so rounds, the amplitudes formed for the weights alone
         L.append("#define SDEACC(d, k) do { if constexpr (SDE) { "
                  "const double w_ = (k) * ((double)a.r * (double)a.r + (double)a.i * (double)a.i); "
-                 "sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0; if constexpr (sizeof(R) == 8) asm volatile(\"\" : \"+v\"(sde_all), \"+v\"(sde_ch)); } } while (0)")
+                 "sde_all += w_; sde_ch += ((d) == ch) ? w_ : 0.0;"
+                 + ("" if no_fp64 else " if constexpr (sizeof(R) == 8) asm volatile(\"\" : \"+v\"(sde_all), \"+v\"(sde_ch));")
+                 + " } } while (0)")
         L.extend(body)
         L.append("    if constexpr (SDE) {")
         L.append("        if (live && e < n_evt) {")
@@ -1128,7 +1140,8 @@ class Process:
             if fused:
                 L.append("    if (fc.aop) {  // colour sum here: D |M_h|^2 of this lane's event, to [h][event]")
                 L.append("        double me_h;")
-                if not jamps_in_lds and self.nc <= 6:
+                scalar = not jamps_in_lds and self.nc <= 6 and not no_fp64
+                if scalar:
                     # up to six flows in FP64: the scalar colour sum from the registers
                     L.append("        if constexpr (sizeof(R) == 8) {")
                     L.append("            me_h = colour_sum_regs<NC>(Jr, static_cast<const double*>(fc.aop));")
@@ -1162,7 +1175,7 @@ class Process:
                 L.append("        else")
                 L.append(f"            me_h = colour_sum_lds_h16<NC, Fp16Terms>({src}, static_cast<const _Float16*>(fc.aop), "
                          "static_cast<const _Float16*>(fc.aop), 0, lane);")
-                if not jamps_in_lds and self.nc <= 6:
+                if scalar:
                     L.append("        }")
                 if hsum:
                     L.append("        if constexpr (hsum) {  // the helicity sum: the separate kernel's groups and order")
@@ -1212,7 +1225,7 @@ class Process:
             raise ValueError("the lane-per-event kernel sums at most six colour flows in registers")
         L = []
         L.append("template <class R>")
-        L.append(f"__global__ __launch_bounds__(64, sizeof(R) == 8 ? {LANE_MIN_WAVES[0]} : {LANE_MIN_WAVES[1]}) void amp_lanes("
+        L.append(f"__global__ __launch_bounds__(64, {self._by_precision(*LANE_MIN_WAVES)}) void amp_lanes("
                  "const double* __restrict__ mom, int64_t n_evt, "
                  "const signed char* __restrict__ hel, int n_good, double mt, double gs, FusedColour fc)")
         L.append("{")
@@ -1253,9 +1266,12 @@ class Process:
         L += ["    " + ln for ln in body]
         L.append("#pragma unroll")
         L.append("        for (int k = 0; k < 2 * NC; ++k) asm volatile(\"\" : \"+v\"(Jr[k]));  // the jamps as the other paths hold them")
-        L.append("        if constexpr (sizeof(R) == 8)")
-        L.append("            m += colour_sum_regs<NC>(Jr, static_cast<const double*>(fc.aop));")
-        L.append("        else if constexpr (NC == 1) {  // the 16-bit forms: one flow only")
+        if self.name in CHANNELS_IN_RECURSION:
+            L.append("        if constexpr (NC == 1) {  // the 16-bit forms: one flow only")
+        else:
+            L.append("        if constexpr (sizeof(R) == 8)")
+            L.append("            m += colour_sum_regs<NC>(Jr, static_cast<const double*>(fc.aop));")
+            L.append("        else if constexpr (NC == 1) {  // the 16-bit forms: one flow only")
         L.append("            if (fc.form == ME_MIXED_BF16)")
         L.append("                m += cs1_h16<Bf16Terms>(Jr[0], Jr[1], static_cast<const __bf16*>(fc.aop));")
         L.append("            else")
