@@ -57,21 +57,33 @@ def timed_steps(proc, x, steps, warmup, torch):
     return out, (t1 - t0) * 1e3 / steps, lat, ms_amp, ms_cs, n_amp, n_cs
 
 
-def kernel_source_hash(process):
-    """hash of the sources that define the amplitude kernel of `process` and its launch (the
-    helper headers and the generated file up to the process descriptor)"""
+def kernel_source_hash(process, csrc=os.path.join(ROOT, "paper_2210_11122_amd", "csrc")):
+    """hash of the sources that define the amplitude kernels of `process` and their launch: the
+    generated file up to the process descriptor, the FP64 kernel's file and every header of csrc that
+    either includes, directly or through another"""
     import hashlib
-    csrc = os.path.join(ROOT, "paper_2210_11122_amd", "csrc")
-    h = hashlib.sha256()
-    with open(os.path.join(csrc, "generated", f"proc_{process}.hip"), "rb") as fh:
-        gen = fh.read().split(b"const ProcessDesc* process_")[0]
-    heads = ["helas.hpp"] + (["colorsum.hpp"] if b'#include "../colorsum.hpp"' in gen else [])
+    import re
+    texts = {}
+
+    def read(path):
+        path = os.path.normpath(path)
+        if path in texts:
+            return
+        with open(path, "rb") as fh:
+            texts[path] = fh.read().split(b"const ProcessDesc* process_")[0] if path.endswith(".hip") else fh.read()
+        for name in re.findall(rb'#include "([^"]+)"', texts[path]):
+            for base in (os.path.dirname(path), csrc):
+                found = os.path.join(base, name.decode())
+                if os.path.exists(found):
+                    read(found)
+                    break
+
+    read(os.path.join(csrc, "generated", f"proc_{process}.hip"))
     if os.path.exists(os.path.join(csrc, f"rec_{process}.hip")):   # the FP64 kernel
-        heads += [f"rec_{process}.hip", "recursion.hpp", "flows.hpp"]
-    for name in heads:
-        with open(os.path.join(csrc, name), "rb") as fh:
-            h.update(fh.read())
-    h.update(gen)
+        read(os.path.join(csrc, f"rec_{process}.hip"))
+    h = hashlib.sha256()
+    for path in sorted(texts, key=lambda p: os.path.relpath(p, csrc)):
+        h.update(texts[path])
     return h.hexdigest()[:16]
 
 

@@ -33,3 +33,29 @@ def test_more_than_one_gpu_is_refused():
                        text=True, timeout=120, cwd=root)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout == ""
+
+
+def test_kernel_hash_covers_every_included_header(tmp_path):
+    """committed HBM counters are dropped when any source of the amplitude kernels has changed, also one that is
+    included through another; not for a source that the kernels do not include"""
+    import os
+    import shutil
+    csrc = os.path.join(bench.ROOT, "paper_2210_11122_amd", "csrc")
+    copy = str(tmp_path / "csrc")
+    shutil.copytree(csrc, copy)
+    used = {"gg_ttgg": ["generated/proc_gg_ttgg.hip", "rec_gg_ttgg.hip", "recursion.hpp", "flows.hpp", "helas.hpp",
+                        "colorsum.hpp", "process.hpp", "generated/colour_blocks.hpp"],
+            "gg_ttg": ["rec_gg_ttg.hip", "recursion.hpp", "colorsum.hpp", "process.hpp", "generated/channels.hpp"],
+            "gg_ttggg": ["rec_gg_ttggg.hip", "recursion.hpp", "flows.hpp", "helas.hpp", "process.hpp"]}
+    for process, names in used.items():
+        want = bench.kernel_source_hash(process)
+        assert bench.kernel_source_hash(process, copy) == want
+        for name in names + ["rambo.hpp"]:
+            path = os.path.join(copy, *name.split("/"))
+            with open(path, "rb") as fh:
+                text = fh.read()
+            with open(path, "wb") as fh:
+                fh.write(b"// another line\n" + text)
+            assert (bench.kernel_source_hash(process, copy) == want) == (name == "rambo.hpp"), (process, name)
+            with open(path, "wb") as fh:
+                fh.write(text)
