@@ -224,7 +224,8 @@ int me_profile(me_handle *h, int enable, double *ms_amp, double *ms_colour, int6
  * so each helicity's |M_h|^2 is bitwise the same) and writes one FP64 value per (event,
  * evaluated helicity combination) instead of the jamps; a second kernel sums the helicities in the
  * separate kernel's groups and order (ee_mumu, ee_mumu_z, and in FP64 gg_tt and gg_ttg above 4096
- * events, sum them in the same kernel, which also applies the channel weights of me_sigma_channel).  0: always the separate colour-sum kernel.  Both settings, and me_sigma_hel and
+ * events, sum them in the same kernel; in FP64 that of ee_mumu, gg_tt and gg_ttg also applies the channel
+ * weights of me_sigma_channel).  0: always the separate colour-sum kernel.  Both settings, and me_sigma_hel and
  * me_sigma_select (which take |M_h|^2 and flow weights from the kernel in FP64 gg_ttgg, me_sigma_hel also in
  * FP64 gg_ttg, and else from the jamps), give bitwise the same |M|^2.
  * ME_EINVAL for an unknown option or a value other than 0 or 1. */

@@ -1,9 +1,10 @@
 // me_abi.cpp -- the C ABI of libme.so (declared in include/me.h).
 //
-// A handle owns the resident tables of one process: the colour matrix as matrix-core
-// operands, the list of helicities that contribute, and one jamp scratch buffer per
-// stream.  me_sigma runs, chunk by chunk, the generated amplitude kernel (one lane per
-// (event, helicity)) and the colour-sum kernel (matrix cores, helicity sum in FP64).
+// A handle owns the resident tables of one process: the colour matrix as operands, the list of helicities
+// that contribute (in FP64 also as pairs of opposite ones), and one scratch buffer per stream.  me_sigma runs,
+// chunk by chunk, the amplitude kernels (FP64: the recursion of rec_*.hip; mixed forms, gg_gg and ee_mumu_z: the
+// generated diagram program, one lane per (event, helicity)) and, where these do not end with them, the colour
+// sum (FP64 in the lanes, mixed on the matrix cores) and the helicity sum (FP64).
 #include "me.h"
 
 #include <hip/hip_runtime.h>
@@ -49,9 +50,9 @@ struct Scratch {
     size_t bytes = 0;
 };
 
-// Two internal streams per (device, caller stream): the chunks of a process with segment
-// kernels alternate between them, so that the reduction of one chunk (bound by HBM) runs beside
-// the segment kernels of the next (bound by the VALU).  One pair serves every handle and lives
+// Two internal streams per (device, caller stream): the chunks of gg_ttggg alternate between them, so
+// that the parts of one chunk that wait for memory (mixed: the reduction; FP64: the colour sum and the level
+// kernels) run beside the arithmetic of the next.  One pair serves every handle and lives
 // until the process ends: a pair per handle would crowd the device's few hardware queues, and
 // streams that share a queue run one after the other.
 struct Helpers {
@@ -895,11 +896,11 @@ int sigma_piped(me_handle* h, const double* momenta, int64_t n_evt, double* out,
 }
 
 // How a call of n_evt events runs: equal chunks no larger than the handle's chunk; for processes
-// with segment kernels, the plain |M|^2 of more than one chunk alternates its chunks between two
+// with segment kernels in their mixed forms (in FP64 too), the plain |M|^2 of more than one chunk alternates its chunks between two
 // internal streams, each with a scratch buffer of its own (full-size chunks keep the short segment
 // launches several rounds of waves deep).  Scratch per event of a chunk: the plain |M|^2 of a
-// kernel with the colour sum inside keeps one double per (event, helicity); otherwise the jamps
-// (and partial slots) of every helicity plus the helicity-group sums, and `extra` bytes.
+// kernel with the colour sum inside keeps one double per (event, row); otherwise the jamps
+// (and partial slots) of every row plus the helicity-group sums, and `extra` bytes.
 struct CallPlan {
     int64_t chunk;
     bool piped;

@@ -5,9 +5,6 @@
 
 namespace me {
 
-// chan == nullptr: plain kernels; otherwise chan[n_evt] channel ids and sde[row][2][ld] the
-// per-lane single-diagram sums (channel, all).  A row of the jamps is a good helicity, or a pair of them
-// (HelicityGroups)
 // The colour sum inside the amplitude kernel (processes with fused_colour): the operand tables
 // of the separate colour-sum kernel of the same form.  With a FusedColour the kernel writes
 // D |M_h|^2 as doubles to ((double*)jamp)[row * n_evt + event] instead of the jamps.
@@ -18,7 +15,7 @@ struct FusedColour {
     int form;            // ME_FP64, ME_MIXED_FP16 or ME_MIXED_BF16 (me.h)
     // processes with hel_sum_in_kernel or lane_min_f64 / lane_min_mixed: if hsum_out is set, the kernel also
     // sums the good helicities (one workgroup holding all of an event block's, or one lane per
-    // event for batches of at least that size), in groups of hel_per_group from the first
+    // event for batches of at least that size, or in FP64 the forms of rec_*.hip), in groups of hel_per_group from the first
     // (the order of the separate helicity-sum kernel), times hsum_scale, into hsum_out[event];
     // nothing goes to the jamp scratch
     double* hsum_out;
@@ -60,7 +57,9 @@ __device__ __forceinline__ double members_of(const int2* __restrict__ members, i
     return (m.x >= 0 ? 1.0 : 0.0) + (m.y >= 0 ? 1.0 : 0.0);
 }
 
-// fc: null, or the fused colour sum (then chan must be null, but for channel_in_kernel)
+// The jamps jamp[row][2 flow + re/im][ld]; a row is a good helicity, or a pair of them (HelicityGroups).
+// chan: null, or chan[n_evt] channel ids, for which the per-lane single-diagram sums (channel, all) go to
+// sde[row][2][ld].  fc: null, or the fused colour sum (then chan must be null, but for channel_in_kernel)
 typedef hipError_t (*amp_launch_f64)(const double* mom, int64_t n_evt, int64_t ld, const signed char* hel,
                                      int n_good, double mt, double g, double* jamp, const int* chan, double* sde,
                                      const FusedColour* fc, const HelicityGroups& hg, hipStream_t st);

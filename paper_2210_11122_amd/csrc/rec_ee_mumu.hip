@@ -3,9 +3,10 @@
 // The amplitude is the product of an electron and a muon current over s.  The spinors and currents
 // of each helicity are formed once per event and every good combination is one product of two
 // currents; the colour sum (one flow) and the helicity sum stay in the lane, one launch for any
-// batch size.  2^20 events 69 -> 37 us per call (the bytes of momenta and results take 28 us at the
-// rate of a large copy); 8192 events 8 us, host time.  (Cut to 128 registers for four waves per SIMD
-// it spills.)
+// batch size.  2^20 events 92 -> 51 us per call with the momenta read from HBM (2.8 TB/s; the bytes take
+// 28 us at the rate of a large copy), 69 -> 36 us where one batch is evaluated again and again and stays in
+// the 256 MB last-level cache; 8192 events 8.6 us, host time.  (Cut to 128 registers for four waves per
+// SIMD it spills.)
 #include "colorsum.hpp"
 #include "process.hpp"
 #include "recursion.hpp"

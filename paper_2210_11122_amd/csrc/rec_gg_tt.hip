@@ -4,8 +4,9 @@
 // the polarisation vectors, strings and two-gluon currents of each helicity are formed once and shared
 // by the combinations that have them in common (1.2k FP64 instructions per event; the diagram program
 // took about 1k for each of the 12 good combinations).  The colour sum and the helicity sum stay in the
-// lane: one launch, also for the smallest batch.  2^19 events 118.7 -> 38.1 us per call (67.4 with all
-// 16 evaluated; the bytes of momenta and results take 14 us), 256 events 11.2 -> 8.1 us (host time).
+// lane: one launch, also for the smallest batch.  2^19 events 119 -> 37 us per call (67 with all 16
+// evaluated; 49 us with the momenta read from HBM and not from the last-level cache; the bytes of momenta and
+// results take 14 us), 256 events 11.7 -> 8.6 us (host time).
 // The channel weight is applied in the same launch: 65000 events 43.5 -> 12.3 us per call (its sums are kept per row
 // and added in the rows' order at the end; 2^19 events 43.8 us, 43.7 added as they came).
 #include "colorsum.hpp"

@@ -5,8 +5,8 @@
 // hold the four configurations of 64 events and sum the helicities, with the channel weight where one is asked
 // for (its diagrams' squares are formed from the same strings).  The diagram program took one lane per
 // (event, helicity) and 24 of them made each gluon current anew.  Bound by FP64 issue: 2^20 events
-// 2842 -> 852 us per call (1519 with all eight gluon configurations), 100003 events with channel weights
-// 423 -> 148 us; the bytes (176 MB) take 35 us.
+// 2844 -> 862 us per call (1519 with all eight gluon configurations), 100003 events with channel weights
+// 423 -> 140 us; the bytes (176 MB) take 35 us.
 #include "colorsum.hpp"
 #include "generated/channels.hpp"
 #include "process.hpp"
@@ -39,8 +39,8 @@ __global__ __launch_bounds__(256, N == 1 ? 2 : 1) void amp_rec(const double* __r
     __shared__ double lds[4 * NPAR * 64];
     __shared__ double me_lds[HSUM ? MAX_ROWS * 64 : 1];
     // With the channel weights summed here (spills) the propagators of two gluons are made once for the
-    // four waves and read from LDS: 100003 events 142 us per call, 148 with them made in each lane; without
-    // the weights in each lane (2^20 events 846 us, 859 from LDS)
+    // four waves and read from LDS: 100003 events take 4 % less than with them made in each lane.  Without
+    // the weights they are made in each lane: from LDS 2^20 events take 1.5 % more
     constexpr bool SHARED_PROPS = HSUM && SDE;
     __shared__ double prop_lds[SHARED_PROPS ? 3 * 64 : 1];
     __shared__ double sde_lds[HSUM && SDE ? 2 * MAX_ROWS * 64 : 1];

@@ -5,10 +5,10 @@
 // flows that have gluon 0 among the first two, or among the last two, for one of the four quark spin
 // configurations.  Bound by FP64 issue (3.4k vector instructions per wave; the issue slots are 63 % full)
 // with two waves per SIMD, for which the 158 KB of LDS leave room.  2^19 events: the diagram program
-// 20.6 ms per call, 4.95 with four waves that made their strings themselves, 4.85 now.  The
+// 20.6 ms per call, 4.9 now (2 % more with four waves that made their strings themselves).  The
 // kernel also gives the helicities' |M_h|^2 and the flows' weights, so neither call takes the jamps through
 // memory: 20000 events with the per-helicity output 260 -> 216 us, with selection 326 -> 265 us (9973
-// events 192 -> 151).
+// events 192 -> 149).
 #include "colorsum.hpp"
 #include "process.hpp"
 #include "recursion.hpp"

@@ -2,11 +2,12 @@
 //
 // Five gluons have 65 independent currents per helicity configuration, and a current of k gluons
 // depends on their k helicities only.  So the currents of two to four gluons and the strings of
-// one and two gluons of either quark are computed once per event into memory (1054 vectors, 67 KB
-// per event, against 128 helicity configurations that use about 150 of them each), level by level,
-// one lane per event.  Two kernels then work per (event, helicity): five_currents contracts the
-// 24 independent currents of all five gluons with the quark currents, and amp_rec forms the 120
-// flows, 24 at a time (those with the same last gluon), each stored once.
+// one and two gluons of either quark are computed once per event into memory, level by level,
+// one lane per event: 737 vectors (47 KB) per event, of which each of the 64 pairs of helicity
+// configurations uses about 150.  (The slots are numbered for both helicities of every gluon, 1054 of 64 B;
+// the 317 with gluon 0 at helicity + are reserved and stay unused.)  Two kernels then work per (event, pair):
+// five_currents contracts the 24 independent currents of all five gluons with the quark currents, and amp_rec
+// forms the 120 flows, 24 at a time (those with the same last gluon), each stored once.
 //
 // Against the 14 diagram segments (247k flops per lane, 977 partial jamp sums through memory):
 // 2^17 events, colour sum included, 208.9 -> 24.4 ms per call (43.8 with all 128 helicities

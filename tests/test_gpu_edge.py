@@ -143,3 +143,15 @@ def test_massless_mhv_helicities_closed_form(name, n_evt):
             assert abs(hel[e, col[h]] / want - 1) <= 1e-11, (name, e, h, hel[e, col[h]], want)
             checked += 1
     assert checked == n_evt * (2 * (n - 2) if n == 4 else 4 * (n - 2))
+
+
+@pytest.mark.parametrize("name", ["gg_ttg", "gg_ttgg", "gg_ttggg"])
+def test_most_singular_events_of_a_batch(name):
+    """of 20000 RAMBO events the three with a final gluon closest to a beam and the three with two final gluons
+    closest to each other (smallest 2 k.k'): P^2 of the pair has lost most digits there"""
+    p = oracle.rambo(51, W.sqrt_s(name), W.final_masses(name), 20000)
+    dot = lambda i, j: np.abs(p[:, i, 0] * p[:, j, 0] - (p[:, i, 1:] * p[:, j, 1:]).sum(-1))
+    gluons = range(4, p.shape[1])
+    groups = [[(i, j) for i in (0, 1) for j in gluons], [(i, j) for i in gluons for j in gluons if i < j]]
+    pick = [np.argsort(np.min([dot(i, j) for i, j in g], axis=0))[:3] for g in groups if g]
+    check(name, list(p[np.concatenate(pick)]))
